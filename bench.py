@@ -52,8 +52,15 @@ def within_budget(args, seconds, what):
     return False
 
 
+def transform_grid(nd, gw, gc):
+    """Points per axis of the library's transforms: the smallest alias-free multiple of 4."""
+    rw, rc = int(np.abs(gw).max()), int(np.abs(gc).max())
+    return min(nd, -(-max(2 * rw + rc + 1, 2 * rc + 1, 16) // 4) * 4)
+
+
 def flops_model(nd, k, ng, npair, nband, with_inverse=True):
-    """Algorithmic flop counts: pruned forward transform per pair (three passes over
+    """Algorithmic flop counts of a build on an nd^3 grid (the GPU's: transform_grid, the grid its
+    transforms run on; the oracle's: the stated grid): pruned forward transform per pair (three passes over
     N, N K/N_d and N K^2/N_d^2 points at 5 n log2 n), the product (6 N), the band
     transforms (5 N log2 N each), the Hermitian contraction (4 NG^2 per pair) and the static
     inverse by Hermitian sweeps (a rank-64 update of the lower triangle per 64 pivots, 4 NG^3)."""
@@ -68,8 +75,8 @@ def flops_model(nd, k, ng, npair, nband, with_inverse=True):
             "eps_inv": inverse, "total": (planes + finish + contract) * npair + band * nband + inverse}
 
 
-KERNEL_OF_STAGE = {"planes": ("pair_transform.hip", ("k_pair_planes<{t}, 72, 8, 15", "k_pair_planes_split<{t}, 72, 8, 15")),
-                   "finish": ("pair_transform.hip", "k_pair_finish<{t}, 72, 8, 15"),
+KERNEL_OF_STAGE = {"planes": ("pair_transform.hip", "k_pair_planes<{t}, 7"),
+                   "finish": ("pair_transform.hip", "k_pair_finish<{t}, 7"),
                    "contract": ("contract.hip", "k_contract_batch<{m},")}
 
 
@@ -187,7 +194,7 @@ def run_headline(args, torch, synth, p, dev):
     vcoul = t(synth.coulomb(gc, cfg.qs[0], cfg.cell))
     k = 2 * int(np.abs(gc).max()) + 1
     npair = cfg.nv * len(col)
-    fl = flops_model(nd, k, ng, npair, cfg.nv + len(col))
+    fl = flops_model(transform_grid(nd, gw, gc), k, ng, npair, cfg.nv + len(col))
     head = args.head_mode
     modes = [head] + ([] if args.no_fp64_step or head == "fp64" else ["fp64"])
     wsb = max(p.gw_chi0_workspace_size(ctx, [prob], 1, p.PRECISIONS[m]) for m in modes)
@@ -252,7 +259,7 @@ def run_headline(args, torch, synth, p, dev):
         peak = PEAK["fp64_vec"] if head == "fp64" else PEAK["fp32_vec_nopk"]
         work = fl[dom] / launches
         kern = {"planes": ["k_pair_planes"], "finish": ["k_pair_finish"], "band": ["k_band"]}.get(dom, [dom])
-        traffic = traffic_for([f"{x}{v}<{fp}, {nd}, " for x in kern for v in ("", "_split", "_dl")],
+        traffic = traffic_for([f"{x}<{fp}, {(k - 1) // 2}" for x in kern],
                               "pair_transform.hip" if dom in ("planes", "finish") else "band_fft.hip")
         basis = ("256 CU x 4 SIMD x 16 lanes x 2 flop (FMA) x 2.4 GHz: the float64 vector rate, and the float32 "
                  "rate without packed instructions, which the library is compiled without")
@@ -301,7 +308,8 @@ def run_headline(args, torch, synth, p, dev):
             "warmup": args.warmup, "ms_per_step": hr["ms_per_step"], "higher_is_better": True, "scaling": "weak",
             "vs_baseline": None, "dtype": {"fp64": "f64", "fp32": "f32", "bf16x3": "bf16x3"}[head],
             "data": "synthetic",
-            "config": {"workload": cfg.name, "grid": nd, "npw": len(gw), "nv": cfg.nv, "nc_generated": cfg.nc,
+            "config": {"workload": cfg.name, "grid": nd, "transform_grid": transform_grid(nd, gw, gc), "npw": len(gw),
+                       "nv": cfg.nv, "nc_generated": cfg.nc,
                        "ncol": len(col), "explicit": n0, "windows": len(col) - n0, "ng": ng, "pairs": npair,
                        "q": list(cfg.qs[0]), "omega": 0.0, "e0_ev": cfg.e0_ev, "de_ev": cfg.de_ev,
                        "precision": head},
@@ -379,7 +387,7 @@ def run_c2_beside(args, torch, synth, p, dev, ctx):
     vcoul = t(synth.coulomb(gc, cfg.qs[0], cfg.cell))
     k = 2 * int(np.abs(gc).max()) + 1
     npair = cfg.nv * cfg.nc
-    fl = flops_model(nd, k, ng, npair, cfg.nv + cfg.nc)
+    fl = flops_model(transform_grid(nd, gw, gc), k, ng, npair, cfg.nv + cfg.nc)
     modes = ["fp64", "fp32", "bf16x3"]
     ws = torch.empty(max(p.gw_chi0_workspace_size(ctx, [prob], 1, p.PRECISIONS[m]) for m in modes), dtype=torch.uint8,
                      device=dev)
@@ -515,7 +523,7 @@ def main():
     vcoul = t(synth.coulomb(gc, cfg.qs[0], cfg.cell))
     k = 2 * int(np.abs(gc).max()) + 1
     npair = cfg.nv * cfg.nc
-    fl = flops_model(nd, k, ng, npair, cfg.nv + cfg.nc)
+    fl = flops_model(transform_grid(nd, gw, gc), k, ng, npair, cfg.nv + cfg.nc)
     modes = [m for m in args.modes.split(",") if m]
     wsb = max(p.gw_chi0_workspace_size(ctx, [prob], 1, p.PRECISIONS[m]) for m in modes)
     ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
@@ -690,7 +698,8 @@ def run_batched(args, torch, synth, p, dev):
     k = [2 * int(np.abs(synth.chi_sphere(n, q, cfg.cell)).max()) + 1 for n, q in zip(cfg.ng, cfg.qs)]
     work = {"planes": 0.0, "finish": 0.0, "contract": 0.0, "band": 0.0}
     for n, kk in zip(ngs, k):
-        f = flops_model(nd, kk, n, npair, cfg.nv + cfg.nc, with_inverse=False)
+        # the spheres of nd // 4 and (kk - 1) / 2 on their transform grid
+        f = flops_model(transform_grid(nd, np.array([nd // 4]), np.array([(kk - 1) // 2])), kk, n, npair, cfg.nv + cfg.nc, with_inverse=False)
         work["planes"] += f["planes"]
         work["finish"] += f["finish"]
         work["band"] += f["band"]
@@ -798,7 +807,7 @@ def run_grouped(args, torch, synth, p, dev, backward):
     head = torch.from_numpy(synth.loss_head_block(gc)).to(dev)
     k = 2 * int(np.abs(gc).max()) + 1
     npair = cfg.nv * len(col)
-    fl = flops_model(nd, k, ng, npair, cfg.nv + len(col))
+    fl = flops_model(transform_grid(nd, gw, gc), k, ng, npair, cfg.nv + len(col))
     # the adjoint recomputes the pair densities and forms Y = M Gbar^T (8 NG^2 per pair)
     # and Zbar -> chi0bar (two NG^3 complex products, 16 NG^3)
     bw = fl["planes"] + fl["finish"] + fl["band"] + 2.0 * fl["contract"] + 2.0 * fl["eps_inv"] if backward else 0.0
@@ -1124,7 +1133,7 @@ def run_extensions(args, torch, synth, p, dev):
     dt, _ = timed(lambda: p.gw_chi0_build_ksum(ctx, probs, len(gc), [0.0], 0.0, prec, workspace=ws, out=chi))
     k = 2 * int(np.abs(gc).max()) + 1
     npair = 128 * 500 * len(kp)
-    fl = flops_model(cfg.nd, k, len(gc), npair, len(kp) * 628, with_inverse=False)
+    fl = flops_model(transform_grid(cfg.nd, u, gc), k, len(gc), npair, len(kp) * 628, with_inverse=False)
     out["ksum"] = {"k_points": len(kp), "pairs": npair, "ng": len(gc), "seconds": dt,
                    "tflops": fl["total"] / dt / 1e12, "band_pairs_per_s": npair / dt}
     log(f"k-point sum: {dt * 1e3:.1f} ms, {out['ksum']['tflops']:.2f} TFLOP/s")

@@ -104,8 +104,8 @@ gw_status gw_ctx_set_overlap(gw_ctx* ctx, int mode);
 /* ---------------------------------------------------------------- geometry */
 
 /* Plane-wave geometry of one q-point (set-up; synchronises the stream).
- *   n_fft[3]   FFT grid N1, N2, N3 (host).  The kernels need N1 = N2 = N3, a multiple
- *              of 8 from 16 to 128; other grids give GW_EUNSUPPORTED.
+ *   n_fft[3]   FFT grid N1, N2, N3 (host), N1 = N2 = N3, a multiple of 8 from 16 to 128;
+ *              other grids give GW_EUNSUPPORTED.
  *   cell, q    host, or both NULL: the lattice vectors a1, a2, a3 as rows (9 doubles, bohr)
  *              and q in reciprocal-lattice units (3 doubles).  With them the dielectric
  *              sphere is checked to be the first ng G-vectors in the order
@@ -123,13 +123,14 @@ gw_status gw_ctx_set_overlap(gw_ctx* ctx, int mode);
  * 2 max|n_wf,i| + max|n_chi,i| < N_i per axis, which makes the grid evaluation of
  * M_vc(G) equal to the plane-wave convolution sum_G' conj(c_v(G'+G)) c_c(G')
  * (reading of Eq. (chi0)'s matrix element, whose exponent is printed without ".r").
- * Every grid that meets the bound gives the same chi0 up to rounding, so the smallest
- * supported one is the cheapest (the 72^3 workload's spheres, 2 x 18 + 7 = 43, are exact on
- * 48^3).  Tuned pair kernels are compiled for these (grid, K = 2 max|n_chi| + 1): 24^3 with
- * K 5, 7, 9, 11; 48^3 with 15; 64^3 with 19; 72^3 with 9 ... 19 (odd); 96^3 with 17, 19, 21,
- * 25; 128^3 with 23, 25, 27.  Any other grid and K <= 31 runs a generic pair kernel (run-time
- * N and K, slower); K > 31 gives GW_EUNSUPPORTED, and so do the coefficient gradients of
- * gw_chi0_backward on a shape without a compiled kernel.  The geometry keeps
+ * Every grid that meets the bound gives the same chi0 up to rounding, and the transforms run on
+ * the smallest one: N_t points per axis, N_t the smallest multiple of 4 with
+ * N_t > 2 max|n_wf| + max|n_chi|, N_t >= 2 max|n_chi| + 1 and N_t >= 16, at most N (the 72^3
+ * workload's spheres, 2 x 18 + 7, on 44^3; the 128^3 one's, 2 x 32 + 12, on 80^3).  The pair
+ * kernels take spheres up to max|n_chi| = 15; wider ones give GW_EUNSUPPORTED.  The coefficient
+ * gradients of gw_chi0_backward are offered for these (n_fft, K = 2 max|n_chi| + 1) and give
+ * GW_EUNSUPPORTED elsewhere: 24^3 with K 5, 7, 9, 11; 48^3 with 15; 64^3 with 19; 72^3 with
+ * 9 ... 19 (odd); 96^3 with 17, 19, 21, 25; 128^3 with 23, 25, 27.  The geometry keeps
  * its own device copies of the index tables.  Destroying a geometry also drops the graphs
  * that graph mode captured with it (gw_ctx_set_graph); a geometry may outlive its context
  * (it is then only destroyed). */
@@ -230,8 +231,8 @@ gw_status gw_chi0_build_ksum(gw_ctx* ctx, const gw_chi0_problem* probs, int nk, 
  *   grad_n_col  device, same length: dL/dn_col, the derivative with respect to the
  *               weight g(E_i) dE_i of Eq. (energyintegration) (nullable).
  *   grad_coef_v  device complex128, sum over problems of nv x npw: dL/dRe + i dL/dIm of
- *               coef_v (nullable = skip).  GW_FP64 only, and only for (grid, K) shapes with a
- *               compiled pair kernel (gw_geom_create; GW_EUNSUPPORTED otherwise).
+ *               coef_v (nullable = skip).  GW_FP64 only, and only for the (n_fft, K) shapes
+ *               listed at gw_geom_create (GW_EUNSUPPORTED otherwise).
  *   grad_coef_c  device complex128, sum over problems of nband x npw, per coefficient row
  *               of coef_c: the columns that use one row (col_band) add up; rows no column
  *               uses get zero (nullable = skip; GW_FP64 only).
@@ -266,7 +267,7 @@ gw_status gw_chi0_backward_ksum(gw_ctx* ctx, const gw_chi0_problem* probs, int n
  * Needs a context on a non-null stream.  Disabling drops the cached graphs. */
 gw_status gw_ctx_set_graph(gw_ctx* ctx, int enable);
 
-/* Launch-shape tuner: on the first conduction chunk of each problem, times the five
+/* Launch-shape tuner: on the first conduction chunk of each problem, times the
  * forms of the pair kernel and the contraction with
  * 1..32 pair-range splits, and keeps the fastest per problem shape in the context.
  * Later gw_chi0_workspace_size / gw_chi0_build calls use the tuned shapes (query the
@@ -274,17 +275,11 @@ gw_status gw_ctx_set_graph(gw_ctx* ctx, int enable);
  * gw_chi0_build. */
 gw_status gw_tune(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nomega, gw_precision prec,
                   void* workspace, size_t ws_bytes);
-/* The tuned shapes for prob's problem shape: pair-kernel form (1, 2 = 256 threads with
- * one or two resident workgroups per CU, 3 / 4 = split-line form with 4 / 2 valence bands
- * per workgroup, 5 = lean split-line form with 2 valence bands, which keeps the stage-2
- * items beyond one per thread in LDS; it exists where the dielectric sphere spans 17 or 19
- * frequencies along x3 on the 72^3 grid, and in float32 also from 17 on the 96^3 grid and
- * from 23 on the 128^3 grid; elsewhere form 5 runs form 1; 6 / 7 = direct-load split-line form
- * with 4 valence bands and four step buffers / 2 valence bands and two step buffers, which
- * streams the band rows from memory straight into LDS; it exists where a radix-R chunk row is
- * 128 bytes (float32 on 64^3, 96^3 and 128^3 grids, float64 on radix-8 grids) and its LDS
- * fits, elsewhere it runs form 1) and the number of pair-range splits of the contraction;
- * both 0 if the shape was not tuned. */
+/* The tuned shapes for prob's problem shape: pair-kernel form (float32 up to max|n_chi| = 7:
+ * 1 = 4 valence x 16 conduction bands per workgroup, 2 = 4 x 8 with two row quads per step and each
+ * line's x3 sum shared by two waves, on grids up to 52 points, 3 = the same for any grid; elsewhere,
+ * and for forms not built for the sphere, the one form there is) and the number of pair-range
+ * splits of the contraction; both 0 if the shape was not tuned. */
 gw_status gw_tune_get(gw_ctx* ctx, const gw_chi0_problem* prob, gw_precision prec, int* pair_variant, int* ksplit);
 /* Sets the shapes for prob's problem shape, e.g. to restore what gw_tune_get reported in
  * an earlier process: pair_variant 0..7 (0 = automatic), ksplit 0..32 (0 = automatic);

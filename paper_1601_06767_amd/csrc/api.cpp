@@ -138,14 +138,15 @@ std::string check_sphere_order(const double* cell, const double* q, int ng, cons
 
 namespace gw {
 
-// Line split N = R S of the band and pair transforms: radix 16 from N = 64 on where 16 divides N
-// (64, 80, 96, 112, 128), else radix 8; N a multiple of 8 (the pair kernel's x2 row groups) from
-// 16 to 128 (the band transform's LDS line buffer).
-bool line_split(int nd, LineSplit* out) {
-  if (nd < 16 || nd > 128 || nd % 8 != 0) return false;
-  const int R = nd >= 64 && nd % 16 == 0 ? 16 : 8;
-  *out = {R, nd / R};
-  return true;
+bool grid_supported(int nd) { return nd >= 16 && nd <= 128 && nd % 8 == 0; }
+
+bool coef_grad_offered(int nd, int K) {
+  static const int shapes[][2] = {{24, 5},  {24, 7},  {24, 9},  {24, 11}, {48, 15}, {64, 19}, {72, 9},
+                                  {72, 11}, {72, 13}, {72, 15}, {72, 17}, {72, 19}, {96, 17}, {96, 19},
+                                  {96, 21}, {96, 25}, {128, 23}, {128, 25}, {128, 27}};
+  for (const auto& s : shapes)
+    if (s[0] == nd && s[1] == K) return true;
+  return false;
 }
 
 }  // namespace gw
@@ -250,8 +251,7 @@ gw_status gw_geom_create(gw_ctx* ctx, const int n_fft[3], const double* cell, co
   for (int i = 0; i < 3; ++i)
     if (n_fft[i] < 1) return gw::fail(ctx, GW_EINVAL, "FFT grid must be positive");
   const int nd = n_fft[0];
-  gw::LineSplit ls;
-  if (n_fft[1] != nd || n_fft[2] != nd || !gw::line_split(nd, &ls))
+  if (n_fft[1] != nd || n_fft[2] != nd || !gw::grid_supported(nd))
     return gw::fail(ctx, GW_EUNSUPPORTED, "FFT grid must be cubic with N a multiple of 8 from 16 to 128");
   int rw = 0, rc = 0;
   std::unordered_set<long long> seen;
@@ -281,51 +281,93 @@ gw_status gw_geom_create(gw_ctx* ctx, const int n_fft[3], const double* cell, co
   g.ng = ng;
   g.rw = rw;
   g.W = 2 * rw + 1;
-  g.rchi = rc;
-  g.K = 2 * rc + 1;
+  // Every alias-free grid gives the same pair densities (the product of two bands reaches 2 rw, so
+  // that no G + nt m with m != 0 lands on a G of the dielectric sphere once nt > 2 rw + rc), and the
+  // transforms' work grows with nt^3: they run on the smallest one, a multiple of 4 for the
+  // folded quads (the 72^3 workload's spheres, 2 x 18 + 7, on 44^3; the 128^3 one's on 80^3).
+  g.rchi = std::max(rc, 1);
+  g.K = 2 * g.rchi + 1;
+  g.nt = std::min(nd, (int)round_up(std::max({2 * rw + rc + 1, g.K, 16}), 4));
   g.ngp = (int)round_up(ng, gw::kTile);
-  g.line = ls;
   if (cell) {
     g.has_q = true;
     for (int d = 0; d < 3; ++d) g.q[d] = q[d];
     for (int d = 0; d < 9; ++d) g.cell[d] = cell[d];
   }
   if (g.W > 2 * 64 + 1) return gw::fail(ctx, GW_EUNSUPPORTED, "wavefunction sphere too wide");
-  // the pair kernels read the planes in the band transform's split order: same radix
-  if (gw::pair_supported(nd, g.K) && gw::pair_radix(nd, g.K) != ls.R)
-    return gw::fail(ctx, GW_EUNSUPPORTED, "pair kernel radix differs from the band transform's split");
-  if (!gw::pair_supported(nd, g.K))
+  if (rc > gw::kMaxRc)
     return gw::fail(ctx, GW_EUNSUPPORTED,
-                "no pair kernel for N = " + std::to_string(nd) + ", K = " + std::to_string(g.K) +
+                "no pair kernel for N = " + std::to_string(nd) + ", K = " + std::to_string(2 * rc + 1) +
                     " (dielectric sphere half-width " + std::to_string(rc) + "; at most " +
-                    std::to_string((gw::kPairGenKMax - 1) / 2) + ")");
+                    std::to_string(gw::kMaxRc) + ")");
   std::vector<int32_t> wf_map((size_t)g.W * g.W * g.W, -1);
   for (int i = 0; i < npw; ++i) {
     const int32_t* n = gvec_wf + 3 * i;
     wf_map[((size_t)(n[0] + rw) * g.W + (n[1] + rw)) * g.W + (n[2] + rw)] = i;
   }
-  std::vector<int32_t> chi_map((size_t)g.K * g.K * g.K, -1);
+  // lines (n2, n3): per n2 the interval of n3 that holds a G, numbered n2 by n2
+  const int K = g.K, hk = g.rchi, nt = g.nt, nq = nt / 4;
+  std::vector<int32_t> lo(K, K), hi(K, -1), rowtab((size_t)K * 3);
+  for (int i = 0; i < ng; ++i) {
+    const int j2 = gvec_chi[3 * i + 1] + hk, j3 = gvec_chi[3 * i + 2] + hk;
+    lo[j2] = std::min(lo[j2], j3);
+    hi[j2] = std::max(hi[j2], j3);
+  }
+  for (int j = 0; j < K; ++j) {
+    rowtab[3 * j] = g.nl - lo[j];
+    rowtab[3 * j + 1] = lo[j];
+    rowtab[3 * j + 2] = hi[j];
+    if (hi[j] >= lo[j]) g.nl += hi[j] - lo[j] + 1;
+  }
+  std::vector<int32_t> chi_map((size_t)K * g.nl, -1);
   for (int i = 0; i < ng; ++i) {
     const int32_t* n = gvec_chi + 3 * i;
-    chi_map[((size_t)(n[0] + rc) * g.K + (n[1] + rc)) * g.K + (n[2] + rc)] = i;
+    chi_map[(size_t)(n[0] + hk) * g.nl + rowtab[3 * (n[1] + hk)] + n[2] + hk] = i;
   }
-  std::vector<double2> tw64(nd);
-  std::vector<float2> tw32(nd);
-  for (int j = 0; j < nd; ++j) {
-    const long double a = 2.0L * 3.141592653589793238462643383279502884L * (long double)j / (long double)nd;
-    tw64[j] = double2{(double)cosl(a), (double)sinl(a)};
-    tw32[j] = float2{(float)cosl(a), (float)sinl(a)};
+  const size_t nchi = chi_map.size();
+  chi_map.insert(chi_map.end(), rowtab.begin(), rowtab.end());
+  // unit roots of the transform grid and the factors of fold.h
+  std::vector<double2> tw(nt);
+  for (int k = 0; k < nt; ++k) {
+    const long double a = 2.0L * 3.141592653589793238462643383279502884L * (long double)k / (long double)nt;
+    tw[k] = double2{(double)cosl(a), (double)sinl(a)};
   }
-  // the twiddles of the pruned outputs per chunk index b: kernels index them by (b, j) alone
-  const size_t ntwk = (size_t)nd * g.K;
-  std::vector<double2> twk64(ntwk);
-  std::vector<float2> twk32(ntwk);
-  for (int b = 0; b < nd; ++b)
-    for (int j = 0; j < g.K; ++j) {
-      const int k = (((j - rc) * b) % nd + nd) % nd;
-      twk64[(size_t)b * g.K + j] = tw64[k];
-      twk32[(size_t)b * g.K + j] = tw32[k];
+  auto quarter = [](int n) { return n % 2 == 0 ? (n % 4 == 0 ? 1.0 : -1.0) : (n % 4 == 1 ? 1.0 : -1.0); };
+  const int nmax = std::max(rw, hk);   // the gradients' inverse transforms use the first hk + 1 rows
+  std::vector<double2> pts64((size_t)(nmax + 1) * nq);
+  for (int n = 0; n <= nmax; ++n)
+    for (int j = 0; j < nq; ++j) pts64[(size_t)n * nq + j] = j == 0 ? double2{1.0, quarter(n)} : tw[n * j % nt];
+  std::vector<float2> pts32(pts64.size());
+  for (size_t i = 0; i < pts64.size(); ++i) pts32[i] = float2{(float)pts64[i].x, (float)pts64[i].y};
+  const size_t npts = pts64.size();
+  pts64.insert(pts64.end(), tw.begin(), tw.end());
+  std::vector<double> fac64((size_t)nq * 2 * (hk + 1), 1.0);
+  for (int j = 0; j < nq; ++j)
+    for (int n = 0; n <= hk; ++n) {
+      double* f = &fac64[(size_t)j * 2 * (hk + 1)];
+      f[n] = j == 0 ? quarter(n) : tw[n * j % nt].x;
+      f[hk + 1 + n] = j == 0 ? 0.0 : tw[n * j % nt].y;
     }
+  std::vector<float> fac32(fac64.begin(), fac64.end());
+  const size_t nfac = fac32.size();
+  // MFMA blocks of a quad: groups of four frequencies of even C, odd C, even S, odd S; of quad 0:
+  // even C and odd C (ones), the second even C, odd S
+  const int ne = hk / 2 + 1, no = (hk + 1) / 2, ns = hk / 2;
+  const int ge = (ne + 3) / 4, go = (no + 3) / 4, gs = (ns + 3) / 4;
+  fac32.resize(nfac + (size_t)nq * 64, 0.f);
+  for (int j = 0; j < nq; ++j) {
+    const double* f = &fac64[(size_t)j * 2 * (hk + 1)];
+    float* a = &fac32[nfac + (size_t)j * 64];
+    for (int i = 0; i < ne; ++i) a[i] = j == 0 ? 1.f : (float)f[2 * i];
+    for (int i = 0; i < no; ++i) a[4 * ge + i] = j == 0 ? 1.f : (float)f[2 * i + 1];
+    if (j == 0) {
+      for (int i = 0; i < ne; ++i) a[4 * (ge + go) + i] = (float)f[2 * i];
+      for (int i = 0; i < no; ++i) a[4 * (2 * ge + go) + i] = (float)f[2 * i + 1];
+    } else {
+      for (int i = 0; i < ns; ++i) a[4 * (ge + go) + i] = (float)f[hk + 1 + 2 * i + 2];
+      for (int i = 0; i < no; ++i) a[4 * (ge + go + gs) + i] = (float)f[hk + 1 + 2 * i + 1];
+    }
+  }
   gw_geom* gg = new (std::nothrow) gw_geom();
   if (!gg) return gw::fail(ctx, GW_ENOMEM, "out of host memory");
   gg->ctx = ctx;
@@ -337,18 +379,19 @@ gw_status gw_geom_create(gw_ctx* ctx, const int n_fft[3], const double* cell, co
   hipError_t e = hipSuccess;
   int nalloc = 0;
   const int fail_at = fault_alloc_index();
-  e = e == hipSuccess ? setup_alloc((void**)&g.d_wf_map, wf_map.size() * 4, &nalloc, fail_at) : e;
-  e = e == hipSuccess ? setup_alloc((void**)&g.d_chi_map, chi_map.size() * 4, &nalloc, fail_at) : e;
-  e = e == hipSuccess ? setup_alloc((void**)&g.d_tw64, nd * sizeof(double2), &nalloc, fail_at) : e;
-  e = e == hipSuccess ? setup_alloc((void**)&g.d_tw32, nd * sizeof(float2), &nalloc, fail_at) : e;
-  e = e == hipSuccess ? setup_alloc((void**)&g.d_twk64, ntwk * sizeof(double2), &nalloc, fail_at) : e;
-  e = e == hipSuccess ? setup_alloc((void**)&g.d_twk32, ntwk * sizeof(float2), &nalloc, fail_at) : e;
-  if (e == hipSuccess) e = hipMemcpy(g.d_wf_map, wf_map.data(), wf_map.size() * 4, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(g.d_chi_map, chi_map.data(), chi_map.size() * 4, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(g.d_tw64, tw64.data(), nd * sizeof(double2), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(g.d_tw32, tw32.data(), nd * sizeof(float2), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(g.d_twk64, twk64.data(), ntwk * sizeof(double2), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(g.d_twk32, twk32.data(), ntwk * sizeof(float2), hipMemcpyHostToDevice);
+  auto upload = [&](void** p, const void* src, size_t bytes) {
+    if (e == hipSuccess) e = setup_alloc(p, bytes, &nalloc, fail_at);
+    if (e == hipSuccess) e = hipMemcpy(*p, src, bytes, hipMemcpyHostToDevice);
+  };
+  upload((void**)&g.d_wf_map, wf_map.data(), wf_map.size() * sizeof(int32_t));
+  upload((void**)&g.d_chi_map, chi_map.data(), chi_map.size() * sizeof(int32_t));
+  upload((void**)&g.d_pts64, pts64.data(), pts64.size() * sizeof(double2));
+  upload((void**)&g.d_pts32, pts32.data(), pts32.size() * sizeof(float2));
+  upload((void**)&g.d_fac64, fac64.data(), fac64.size() * sizeof(double));
+  upload((void**)&g.d_fac32, fac32.data(), fac32.size() * sizeof(float));
+  g.d_rowtab = g.d_chi_map + nchi;
+  g.d_tw64 = g.d_pts64 + npts;
+  g.d_amat = g.d_fac32 + nfac;
   (void)hipSetDevice(prev);
   gg->g = g;
   if (e != hipSuccess) {
@@ -390,10 +433,10 @@ gw_status gw_geom_destroy(gw_geom* geom) {
   Geom& g = geom->g;
   if (g.d_wf_map) (void)hipFree(g.d_wf_map);
   if (g.d_chi_map) (void)hipFree(g.d_chi_map);
-  if (g.d_tw64) (void)hipFree(g.d_tw64);
-  if (g.d_tw32) (void)hipFree(g.d_tw32);
-  if (g.d_twk64) (void)hipFree(g.d_twk64);
-  if (g.d_twk32) (void)hipFree(g.d_twk32);
+  if (g.d_pts64) (void)hipFree(g.d_pts64);
+  if (g.d_pts32) (void)hipFree(g.d_pts32);
+  if (g.d_fac64) (void)hipFree(g.d_fac64);
+  if (g.d_fac32) (void)hipFree(g.d_fac32);
   delete geom;
   return GW_OK;
 }

@@ -28,6 +28,10 @@ namespace {
 size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
 
 constexpr int kPairTarget = 32768;   // band pairs per conduction chunk
+constexpr int kColumnStep = 16;      // conduction columns of a chunk: whole workgroups of the pair kernel
+
+// columns of a chunk beside nvs (padded) valence slots
+int chunk_columns(int nvs) { return std::max(8, (kPairTarget / nvs) / 8 * 8); }
 constexpr int kBandBatch = 32;       // bands per band-transform launch group
 
 int mode_of(gw_precision p) { return p == GW_FP64 ? 0 : (p == GW_FP32 ? 1 : 2); }
@@ -85,8 +89,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
     ProbPlan q;
     q.p = &probs[i];
     q.nvs = (int)round_up(probs[i].nv, 4);
-    int cc = std::max(8, (kPairTarget / q.nvs) / 8 * 8);
-    q.cc = std::min<int>(cc, (int)round_up(probs[i].ncol, 8));
+    q.cc = (int)round_up(std::min<int>(chunk_columns(q.nvs), probs[i].ncol), kColumnStep);
     q.npair = q.nvs * q.cc;
     const int nt = g.ngp / gw::contract_tile(L.mode);
     q.ntl = nt * (nt + 1) / 2;
@@ -125,7 +128,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
   size_t max_psic = 0, max_scr = 0, max_q = 0, max_part = 0, max_np = 0;
   for (auto& q : L.pp) {
     const Geom& g = q.p->geom->g;
-    const size_t npts = (size_t)g.nd * g.nd * g.nd;
+    const size_t npts = g.band_elems(L.fp64);
     q.off_psiv = take((size_t)q.nvs * npts * L.csz);
     q.off_m = take((size_t)q.npair * g.ngp * L.csz);
     q.off_w = take((size_t)nomega * L.nparts * q.npair * sizeof(double));
@@ -140,7 +143,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
     }
     max_psic = std::max(max_psic, (size_t)q.cc * npts * L.csz);
     max_scr = std::max(max_scr, gw::band_scratch_bytes(g, kBandBatch, L.fp64));
-    max_q = std::max(max_q, (size_t)q.npair * g.nd * g.K * g.K * L.csz);
+    max_q = std::max(max_q, (size_t)q.npair * g.q_elems() * L.csz);
     max_part = std::max(max_part, gw::adjoint_partial_bytes(q.npair, g.ngp));
     max_np = std::max(max_np, (size_t)q.npair);
     L.max_cc = std::max(L.max_cc, q.cc);
@@ -166,7 +169,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
       size_t mb = 0, uc = 0, uv = 0, cb = 0;
       for (const auto& q : L.pp) {
         const Geom& g = q.p->geom->g;
-        const size_t npts = (size_t)g.nd * g.nd * g.nd;
+        const size_t npts = g.band_elems(true);
         mb = std::max(mb, (size_t)q.npair * g.ngp * sizeof(double2));
         uc = std::max(uc, (size_t)q.cc * npts * sizeof(double2));
         uv = std::max(uv, (size_t)q.nvs * npts * sizeof(double2));
@@ -186,7 +189,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
 
 gw_status band_to_real(gw_ctx* ctx, const Layout& L, const Geom& g, const double2* coef, int nrows,
                        const int32_t* band_idx, int band0, int nvalid, int nslot, char* ws, char* psi) {
-  const size_t npts = (size_t)g.nd * g.nd * g.nd;
+  const size_t npts = g.band_elems(L.fp64);
   for (int s0 = 0; s0 < nslot; s0 += kBandBatch) {
     const int ns = std::min(kBandBatch, nslot - s0);
     void* tB = ws + L.off_scr;
@@ -427,7 +430,7 @@ gw_status enqueue_build_all(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob
 gw_status coef_grad_chunk(gw_ctx* ctx, const Layout& L, const ProbPlan& q, const Geom& g, const double* omega,
                           int nomega, double delta, const double2* gbar, int c0, char* ws, double2* gcc, bool want_v) {
   const gw_chi0_problem& p = *q.p;
-  const size_t npts = (size_t)g.nd * g.nd * g.nd;
+  const size_t npts = g.band_elems(true);
   double* w = (double*)(ws + q.off_w);
   GW_HIP(ctx, gw::launch_fill_c128(ws + L.off_mbar, (size_t)q.npair * g.ngp, ctx->stream));
   for (int iw = 0; iw < nomega; ++iw) {
@@ -611,7 +614,7 @@ gw_status backward_entry(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, i
     return gw::fail(ctx, GW_EUNSUPPORTED, "coefficient gradients are computed in the float64 mode only");
   if (want_coef)
     for (int i = 0; i < nprob; ++i)
-      if (probs && probs[i].geom && !gw::pair_instance(probs[i].geom->g.nd, probs[i].geom->g.K))
+      if (probs && probs[i].geom && !gw::coef_grad_offered(probs[i].geom->g.nd, probs[i].geom->g.K))
         return gw::fail(ctx, GW_EUNSUPPORTED,
                         "coefficient gradients need a compiled pair-transform instance for N = " +
                             std::to_string(probs[i].geom->g.nd) + ", K = " + std::to_string(probs[i].geom->g.K));
@@ -632,7 +635,7 @@ gw_status backward_entry(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, i
     double* gn = grad_n_col ? grad_n_col + off_ec : nullptr;
     gw::StageScope sc(ctx, gw::kStageBackward);
     if (gev) GW_HIP(ctx, gw::launch_fill_f64(gev, p.nv, 0.0, ctx->stream));
-    const size_t npts = (size_t)g.nd * g.nd * g.nd;
+    const size_t npts = g.band_elems(L.fp64);
     double2* gcv = grad_coef_v ? (double2*)grad_coef_v + off_cv : nullptr;
     double2* gcc = grad_coef_c ? (double2*)grad_coef_c + off_cc : nullptr;
     if (gcc) GW_HIP(ctx, gw::launch_fill_c128(gcc, (size_t)p.nband * g.npw, ctx->stream));
@@ -732,7 +735,8 @@ gw_status gw_pair_density(gw_ctx* ctx, const gw_chi0_problem* prob, int v0, int 
   sub.ncol = ncs;
   const Layout L = make_layout(ctx, &sub, 1, 1, false, prec, false);
   const ProbPlan& q = L.pp[0];
-  if (q.cc < (int)round_up(ncs, 8)) return gw::fail(ctx, GW_EINVAL, "pair block too large for one pass");
+  if (chunk_columns(q.nvs) < (int)round_up(ncs, 8))
+    return gw::fail(ctx, GW_EINVAL, "pair block too large for one pass");
   if (L.total > ws_bytes) return gw::fail(ctx, GW_EINVAL, "workspace too small: need " + std::to_string(L.total));
   DeviceScope dev(ctx->device);
   s = check_values(ctx, prob, 1);

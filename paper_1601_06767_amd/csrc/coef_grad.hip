@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "fold.h"
 #include "internal.h"
 
 namespace gw {
@@ -40,139 +41,178 @@ __global__ void k_weight_rows(const double2* __restrict__ m, int npair, int ngp,
   a[e] = cmul(s, m[e]);
 }
 
-// qbar[pair][p1][l] = scale sum_{n1} e^{-2 pi i n1 x1 / N} mbar[pair][G(n1, l)]  (x1 = b + S a,
-// p1 = b R + a), the transpose of the finish stage; one workgroup per pair.
-template <int ND, int R, int K>
+// qbar[pair][x1][l] = scale sum_{n1} e^{-2 pi i n1 x1 / N} mbar[pair][G(n1, l)], the transpose of the
+// finish stage: per line l the points of each quad from the folded frequencies (the conjugate of
+// points_of_quads' sum: A - i B); one workgroup per pair, quads wave-uniform (scalar factors).
+template <int RC>
 __global__ __launch_bounds__(256) void k_qbar(const double2* __restrict__ mbar, const int32_t* __restrict__ chi_map,
-                                              int ngp, double scale, const double2* __restrict__ twk,
+                                              int ngp, int nt, int nl, double scale, const double* __restrict__ fac,
                                               double2* __restrict__ qbar) {
-  constexpr int S = ND / R;
-  constexpr int RCH = (K - 1) / 2;
+  constexpr int K = 2 * RC + 1;
   const size_t pair = blockIdx.x;
+  const int nq = nt / 4, h = nt / 2;
   const double2* src = mbar + pair * ngp;
-  double2* dst = qbar + pair * ND * (K * K);
-  for (int l = threadIdx.x; l < K * K; l += blockDim.x) {
+  for (int l = threadIdx.x; l < nl; l += blockDim.x) {
+    double2* dst = qbar + pair * nt * (size_t)nl + l;
+    double2 e[RC + 1], o[RC + 1];   // folded frequencies
     double2 t[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      const int ig = chi_map[j * K * K + l];
-      t[j] = ig >= 0 ? conjd(src[ig]) : double2{0.0, 0.0};
+      const int ig = chi_map[(size_t)j * nl + l];
+      t[j] = ig >= 0 ? src[ig] : double2{0.0, 0.0};
+      t[j] = double2{t[j].x * scale, t[j].y * scale};
+    }
+    e[0] = t[RC];
+#pragma unroll
+    for (int n = 1; n <= RC; ++n) {
+      e[n] = cadd(t[RC + n], t[RC - n]);
+      o[n] = csub(t[RC + n], t[RC - n]);
+    }
+    auto mac = [](double2& a, double f, double2 x) {
+      a.x = fma(f, x.x, a.x);
+      a.y = fma(f, x.y, a.y);
+    };
+    {   // quad 0: x = 0, H / 2, H, 3 H / 2
+      double2 ae = e[0], ao{0, 0}, be = e[0], bo{0, 0};
+#pragma unroll
+      for (int n = 1; n <= RC; ++n) {
+        if (n % 2 == 0) {
+          ae = cadd(ae, e[n]);
+          be = n % 4 == 0 ? cadd(be, e[n]) : csub(be, e[n]);
+        } else {
+          ao = cadd(ao, e[n]);
+          bo = n % 4 == 1 ? cadd(bo, o[n]) : csub(bo, o[n]);
+        }
+      }
+      dst[0] = cadd(ae, ao);
+      dst[(size_t)(h / 2) * nl] = minus_i(be, bo);
+      dst[(size_t)h * nl] = csub(ae, ao);
+      dst[(size_t)(h + h / 2) * nl] = plus_i(be, bo);
     }
 #pragma unroll 1
-    for (int b = 0; b < S; ++b) {
-      double2 y[R];
+    for (int j = 1; j < nq; ++j) {
+      const double* f = fac + (size_t)j * (2 * RC + 2);
+      double2 ae = e[0], ao{0, 0}, be{0, 0}, bo{0, 0};
 #pragma unroll
-      for (int r = 0; r < R; ++r) y[r] = double2{0.0, 0.0};
-#pragma unroll
-      for (int j = 0; j < K; ++j) cmac(y[((j - RCH) % R + R) % R], twk[b * K + j], t[j]);
-      dft<R>(y);
-#pragma unroll
-      for (int a = 0; a < R; ++a)
-        dst[(size_t)(b * R + a) * (K * K) + l] = double2{y[a].x * scale, -y[a].y * scale};
+      for (int n = 1; n <= RC; ++n) {
+        mac(n % 2 == 0 ? ae : ao, f[n], e[n]);
+        mac(n % 2 == 0 ? be : bo, f[RC + 1 + n], o[n]);
+      }
+      const double2 x = cadd(ae, ao), y = csub(ae, ao), sx = cadd(be, bo), sy = csub(bo, be);
+      dst[(size_t)j * nl] = minus_i(x, sx);
+      dst[(size_t)(h - j) * nl] = minus_i(y, sy);
+      dst[(size_t)(h + j) * nl] = plus_i(y, sy);
+      dst[(size_t)(nt - j) * nl] = plus_i(x, sx);
     }
   }
 }
 
-template <int ND> constexpr int ubar_threads() { return ND <= 72 ? 256 : 512; }
-// workgroups per plane: the rows p2 of a plane are split between them so that a thread
-// keeps one (row, chunk) accumulator of R complex values at the largest grids
-template <int ND> constexpr int ubar_split() { return ND <= 96 ? 1 : 2; }
+// Threads of a k_ubar workgroup and quads of a row that a thread sums at once.
+constexpr int kUt = 256, kUq = 2;
 
-// One workgroup per (x1 plane, row part, own band).  For every partner band: h of the pair on this
-// plane from qbar (x2 transform into LDS, then x3 transform per (row, chunk) task), times
+// One workgroup per (x1 plane, part of its x2 quads, own band).  For every partner band: h of the
+// pair on this plane from qbar (x2 transform into LDS, then x3 transform per (row, quads) task), times
 // the partner's plane, accumulated in registers; the plane of ubar is written (COND) or
-// added (valence, accumulated over conduction chunks) at the end.
+// added (valence, accumulated over conduction chunks) at the end.  TPT tasks per thread.
 //   COND:  own = column c < ncs (pairs v * ncs + c, v < nvs), ubar_c += h_vc u_v
 //   !COND: own = valence slot v < nvs (pairs v * ncs + c, c < ncs), ubar_v += conj(h_vc) u_c
-template <int ND, int R, int K, bool COND>
-__global__ __launch_bounds__(ubar_threads<ND>()) void k_ubar(const double2* __restrict__ qbar,
-                                                             const double2* __restrict__ partner, int nvs, int ncs,
-                                                             const double2* __restrict__ twk,
-                                                             double2* __restrict__ ubar) {
-  constexpr int NT = ubar_threads<ND>();
-  constexpr int RS = ubar_split<ND>();
-  constexpr int S = ND / R;
-  constexpr int S2 = ND / kRows;
-  constexpr int S2P = S2 / RS;                   // row groups b2 of this part
-  constexpr int NROW = ND / RS;                  // rows p2 of this part
-  constexpr int RCH = (K - 1) / 2;
-  constexpr int NTASK = NROW * S;                // (row p2, x3 chunk b)
-  constexpr int TPT = (NTASK + NT - 1) / NT;     // tasks per thread
-  constexpr size_t NPL = (size_t)ND * ND;
-  static_assert(S2 % RS == 0, "row groups split evenly");
-  __shared__ double2 s_q[K * K];
-  __shared__ double2 s_t[NROW * K];              // [p2 - row0][n3]
-  const int x1 = blockIdx.x % ND;
-  const int part = (blockIdx.x / ND) % RS;
-  const int own = blockIdx.x / (ND * RS);
-  const int b2_0 = part * S2P;
-  const int row0 = b2_0 * kRows;
-  const int p1 = (x1 % S) * R + x1 / S;
+// The inverse sums run on the conjugates (conj h), so that the factors are the forward ones.
+template <int RC, int TPT, bool COND>
+__global__ __launch_bounds__(kUt) void k_ubar(const double2* __restrict__ qbar, const double2* __restrict__ partner,
+                                              int nvs, int ncs, int nt, int nl, int row, int nparts, int rq,
+                                              const int32_t* __restrict__ rowtab, const double2* __restrict__ pts,
+                                              double2* __restrict__ ubar) {
+  constexpr int K = 2 * RC + 1;
+  const int nq = nt / 4;
+  extern __shared__ __align__(16) unsigned char s_raw[];
+  double2* s_q = (double2*)s_raw;                 // [n2][n3] conj of the pair's lines, K x K
+  double2* s_f = s_q + K * K;                     // [n][j] factors, (RC + 1) x nq
+  double2* s_t = s_f + (RC + 1) * nq;             // [row of the part][n3], 4 rq x (K + 1)
+  constexpr int KS = K + 1;                       // even: rows of n3 folded in place below
+  const int x1 = blockIdx.x % nt;
+  const int part = (blockIdx.x / nt) % nparts;
+  const int own = blockIdx.x / (nt * nparts);
+  const int q0 = part * rq;                       // x2 quads [q0, q1)
+  const int q1 = min(nq, q0 + rq);
+  const int nrow = 4 * (q1 - q0);
+  const int ngq = (nq + kUq - 1) / kUq;           // x3 quad groups of a row
+  const int ntask = nrow * ngq;
   const int tid = threadIdx.x;
   const int npart = COND ? nvs : ncs;
-  double2 acc[TPT][R];
+  for (int i = tid; i < K * K; i += kUt) s_q[i] = double2{0.0, 0.0};   // outside the lines: zero
+  for (int i = tid; i < (RC + 1) * nq; i += kUt) s_f[i] = pts[i];
+  double2 acc[TPT][kUq][4];
 #pragma unroll
   for (int k = 0; k < TPT; ++k)
 #pragma unroll
-    for (int a = 0; a < R; ++a) acc[k][a] = double2{0.0, 0.0};
+    for (int a = 0; a < kUq; ++a)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[k][a][c] = double2{0.0, 0.0};
 #pragma unroll 1
   for (int q = 0; q < npart; ++q) {
     const size_t pair = COND ? (size_t)q * ncs + own : (size_t)own * ncs + q;
-    const double2* src = qbar + (pair * ND + p1) * (K * K);
+    const double2* src = qbar + (pair * nt + x1) * (size_t)nl;
     __syncthreads();   // the previous partner's s_q / s_t are consumed
-    for (int l = tid; l < K * K; l += NT) s_q[l] = conjd(src[l]);
-    __syncthreads();
-    // x2 transform: T[p2 = 8 b2 + a][n3] = sum_{n2} e^{-2 pi i n2 x2 / N} qbar[n2][n3], x2 = b2 + S2 a
-    for (int task = tid; task < K * S2P; task += NT) {
-      const int j3 = task % K, bl = task / K, b2 = b2_0 + bl;
-      double2 y[kRows];
-#pragma unroll
-      for (int r = 0; r < kRows; ++r) y[r] = double2{0.0, 0.0};
-#pragma unroll
-      for (int j = 0; j < K; ++j) cmac(y[((j - RCH) % kRows + kRows) % kRows], twk[b2 * K + j], s_q[j * K + j3]);
-      dft<kRows>(y);
-#pragma unroll
-      for (int a = 0; a < kRows; ++a) s_t[(bl * kRows + a) * K + j3] = y[a];   // still conjugated
+    for (int i = tid; i < K * K; i += kUt) {
+      const int j2 = i / K, j3 = i % K;
+      const int32_t* e = rowtab + 3 * j2;
+      if (j3 >= e[1] && j3 <= e[2]) s_q[i] = conjd(src[e[0] + j3]);
     }
     __syncthreads();
-    // x3 transform per (p2, b): h[p2][b R + a], then times the partner's plane
-    const double2* up = partner + ((size_t)q * ND + x1) * NPL;
+    // x2: the four rows of a quad for one n3
+    for (int task = tid; task < K * (q1 - q0); task += kUt) {
+      const int j3 = task % K, ql = task / K, j = q0 + ql;
+      double2 y[1][4];
+      points_of_quads<double2, 1>(
+          RC, j == 0, [&](int n) { return s_q[(n + RC) * K + j3]; }, [&](int n, int) { return s_f[n * nq + j]; }, y);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) s_t[(4 * ql + a) * KS + j3] = y[0][a];
+    }
+    __syncthreads();
+    // x3: quads of a row, times the partner's values
+    const double2* up = partner + ((size_t)q * nt + x1) * (size_t)nt * row;
 #pragma unroll
     for (int k = 0; k < TPT; ++k) {
-      const int task = tid + NT * k;
-      if (task < NTASK) {
-        const int pl = task / S, b = task % S;
-        double2 y[R];
+      const int task = tid + kUt * k;
+      if (task < ntask) {
+        const int rl = task % nrow, jq = task / nrow;
+        const int j0 = min(jq * kUq, nq - kUq);
+        double2 y[kUq][4];
+        const double2* tr = s_t + rl * KS + RC;
+        points_of_quads<double2, kUq>(
+            RC, j0 == 0, [&](int n) { return tr[n]; }, [&](int n, int a) { return s_f[n * nq + j0 + a]; }, y);
+        const double2* u = up + (size_t)(4 * q0 + rl) * row + 4 * j0;
 #pragma unroll
-        for (int r = 0; r < R; ++r) y[r] = double2{0.0, 0.0};
-        // s_t already holds conj(T), the inner conjugation of the identity
+        for (int a = 0; a < kUq; ++a)
 #pragma unroll
-        for (int j = 0; j < K; ++j) cmac(y[((j - RCH) % R + R) % R], twk[b * K + j], s_t[pl * K + j]);
-        dft<R>(y);
-        const double2* u = up + (size_t)(row0 + pl) * ND + b * R;
-#pragma unroll
-        for (int a = 0; a < R; ++a) {
-          const double2 h = conjd(y[a]);
-          const double2 v = u[a];
-          acc[k][a] = COND ? cadd(acc[k][a], cmul(h, v)) : cadd(acc[k][a], cmul(conjd(h), v));
-        }
+          for (int c = 0; c < 4; ++c) {
+            const double2 v = u[4 * a + c];
+            // y = conj h
+            acc[k][a][c] = COND ? cadd(acc[k][a][c], cmulc(y[a][c], v)) : cadd(acc[k][a][c], cmul(y[a][c], v));
+          }
       }
     }
   }
-  double2* out = ubar + ((size_t)own * ND + x1) * NPL;
+  double2* out = ubar + ((size_t)own * nt + x1) * (size_t)nt * row;
 #pragma unroll
   for (int k = 0; k < TPT; ++k) {
-    const int task = tid + NT * k;
-    if (task < NTASK) {
-      const int pl = task / S, b = task % S;
-      double2* o = out + (size_t)(row0 + pl) * ND + b * R;
+    const int task = tid + kUt * k;
+    if (task < ntask) {
+      const int rl = task % nrow, jq = task / nrow;
+      const int j0 = min(jq * kUq, nq - kUq);
+      // an overlapping last group repeats the quads of its neighbour: written by the group that owns them
+      double2* o = out + (size_t)(4 * q0 + rl) * row + 4 * j0;
 #pragma unroll
-      for (int a = 0; a < R; ++a) {
-        if (COND)
-          o[a] = acc[k][a];
-        else
-          o[a] = cadd(o[a], acc[k][a]);
-      }
+      for (int a = 0; a < kUq; ++a)
+        if (j0 + a >= jq * kUq) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            if (COND)
+              o[4 * a + c] = acc[k][a][c];
+            else
+              o[4 * a + c] = cadd(o[4 * a + c], acc[k][a][c]);
+          }
+        }
     }
   }
 }
@@ -180,14 +220,14 @@ __global__ __launch_bounds__(ubar_threads<ND>()) void k_ubar(const double2* __re
 constexpr int kJB = 8;   // outputs per thread of the transposed band passes
 
 // transpose of the x1 pass: tB[slot][j1][p23] = sum_{x1} e^{-2 pi i n1 x1 / N} ubar[slot][x1][p23]
-__global__ __launch_bounds__(256) void k_bandT_c(const double2* __restrict__ ubar, int rw, int nd,
+__global__ __launch_bounds__(256) void k_bandT_c(const double2* __restrict__ ubar, int rw, int nd, int row,
                                                  const double2* __restrict__ tw, double2* __restrict__ tB) {
   __shared__ double2 s_tw[128];
   for (int i = threadIdx.x; i < nd; i += blockDim.x) s_tw[i] = conjd(tw[i]);
   __syncthreads();
   const int W = 2 * rw + 1;
   const int nblk = (W + kJB - 1) / kJB;
-  const size_t plane = (size_t)nd * nd;
+  const size_t plane = (size_t)nd * row;
   const int slot = blockIdx.y;
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (long long)nblk * (long long)plane) return;
@@ -219,10 +259,10 @@ __global__ __launch_bounds__(256) void k_bandT_c(const double2* __restrict__ uba
 
 // transposes of the x2 and x3 passes for one (slot, j1) slab, then the sphere gather:
 // cbar[slot][ig] for ig = wf_map[j1][j2][j3] >= 0
-__global__ __launch_bounds__(256) void k_bandT_ab(const double2* __restrict__ tB, int rw, int nd, int S2, int R3,
+__global__ __launch_bounds__(256) void k_bandT_ab(const double2* __restrict__ tB, int rw, int nd, int row,
                                                   const int32_t* __restrict__ wf_map, int npw,
                                                   const double2* __restrict__ tw, double2* __restrict__ cbar) {
-  extern __shared__ unsigned char s_raw[];
+  extern __shared__ __align__(16) unsigned char s_raw[];
   double2* s_tw = (double2*)s_raw;   // conj twiddles, nd
   double2* s_t = s_tw + 128;         // [j2][p3], W x nd
   const int W = 2 * rw + 1;
@@ -231,16 +271,16 @@ __global__ __launch_bounds__(256) void k_bandT_ab(const double2* __restrict__ tB
   const int slot = blockIdx.y;
   for (int i = threadIdx.x; i < nd; i += blockDim.x) s_tw[i] = conjd(tw[i]);
   __syncthreads();
-  const double2* slab = tB + ((size_t)slot * W + j1) * nd * nd;
-  // x2: s_t[j2][p3] = sum_{x2} e^{-2 pi i n2 x2 / N} slab[p2(x2)][p3],  p2 = 8 b2 + a2, x2 = b2 + S2 a2
+  const double2* slab = tB + ((size_t)slot * W + j1) * nd * row;
+  // x2: s_t[j2][p3] = sum_{x2} e^{-2 pi i n2 x2 / N} slab[p2(x2)][p3]
   for (int task = threadIdx.x; task < nd * nblk; task += blockDim.x) {
     const int p3 = task % nd, jb = task / nd;
     double2 acc[kJB];
 #pragma unroll
     for (int k = 0; k < kJB; ++k) acc[k] = double2{0.0, 0.0};
     for (int p2 = 0; p2 < nd; ++p2) {
-      const int x2 = p2 / kRows + S2 * (p2 % kRows);
-      const double2 v = slab[(size_t)p2 * nd + p3];
+      const int x2 = quad_x(p2, nd);
+      const double2 v = slab[(size_t)p2 * row + p3];
 #pragma unroll
       for (int k = 0; k < kJB; ++k) cmac(acc[k], v, s_tw[wrap((jb * kJB + k - rw) * x2, nd)]);
     }
@@ -249,15 +289,14 @@ __global__ __launch_bounds__(256) void k_bandT_ab(const double2* __restrict__ tB
       if (jb * kJB + k < W) s_t[(size_t)(jb * kJB + k) * nd + p3] = acc[k];
   }
   __syncthreads();
-  // x3: cbar(j1, j2, j3) = sum_{x3} e^{-2 pi i n3 x3 / N} s_t[j2][p3(x3)],  p3 = b R3 + a, x3 = b + S3 a
-  const int S3 = nd / R3;
+  // x3: cbar(j1, j2, j3) = sum_{x3} e^{-2 pi i n3 x3 / N} s_t[j2][p3(x3)]
   for (int task = threadIdx.x; task < W * nblk; task += blockDim.x) {
     const int j2 = task % W, jb = task / W;
     double2 acc[kJB];
 #pragma unroll
     for (int k = 0; k < kJB; ++k) acc[k] = double2{0.0, 0.0};
     for (int p3 = 0; p3 < nd; ++p3) {
-      const int x3 = p3 / R3 + S3 * (p3 % R3);
+      const int x3 = quad_x(p3, nd);
       const double2 v = s_t[(size_t)j2 * nd + p3];
 #pragma unroll
       for (int k = 0; k < kJB; ++k) cmac(acc[k], v, s_tw[wrap((jb * kJB + k - rw) * x3, nd)]);
@@ -292,25 +331,45 @@ __global__ void k_fill_c128(double2* __restrict__ p, size_t n) {
     p[i] = double2{0.0, 0.0};
 }
 
-template <int ND, int R, int K>
+template <int RC>
 hipError_t run_qbar(const Geom& g, const void* mbar, int npair, void* qbar, hipStream_t st) {
-  k_qbar<ND, R, K><<<npair, 256, 0, st>>>((const double2*)mbar, g.d_chi_map, g.ngp, 1.0 / ((double)ND * ND * ND),
-                                          g.d_twk64, (double2*)qbar);
+  const int threads = std::min(256, (g.nl + 63) / 64 * 64);
+  k_qbar<RC><<<npair, threads, 0, st>>>((const double2*)mbar, g.d_chi_map, g.ngp, g.nt, g.nl,
+                                        1.0 / ((double)g.nt * g.nt * g.nt), g.d_fac64, (double2*)qbar);
   return hipGetLastError();
 }
 
-template <int ND, int R, int K>
-hipError_t run_ubar(const Geom& g, const void* qbar, const void* partner, int nvs, int ncs, bool cond, int nown,
-                    void* ubar, hipStream_t st) {
-  constexpr int NT = ubar_threads<ND>();
-  const dim3 grid((unsigned)(ND * ubar_split<ND>() * nown));
-  if (cond)
-    k_ubar<ND, R, K, true><<<grid, NT, 0, st>>>((const double2*)qbar, (const double2*)partner, nvs, ncs, g.d_twk64,
-                                                (double2*)ubar);
-  else
-    k_ubar<ND, R, K, false><<<grid, NT, 0, st>>>((const double2*)qbar, (const double2*)partner, nvs, ncs, g.d_twk64,
-                                                 (double2*)ubar);
+template <int RC, int TPT, bool COND>
+hipError_t run_ubar_tpt(const Geom& g, const void* qbar, const void* partner, int nvs, int ncs, int nparts, int rq,
+                        void* ubar, hipStream_t st) {
+  constexpr int K = 2 * RC + 1;
+  const size_t lds = ((size_t)K * K + (RC + 1) * (g.nt / 4) + (size_t)4 * rq * (K + 1)) * sizeof(double2);
+  static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ubar<RC, TPT, COND>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (allowed != hipSuccess) return allowed;
+  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)(g.nt * nparts * (COND ? ncs : nvs));
+  k_ubar<RC, TPT, COND><<<grid, kUt, lds, st>>>((const double2*)qbar, (const double2*)partner, nvs, ncs, g.nt, g.nl,
+                                                g.row(true), nparts, rq, g.d_rowtab, g.d_pts64, (double2*)ubar);
   return hipGetLastError();
+}
+
+// A thread holds kUq quads (8 complex accumulators) per task; the plane's x2 quads are split over
+// parts so that a thread has at most two tasks.
+template <int RC>
+hipError_t run_ubar(const Geom& g, const void* qbar, const void* partner, int nvs, int ncs, bool cond, void* ubar,
+                    hipStream_t st) {
+  const int nq = g.nt / 4, ngq = (nq + kUq - 1) / kUq;
+  const int rq_max = std::max(1, 2 * kUt / (4 * ngq));   // x2 quads whose tasks fit two per thread
+  const int nparts = (nq + rq_max - 1) / rq_max;
+  const int rq = (nq + nparts - 1) / nparts;
+  const int ntask = 4 * rq * ngq;
+  if (ntask > 2 * kUt) return hipErrorInvalidValue;
+  if (ntask <= kUt)
+    return cond ? run_ubar_tpt<RC, 1, true>(g, qbar, partner, nvs, ncs, nparts, rq, ubar, st)
+                : run_ubar_tpt<RC, 1, false>(g, qbar, partner, nvs, ncs, nparts, rq, ubar, st);
+  return cond ? run_ubar_tpt<RC, 2, true>(g, qbar, partner, nvs, ncs, nparts, rq, ubar, st)
+              : run_ubar_tpt<RC, 2, false>(g, qbar, partner, nvs, ncs, nparts, rq, ubar, st);
 }
 
 hipError_t allow_bandT_lds() {
@@ -330,38 +389,40 @@ hipError_t launch_weight_rows(const void* m, int npair, int ngp, const double* w
 }
 
 hipError_t launch_qbar(const Geom& g, const void* mbar, int npair, void* qbar, hipStream_t st) {
-#define X(nd_, r_, k_) \
-  if (g.nd == nd_ && g.K == k_) return run_qbar<nd_, r_, k_>(g, mbar, npair, qbar, st);
-  GW_PAIR_CASES(X)
+  switch (g.rchi) {
+#define X(rc) \
+  case rc: return run_qbar<rc>(g, mbar, npair, qbar, st);
+    GW_RC_CASES(X)
 #undef X
+  }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_ubar(const Geom& g, const void* qbar, const void* partner, int nvs, int ncs, bool cond, void* ubar,
                        hipStream_t st) {
-  const int nown = cond ? ncs : nvs;
-#define X(nd_, r_, k_) \
-  if (g.nd == nd_ && g.K == k_) return run_ubar<nd_, r_, k_>(g, qbar, partner, nvs, ncs, cond, nown, ubar, st);
-  GW_PAIR_CASES(X)
+  switch (g.rchi) {
+#define X(rc) \
+  case rc: return run_ubar<rc>(g, qbar, partner, nvs, ncs, cond, ubar, st);
+    GW_RC_CASES(X)
 #undef X
+  }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_band_from_real(const Geom& g, const void* ubar, int nslot, void* tB, void* cbar, hipStream_t st) {
-  const int nd = g.nd, W = g.W;
-  if (nd > 128 || nd % kRows != 0) return hipErrorInvalidValue;
+  const int nd = g.nt, W = g.W, row = g.row(true);
   const size_t lds = (size_t)(128 + W * nd) * sizeof(double2);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  if (nd > 128 || lds > 160 * 1024) return hipErrorInvalidValue;
   const hipError_t ea = allow_bandT_lds();
   if (ea != hipSuccess) return ea;
   const int nblk = (W + kJB - 1) / kJB;
-  const long long n = (long long)nblk * nd * nd;
-  k_bandT_c<<<dim3((unsigned)((n + 255) / 256), nslot), 256, 0, st>>>((const double2*)ubar, g.rw, nd, g.d_tw64,
+  const long long n = (long long)nblk * nd * row;
+  k_bandT_c<<<dim3((unsigned)((n + 255) / 256), nslot), 256, 0, st>>>((const double2*)ubar, g.rw, nd, row, g.d_tw64,
                                                                        (double2*)tB);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_bandT_ab<<<dim3(W, nslot), 256, lds, st>>>((const double2*)tB, g.rw, nd, nd / kRows, g.line.R, g.d_wf_map,
-                                                g.npw, g.d_tw64, (double2*)cbar);
+  k_bandT_ab<<<dim3(W, nslot), 256, lds, st>>>((const double2*)tB, g.rw, nd, row, g.d_wf_map, g.npw, g.d_tw64,
+                                                (double2*)cbar);
   return hipGetLastError();
 }
 

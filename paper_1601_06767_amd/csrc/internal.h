@@ -90,30 +90,34 @@ struct StageScope {
 
 namespace gw {
 
-// Line decomposition of an N-point transform, x = b + S a  (a in [0,R), b in [0,S)),
-// stored permuted at p = b R + a so that the R points of one b are contiguous.
-struct LineSplit {
-  int R, S;
-};
-bool line_split(int nd, LineSplit* out);
-constexpr int kRows = 8;   // rows of one x2 group in the pair kernel (x2 = b2 + S2 a2, a2 < 8)
+bool grid_supported(int nd);   // stated FFT grids: N a multiple of 8 from 16 to 128
 
 struct Geom {
-  int nd = 0;          // grid points per axis
+  int nd = 0;          // stated grid points per axis
+  int nt = 0;          // points per axis of the transforms: the smallest alias-free multiple of 4 (<= nd)
   int npw = 0, ng = 0;
   int rw = 0, W = 0;   // wavefunction sphere half-width, W = 2 rw + 1
-  int rchi = 0, K = 0; // chi sphere half-width, K = 2 rchi + 1
+  int rchi = 0, K = 0; // chi sphere half-width (at least 1), K = 2 rchi + 1
+  int nl = 0;          // lines (n2, n3) of the chi sphere's box that the pair transform keeps
   int ngp = 0;         // ng rounded up to the contraction tile
-  LineSplit line{};    // split of the x3 (and x1) transforms
   int32_t* d_wf_map = nullptr;   // W^3 box -> wavefunction index or -1
-  int32_t* d_chi_map = nullptr;  // K^3 box -> chi index or -1
-  double2* d_tw64 = nullptr;     // exp(+2 pi i j / nd), j < nd
-  float2* d_tw32 = nullptr;
-  double2* d_twk64 = nullptr;    // [b][j] = exp(+2 pi i (j - rchi) b / nd), b < nd, j < K
-  float2* d_twk32 = nullptr;
+  int32_t* d_chi_map = nullptr;  // [n1][line] -> chi index or -1 (K x nl), then the row table (K x 3)
+  int32_t* d_rowtab = nullptr;   // per n2: first line minus its lowest n3, lowest and highest n3 (from 0)
+  // factors of the folded transforms (fold.h); j < nt / 4 counts the quads
+  double2* d_pts64 = nullptr;    // [n <= max(rw, rchi)][j] = (cos, sin)(2 pi n j / nt), quad 0: (1, cos or sin(n pi/2))
+  float2* d_pts32 = nullptr;
+  double2* d_tw64 = nullptr;     // exp(+2 pi i k / nt), k < nt (behind d_pts64)
+  double* d_fac64 = nullptr;     // [j][n <= rchi] cos, then sin; quad 0: cos or sin(n pi/2)
+  float* d_fac32 = nullptr;
+  float* d_amat = nullptr;       // [j][64] the same as MFMA blocks (behind d_fac32)
   bool has_q = false;            // cell and q given: the dielectric sphere's order was checked
   double q[3] = {0.0, 0.0, 0.0}; // reciprocal-lattice units
   double cell[9] = {};           // lattice vectors as rows (bohr)
+  // real-space bands are [x1][p2][row]: rows of nt values, padded to an odd number of 16-byte
+  // units so that the rows of a quad fall on different LDS banks
+  int row(bool fp64) const { return nt + (fp64 ? 1 : 2); }
+  size_t band_elems(bool fp64) const { return (size_t)nt * nt * row(fp64); }
+  size_t q_elems() const { return (size_t)nt * nl; }   // pair-transform intermediate, per pair
 };
 
 }  // namespace gw
@@ -135,8 +139,6 @@ hipError_t launch_band_to_real(const Geom& g, const double2* coef, int nrows, co
                                int nslot, void* tB, void* psi, hipStream_t st);
 size_t band_scratch_bytes(const Geom& g, int nslot, bool fp64);
 
-// Pair planes: Q[pair][p1][j2][j3] for pairs (v, c), v < nvs (multiple of 4), c < ncs (multiple of 8);
-// pair = v * ncs + c.
 // static COH self-energy (sigma.hip)
 int coh_max_states();
 hipError_t launch_coh_kernel(const void* eps_inv, const double* v, int ng, int ngp, void* at, hipStream_t st);
@@ -158,41 +160,19 @@ hipError_t launch_gpp_coh_sum(const void* part, int ngp, int ne, int ns, int sa,
 hipError_t launch_gpp(const void* eps0, int ng, const double* kvec, const int32_t* gvec, const void* rho, int half,
                       const double* omega, int nomega, double eta, void* modes, void* out, hipStream_t st);
 constexpr int kPairVariants = 7;   // forms of the pair kernel a tuned shape may name
-// minb: 0 = automatic, 1 or 2 = 256-thread kernel with that many resident workgroups per CU,
-// 3 / 4 = split-line kernel with 4 / 2 valence bands per workgroup, 5 = its lean form,
-// 6 / 7 = its direct-load form with 4 / 2 valence bands (a form not built for the instance
-// falls back to the 256-thread kernel).
+// Pair planes: Q[pair][x1][line] for pairs (v, c), v < nvs (multiple of 4), c < ncs (multiple of 8),
+// pair = v * ncs + c.  form: 0 automatic; a form that is not built for the sphere runs the
+// automatic one.
 template <typename T>
 hipError_t launch_pair_planes(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q,
-                              int minb, hipStream_t st);
+                              int form, hipStream_t st);
 // Pair finish: x1 transforms, 1/N, gather to the chi sphere: m[pair][ngp] (zero padded).
 template <typename T>
 hipError_t launch_pair_finish(const Geom& g, const void* q, int npair, void* m, hipStream_t st);
-bool pair_instance(int nd, int K);    // a compiled (N, R, K) instance exists
-bool pair_supported(int nd, int K);   // an instance, or the generic kernel (K <= kPairGenKMax, N split by line_split)
-int pair_radix(int nd, int K);   // line radix R of the (nd, K) instance, else line_split's (0 if none); must equal Geom::line.R
-constexpr int kPairGenKMax = 31;   // widest dielectric sphere (outputs per axis) of the generic pair kernel
-// (grid N, line radix R, pruned outputs K) of the compiled pair-transform instances
-#define GW_PAIR_CASES(X) \
-  X(24, 8, 5)            \
-  X(24, 8, 7)            \
-  X(24, 8, 9)            \
-  X(24, 8, 11)           \
-  X(48, 8, 15)           \
-  X(64, 16, 19)          \
-  X(72, 8, 9)            \
-  X(72, 8, 11)           \
-  X(72, 8, 13)           \
-  X(72, 8, 15)           \
-  X(72, 8, 17)           \
-  X(72, 8, 19)           \
-  X(96, 16, 17)          \
-  X(96, 16, 19)          \
-  X(96, 16, 21)          \
-  X(96, 16, 25)          \
-  X(128, 16, 23)         \
-  X(128, 16, 25)         \
-  X(128, 16, 27)
+constexpr int kMaxRc = 15;   // widest dielectric sphere of the pair kernels (31 outputs per axis)
+#define GW_RC_CASES(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
+// (stated grid, outputs per axis) whose coefficient gradients are offered
+bool coef_grad_offered(int nd, int K);
 
 
 // Weights of Eq. (chi0) per pair p = v * ncs + c (zero for padded pairs):
@@ -243,9 +223,9 @@ hipError_t launch_split_ab(const void* m, const double* w, int npair, int ngp, v
 // a = diag(s) m over npair rows of ngp, s_p = w_p or conj(w_p) (w as launch_weights writes it)
 hipError_t launch_weight_rows(const void* m, int npair, int ngp, const double* w, int nparts, bool conj_w, void* a,
                               hipStream_t st);
-// qbar[pair][p1][K^2] from mbar[pair][ngp]: the transpose of the pair finish stage
+// qbar[pair][x1][line] from mbar[pair][ngp]: the transpose of the pair finish stage
 hipError_t launch_qbar(const Geom& g, const void* mbar, int npair, void* qbar, hipStream_t st);
-// cond: ubar[c][x1][p2][p3] = sum_v h_vc u_v over the nvs valence slots (written);
+// cond: ubar[c][x1][p2][row] = sum_v h_vc u_v over the nvs valence slots (written);
 // else: ubar[v][...] += sum_c conj(h_vc) u_c over the ncs columns (added).  partner: the
 // other set's real-space bands (float64, band layout), qbar: pairs v * ncs + c.
 hipError_t launch_ubar(const Geom& g, const void* qbar, const void* partner, int nvs, int ncs, bool cond, void* ubar,
