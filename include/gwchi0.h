@@ -305,13 +305,15 @@ gw_status gw_pair_density(gw_ctx* ctx, const gw_chi0_problem* prob, int v0, int 
  *   hermitian 0: any chi0 (a dynamic one included): Gauss-Jordan elimination with partial
  *             pivoting.  1: a static chi0, Hermitian and negative semidefinite, with v > 0: then
  *             eps~ = I - V^1/2 chi0 V^1/2 is Hermitian positive definite, eps^-1 = V^1/2 eps~^-1
- *             V^-1/2, and eps~ is inverted by block sweeps (a Cholesky factor per 64 x 64 pivot
- *             block, no pivoting, half the arithmetic); only the lower triangle of chi0
+ *             V^-1/2, and eps~ is inverted by block sweeps (a 64 x 64 pivot block's inverse at a
+ *             time, no pivoting, half the arithmetic); only the lower triangle of chi0
  *             (i >= j) is read.  Other values: GW_EINVAL.
  *   vcoul     device, nbatch x ng doubles, v(q+G) including its normalisation.
  *   chi0      device complex128, nbatch x ng x ng row-major.
  *   eps_inv   device complex128 output, same shape; may not alias chi0.
- *   workspace device scratch of at least gw_eps_inv_workspace_size bytes (either route).
+ *   workspace device scratch (either route): gw_eps_inv_workspace_size bytes hold up to 16 of the
+ *             batch's matrices (within 4 GiB) and run them together; the size for nbatch = 1 is always
+ *             enough, and a size in between runs as many together as it holds.
  * Runs on the stream.  GW_ESINGULAR is reported by gw_eps_inv_status after the stream has
  * run: a zero or non-finite pivot, or with hermitian = 1 a pivot block that is not positive
  * definite or a v <= 0 (the output is then undefined; a chi0 that is not negative
@@ -321,7 +323,7 @@ gw_status gw_eps_inv(gw_ctx* ctx, int ng, int nbatch, int hermitian, const doubl
                      void* workspace, size_t ws_bytes, void* eps_inv);
 /* gw_eps_inv for callers that cannot allocate (code under HIP graph capture, serving loops,
  * harnesses that forbid hipMalloc): the same inverse and kernels, with the scratch in a static
- * device array of the library (about 68 MiB per GPU, set up when the first context is created
+ * device array of the library (about 70 MiB per GPU, set up when the first context is created
  * on a GPU and held until the process ends) instead of a workspace argument.  The caller passes
  * inputs, hermitian and outputs as for gw_eps_inv; the call allocates nothing.  ng <= 2048 (GW_EINVAL
  * beyond: use gw_eps_inv).  Every call on a GPU shares that GPU's array, so calls that overlap on

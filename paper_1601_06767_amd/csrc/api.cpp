@@ -674,7 +674,10 @@ gw_status gw_ctx_stage_times(gw_ctx* ctx, double* ms, long long* counts, int res
 gw_status gw_eps_inv_workspace_size(gw_ctx* ctx, int ng, int nbatch, size_t* bytes) {
   if (!ctx) return GW_EINVAL;
   if (ng < 1 || nbatch < 1 || !bytes) return gw::fail(ctx, GW_EINVAL, "bad arguments");
-  *bytes = std::max(gw::eps_inv_workspace(ng), gw::eps_inv_backward_workspace(ng));
+  // room for several matrices at once, within 4 GiB (one matrix is always enough)
+  const size_t one = gw::eps_inv_workspace(ng);
+  const size_t many = std::max<size_t>(1, std::min<size_t>({(size_t)nbatch, (size_t)gw::kMaxInvBatch, (size_t(4) << 30) / one}));
+  *bytes = std::max(many * one, gw::eps_inv_backward_workspace(ng));
   return GW_OK;
 }
 
@@ -684,7 +687,7 @@ namespace {
 // nbatch inverses on the context's stream: the pivoted Gauss-Jordan route, or the block sweeps
 // of the static (Hermitian) form
 gw_status eps_inv_batch(gw_ctx* ctx, int ng, int nbatch, int hermitian, const double* vcoul, const void* chi0,
-                        void* ws, void* eps_inv) {
+                        void* ws, size_t ws_bytes, void* eps_inv) {
   int prev = 0;
   (void)hipGetDevice(&prev);
   (void)hipSetDevice(ctx->device);
@@ -692,12 +695,16 @@ gw_status eps_inv_batch(gw_ctx* ctx, int ng, int nbatch, int hermitian, const do
     GW_HIP(ctx, gw::launch_flag_clear(ctx->d_pivot_flag, ctx->stream));
     gw::StageScope sc(ctx, gw::kStageEpsInv);
     const size_t nn = (size_t)ng * ng;
-    for (int b = 0; b < nbatch; ++b) {
+    // as many matrices together as the workspace holds
+    const size_t fit = std::min<size_t>(gw::kMaxInvBatch, ws_bytes / gw::eps_inv_workspace(ng));
+    for (int b = 0; b < nbatch;) {
+      const int nb = (int)std::min<size_t>(nbatch - b, fit);
       const double* v = vcoul + (size_t)b * ng;
       const double2* c = (const double2*)chi0 + b * nn;
       double2* z = (double2*)eps_inv + b * nn;
-      GW_HIP(ctx, hermitian ? gw::launch_eps_inv_sweep(ng, v, c, z, ws, ctx->d_pivot_flag, ctx->stream)
-                            : gw::launch_eps_inv(ng, v, c, z, ws, ctx->d_pivot_flag, ctx->stream));
+      GW_HIP(ctx, hermitian ? gw::launch_eps_inv_sweep(ng, nb, v, c, z, ws, ctx->d_pivot_flag, ctx->stream)
+                            : gw::launch_eps_inv(ng, nb, v, c, z, ws, ctx->d_pivot_flag, ctx->stream));
+      b += nb;
     }
     return GW_OK;
   };
@@ -717,7 +724,7 @@ gw_status gw_eps_inv(gw_ctx* ctx, int ng, int nbatch, int hermitian, const doubl
   if (chi0 == eps_inv) return gw::fail(ctx, GW_EINVAL, "eps_inv may not alias chi0");
   if (ws_bytes < gw::eps_inv_workspace(ng))
     return gw::fail(ctx, GW_EINVAL, "workspace too small: need " + std::to_string(gw::eps_inv_workspace(ng)));
-  return eps_inv_batch(ctx, ng, nbatch, hermitian, vcoul, chi0, workspace, eps_inv);
+  return eps_inv_batch(ctx, ng, nbatch, hermitian, vcoul, chi0, workspace, ws_bytes, eps_inv);
 }
 
 gw_status gw_eps_inv_noalloc(gw_ctx* ctx, int ng, int nbatch, int hermitian, const double* vcoul, const void* chi0,
@@ -731,7 +738,7 @@ gw_status gw_eps_inv_noalloc(gw_ctx* ctx, int ng, int nbatch, int hermitian, con
                                         std::to_string(gw::kNoAllocMaxNg) + " (use gw_eps_inv with a workspace)");
   void* scratch = gw::noalloc_scratch(ctx->device);
   if (!scratch) return gw::fail(ctx, GW_EDEVICE, "allocation-free scratch not set up on this device");
-  return eps_inv_batch(ctx, ng, nbatch, hermitian, vcoul, chi0, scratch, eps_inv);
+  return eps_inv_batch(ctx, ng, nbatch, hermitian, vcoul, chi0, scratch, gw::noalloc_scratch_bytes(), eps_inv);
 }
 
 gw_status gw_eps_inv_status(gw_ctx* ctx) {

@@ -2,20 +2,22 @@
 // stated before Eq. (chi0); Table 3's eps_inf = 1/[eps^-1]_00).
 //
 // Inversion: in-place Gauss-Jordan elimination with partial (row) pivoting, blocked by
-// panels of kNb columns.  The panel columns (all rows) are copied to a buffer and each
-// pivot step is one launch that reads the panel from one buffer and writes the updated
-// panel (rows j and p interchanged, pivot row scaled, column j eliminated) to the other;
-// the same launch leaves one pivot candidate per workgroup for the next column, so that
-// the next step finds its pivot by reducing those candidates.  After the panel, its row
-// interchanges are applied to the other columns, the panel holds the columns T[:, J] of
+// panels of kNb columns.  The panel columns (all rows) are copied to a buffer; one workgroup
+// takes S of them at a time into registers and runs their S pivot steps there (k_gj_sub), and a
+// launch over all rows brings the panel's other columns up to date (k_gj_apply); matrices with more
+// rows than its registers hold take one launch per pivot step instead (k_gj_step16).  After the panel,
+// its row interchanges are applied to the other columns, the panel holds the columns T[:, J] of
 // the accumulated elimination transform, and the remaining columns are brought up to
 // date with one rank-kNb update A[:, rest] += (T[:, J] - I[:, J]) A_old[J, rest] on
 // float64 MFMA.  The column interchanges implied by the row pivots are undone at the
 // end.  A zero or non-finite pivot raises a device flag read by gw_eps_inv_status.
+// Several matrices of a batch run together (blockIdx.y), each in its own slice of the workspace.
 //
 // zgemm: C = alpha op(A) op(B) + beta C for complex128 row-major matrices, op = identity
 // or conjugate transpose, on MFMA f64 16x16x4 with 64 x 64 tiles.
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "internal.h"
@@ -30,14 +32,19 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-__global__ void k_form_eps(const double* __restrict__ v, const double2* __restrict__ chi, int n,
+// blockIdx.y: matrix of the batch; v, chi and out advance by one matrix, the workspace by ws bytes
+template <typename T> __device__ __forceinline__ T* slice(T* p, size_t ws) {
+  return (T*)((char*)p + (size_t)blockIdx.y * ws);
+}
+
+__global__ void k_form_eps(const double* __restrict__ v, const double2* __restrict__ chi, int n, size_t ws,
                            double2* __restrict__ eps) {
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (size_t)n * n) return;
   const int i = (int)(e / n), j = (int)(e % n);
-  const double2 c = chi[e];
-  const double vi = v[i];
-  eps[e] = double2{(i == j ? 1.0 : 0.0) - vi * c.x, -vi * c.y};
+  const double2 c = chi[(size_t)blockIdx.y * n * n + e];
+  const double vi = v[(size_t)blockIdx.y * n + i];
+  slice(eps, ws)[e] = double2{(i == j ? 1.0 : 0.0) - vi * c.x, -vi * c.y};
 }
 
 __global__ void k_flag_clear(int* flag) {
@@ -46,29 +53,164 @@ __global__ void k_flag_clear(int* flag) {
 
 constexpr int kStepRows = 4;   // rows per workgroup of the panel kernels (one kNb-wide row per wave)
 
-// candidate (|x|^2, row) of one workgroup's rows i >= i0 in panel column col (row index
-// n and -1 when none qualifies); the larger value wins, the lower row on ties
-__device__ __forceinline__ void step_candidate(const double2* __restrict__ p, int n, int i0, int col, double* cm,
-                                               int* ci) {
-  __shared__ double s_m[kStepRows];
-  __shared__ int s_i[kStepRows];
-  const int r = threadIdx.x >> 6;
-  const int i = blockIdx.x * kStepRows + r;
-  if ((threadIdx.x & 63) == 0) {
-    double m = -1.0;
-    if (i < n && i >= i0) {
-      const double2 x = p[(size_t)i * kNb + col];
-      m = x.x * x.x + x.y * x.y;
+// Panel columns [j0, j0 + nbp) of a into p (n x kNb, zero padded).
+__global__ __launch_bounds__(256) void k_panel_load(const double2* __restrict__ a, int n, int j0, int nbp, size_t ws,
+                                                    double2* __restrict__ p) {
+  const int i = blockIdx.x * kStepRows + (threadIdx.x >> 6);
+  const int c = threadIdx.x & 63;
+  if (i < n) slice(p, ws)[(size_t)i * kNb + c] = c < nbp ? slice(a, ws)[(size_t)i * n + j0 + c] : double2{0.0, 0.0};
+}
+
+// Largest of a wave's values, in every lane (data-parallel-primitive moves: no LDS).
+__device__ __forceinline__ unsigned wave_max(unsigned k) {
+  auto step = [](unsigned x, auto ctrl, auto rows) {
+    const unsigned y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+    return x > y ? x : y;
+  };
+  using std::integral_constant;
+  k = step(k, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});   // row_shr 1, 2, 4, 8
+  k = step(k, integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+  k = step(k, integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+  k = step(k, integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+  k = step(k, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});   // row_bcast 15, 31
+  k = step(k, integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+  return (unsigned)__builtin_amdgcn_readlane((int)k, 63);
+}
+
+// 1 / d for a normal d > 0: the hardware estimate and two Newton steps
+__device__ __forceinline__ double recip(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  return fma(fma(-d, r, 1.0), r, r);
+}
+
+// The S pivot steps of the panel columns [c0, c0 + sc), sc <= S, in one workgroup: each thread holds R
+// rows of the S columns in registers.  Per step: the pivot as the largest |x|^2 of the rows from
+// j on (compared to 2^-9 relative, the lower row on ties, so that value and row share one 32-bit key),
+// its row and row j through LDS, then row j <- row p / d, row p <- row j (old) eliminated, every other
+// row eliminated, column <- the corresponding column of the transform.  Register column 0 is the
+// step's pivot column and every step rotates the columns by one: the loop stays rolled (unrolled, a
+// launch spent its time on instruction fetch, 18 us per step).  Serial: two barriers and a
+// reduction per step.
+constexpr int kGjThreads = 512;
+constexpr int kGjMaxRows = 2048;   // rows the registers hold, and row numbers a key holds
+template <int R, int S>
+__global__ __launch_bounds__(kGjThreads) void k_gj_sub(const double2* __restrict__ pin, int n, int j0, int c0, int sc,
+                                                       size_t ws, double2* __restrict__ tout, int* __restrict__ piv,
+                                                       int* __restrict__ flag) {
+  static_assert(R * kGjThreads <= kGjMaxRows, "row numbers of a key");
+  constexpr int NW = kGjThreads / 64;
+  __shared__ __align__(16) unsigned s_key[2][NW];
+  __shared__ double2 s_prow[2][S], s_rowj[2][S];
+  pin = slice(pin, ws);
+  tout = slice(tout, ws);
+  piv = slice(piv, ws);
+  const int tid = threadIdx.x;
+  double2 x[R][S];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = tid + kGjThreads * r;
+#pragma unroll
+    for (int c = 0; c < S; ++c)
+      x[r][c] = i < n && c < sc ? pin[(size_t)i * kNb + c0 + c] : double2{0.0, 0.0};
+  }
+#pragma unroll 1
+  for (int jc = 0; jc < sc; ++jc) {
+    const int j = j0 + c0 + jc, b = jc & 1;
+    unsigned key = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = tid + kGjThreads * r;
+      const double m = x[r][0].x * x[r][0].x + x[r][0].y * x[r][0].y;
+      const unsigned k = ((unsigned)(__double_as_longlong(m) >> 32) & ~(unsigned)(kGjMaxRows - 1)) | (kGjMaxRows - 1 - i);
+      if (i >= j && i < n && k > key) key = k;
     }
+    key = wave_max(key);
+    if ((tid & 63) == 0) s_key[b][tid >> 6] = key;
+    __syncthreads();
+    key = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) key = max(key, s_key[b][w]);
+    const int p = __builtin_amdgcn_readfirstlane(kGjMaxRows - 1 - (int)(key & (kGjMaxRows - 1)));   // some row >= j
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = tid + kGjThreads * r;
+      if (i == p) {
+#pragma unroll
+        for (int c = 0; c < S; ++c) s_prow[b][c] = x[r][c];
+      }
+      if (i == j) {
+#pragma unroll
+        for (int c = 0; c < S; ++c) s_rowj[b][c] = x[r][c];
+      }
+    }
+    __syncthreads();
+    const double2 d = s_prow[b][0];
+    const double den = d.x * d.x + d.y * d.y;
+    if (tid == 0) {
+      piv[j] = p;
+      if (!(den > 0.0) || !isfinite(den)) *flag = 1;
+    }
+    const double rden = den > 0.0 ? recip(den) : 0.0;
+    const double2 dinv{d.x * rden, -d.y * rden};
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = tid + kGjThreads * r;
+      if (i == p) {   // (p == j: row j itself, replaced below)
+#pragma unroll
+        for (int c = 0; c < S; ++c) x[r][c] = s_rowj[b][c];
+      }
+      // every row but j: x - f q; row j: q / d = 0 - (-1/d) q
+      const bool isj = i == j;
+      double2 f = cmul(x[r][0], dinv);
+      if (isj) f = double2{-dinv.x, -dinv.y};
+#pragma unroll
+      for (int c = 0; c + 1 < S; ++c) {
+        const double2 q = s_prow[b][c + 1];
+        double2 y = x[r][c + 1];
+        if (isj) y = double2{0.0, 0.0};
+        x[r][c].x = fma(f.y, q.y, fma(-f.x, q.x, y.x));
+        x[r][c].y = fma(-f.y, q.x, fma(-f.x, q.y, y.y));
+      }
+      x[r][S - 1] = double2{-f.x, -f.y};
+    }
+    // the LDS rows and keys alternate between two sets: a wave that runs ahead into the next step
+    // writes the other one
+  }
+  // after sc rotations register column c is panel column (sc + c) mod S
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = tid + kGjThreads * r;
+    if (i < n) {
+#pragma unroll
+      for (int c = 0; c < S; ++c) {
+        const int k = sc + c;
+        tout[(size_t)i * S + (k >= S ? k - S : k)] = x[r][c];
+      }
+    }
+  }
+}
+
+// Larger matrices: one launch per pivot step on a sub-panel of kGjSub columns (t buffers, n x kGjSub),
+// all rows over the chip; the launch also leaves one pivot candidate (largest |x|^2, its row; the
+// lower row on ties) per workgroup for the next step's column.
+constexpr int kGjSub = 16;      // widest sub-panel
+constexpr int kGjRows = 16;     // rows per workgroup of these launches (16 columns each)
+__device__ __forceinline__ void gj_candidate(double m, int i, double* cm, int* ci) {
+  // the 16 rows of the workgroup: thread 16 r holds row r's value
+  __shared__ double s_m[kGjRows];
+  __shared__ int s_i[kGjRows];
+  const int r = threadIdx.x >> 4;
+  if ((threadIdx.x & 15) == 0) {
     s_m[r] = m;
-    s_i[r] = (i < n && i >= i0) ? i : n;
+    s_i[r] = i;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     double best = -1.0;
-    int bi = n;
-    for (int k = 0; k < kStepRows; ++k)
-      if (s_i[k] < n && (s_m[k] > best || (s_m[k] == best && s_i[k] < bi))) {
+    int bi = 0x7fffffff;
+    for (int k = 0; k < kGjRows; ++k)
+      if (s_m[k] > best || (s_m[k] == best && s_i[k] < bi)) {
         best = s_m[k];
         bi = s_i[k];
       }
@@ -77,98 +219,132 @@ __device__ __forceinline__ void step_candidate(const double2* __restrict__ p, in
   }
 }
 
-// Panel columns [j0, j0 + nbp) of a into p (n x kNb, zero padded) and the pivot
-// candidates of its first column.
-__global__ __launch_bounds__(256) void k_panel_load(const double2* __restrict__ a, int n, int j0, int nbp,
-                                                    double2* __restrict__ p, double* __restrict__ cm,
-                                                    int* __restrict__ ci) {
-  const int i = blockIdx.x * kStepRows + (threadIdx.x >> 6);
-  const int c = threadIdx.x & 63;
-  if (i < n) p[(size_t)i * kNb + c] = c < nbp ? a[(size_t)i * n + j0 + c] : double2{0.0, 0.0};
-  __syncthreads();
-  step_candidate(p, n, j0, 0, cm, ci);
+__global__ __launch_bounds__(256) void k_gj_load16(const double2* __restrict__ pin, int n, int j0, int c0, int sc,
+                                                   size_t ws, double2* __restrict__ t, double* __restrict__ cm,
+                                                   int* __restrict__ ci) {
+  pin = slice(pin, ws);
+  t = slice(t, ws);
+  const int i = blockIdx.x * kGjRows + (threadIdx.x >> 4), c = threadIdx.x & 15;
+  double2 x{0.0, 0.0};
+  if (i < n && c < sc) x = pin[(size_t)i * kNb + c0 + c];
+  if (i < n) t[(size_t)i * kGjSub + c] = x;
+  gj_candidate(i < n && i >= j0 + c0 ? x.x * x.x + x.y * x.y : -1.0, i, slice(cm, ws), slice(ci, ws));
 }
 
-// One pivot step j = j0 + jc on the panel: pivot p from the candidates, then
-// row j <- row p / d, row p <- row j (old) eliminated, every other row eliminated,
-// column jc <- the corresponding column of the transform.  Reads pin, writes pout.
-__global__ __launch_bounds__(256) void k_gj_step(const double2* __restrict__ pin, double2* __restrict__ pout, int n,
-                                                 int j0, int jc, int nbp, const double* __restrict__ cm_in,
-                                                 const int* __restrict__ ci_in, int ncand, double* __restrict__ cm_out,
-                                                 int* __restrict__ ci_out, int* __restrict__ piv,
-                                                 int* __restrict__ flag) {
-  __shared__ double s_m[256];
-  __shared__ int s_i[256];
-  __shared__ double2 s_prow[kNb], s_rowj[kNb];
-  const int t = threadIdx.x;
-  const int j = j0 + jc;
+__global__ __launch_bounds__(256) void k_gj_step16(const double2* __restrict__ tin, double2* __restrict__ tout, int n,
+                                                   int j, int jc, int ncand, size_t ws, const double* __restrict__ cm_in,
+                                                   const int* __restrict__ ci_in, double* __restrict__ cm_out,
+                                                   int* __restrict__ ci_out, int* __restrict__ piv,
+                                                   int* __restrict__ flag) {
+  __shared__ double s_m[4];
+  __shared__ int s_i[4];
+  tin = slice(tin, ws);
+  tout = slice(tout, ws);
+  cm_in = slice(cm_in, ws);
+  ci_in = slice(ci_in, ws);
+  const int tid = threadIdx.x, i = blockIdx.x * kGjRows + (tid >> 4), c = tid & 15;
+  double2 x{0.0, 0.0};
+  if (i < n) x = tin[(size_t)i * kGjSub + c];
   double best = -1.0;
-  int bi = n;
-  for (int k = t; k < ncand; k += blockDim.x) {
-    const double m = cm_in[k];
-    const int i = ci_in[k];
-    if (i < n && (m > best || (m == best && i < bi))) {
+  int bi = 0x7fffffff;
+  auto take = [&](double m, int k) {
+    if (m > best || (m == best && k < bi)) {
       best = m;
-      bi = i;
+      bi = k;
     }
+  };
+  for (int k = tid; k < ncand; k += 256) take(cm_in[k], ci_in[k]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const double m = __shfl_xor(best, o, 64);
+    const int k = __shfl_xor(bi, o, 64);
+    take(m, k);
   }
-  s_m[t] = best;
-  s_i[t] = bi;
-  __syncthreads();
-  for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-    if (t < h) {
-      const double m = s_m[t + h];
-      const int i = s_i[t + h];
-      if (i < n && (m > s_m[t] || (m == s_m[t] && i < s_i[t]))) {
-        s_m[t] = m;
-        s_i[t] = i;
-      }
-    }
-    __syncthreads();
-  }
-  const double pm = s_m[0];
-  const int p = s_i[0] < n ? s_i[0] : j;   // no finite candidate: keep row j, the flag reports it
-  if (blockIdx.x == 0 && t == 0) {
-    piv[j] = p;
-    if (!(pm > 0.0) || !isfinite(pm)) *flag = 1;
-  }
-  if (t < kNb) {
-    s_prow[t] = pin[(size_t)p * kNb + t];
-    s_rowj[t] = pin[(size_t)j * kNb + t];
+  if ((tid & 63) == 0) {
+    s_m[tid >> 6] = best;
+    s_i[tid >> 6] = bi;
   }
   __syncthreads();
-  const double2 d = s_prow[jc];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) take(s_m[w], s_i[w]);
+  const int p = best >= 0.0 && bi < n ? bi : j;   // no finite candidate: keep row j, the flag reports it
+  if (blockIdx.x == 0 && tid == 0) {
+    slice(piv, ws)[j] = p;
+    if (!(best > 0.0) || !isfinite(best)) *flag = 1;
+  }
+  const double2 d = tin[(size_t)p * kGjSub + jc], q = tin[(size_t)p * kGjSub + c];
   const double den = d.x * d.x + d.y * d.y;
   const double2 dinv = den > 0.0 ? double2{d.x / den, -d.y / den} : double2{0.0, 0.0};
-  const int i = blockIdx.x * kStepRows + (t >> 6);
-  const int c = t & 63;
+  double2 out{0.0, 0.0};
   if (i < n) {
-    double2 out;
     if (i == j) {
-      out = c == jc ? dinv : cmul(s_prow[c], dinv);
+      out = c == jc ? dinv : cmul(q, dinv);
     } else {
-      const double2 x = i == p ? s_rowj[c] : pin[(size_t)i * kNb + c];
-      const double2 f = i == p ? s_rowj[jc] : pin[(size_t)i * kNb + jc];
-      const double2 fp = cmul(f, dinv);
-      if (c == jc) {
-        out = double2{-fp.x, -fp.y};
-      } else {
-        const double2 r = cmul(fp, s_prow[c]);
-        out = double2{x.x - r.x, x.y - r.y};
-      }
+      const int src = i == p ? j : i;
+      if (i == p) x = tin[(size_t)j * kGjSub + c];
+      const double2 f = cmul(tin[(size_t)src * kGjSub + jc], dinv);
+      const double2 r = cmul(f, q);
+      out = c == jc ? double2{-f.x, -f.y} : double2{x.x - r.x, x.y - r.y};
     }
-    pout[(size_t)i * kNb + c] = out;
+    tout[(size_t)i * kGjSub + c] = out;
   }
-  if (jc + 1 < nbp) {
-    __syncthreads();
-    step_candidate(pout, n, j + 1, jc + 1, cm_out, ci_out);
+  // candidate of the next column: its value sits in lane jc + 1 of the row's 16
+  const double m = out.x * out.x + out.y * out.y;
+  const double mn = __shfl(m, ((tid & 63) & ~15) + min(jc + 1, 15), 64);
+  gj_candidate(i < n && i > j ? mn : -1.0, i, slice(cm_out, ws), slice(ci_out, ws));
+}
+
+// The panel's other columns after S pivot steps (columns [c0, c0 + sc), rows J = j0 + c0 ..): with the
+// steps' row interchanges, out[i][c] = in[src(i)][c] + sum_k (T - I)[i][k] in[src(J_k)][c], and T itself
+// in the columns c0 ...  Reads pin, writes pout.
+template <int S>
+__global__ __launch_bounds__(256) void k_gj_apply(const double2* __restrict__ pin, double2* __restrict__ pout, int n,
+                                                  int j0, int c0, int sc, size_t ws, const double2* __restrict__ t,
+                                                  const int* __restrict__ piv) {
+  __shared__ double2 s_row[S][kNb];
+  pin = slice(pin, ws);
+  pout = slice(pout, ws);
+  t = slice(t, ws);
+  piv = slice(piv, ws);
+  const int jb = j0 + c0;
+  int pv[S];
+#pragma unroll
+  for (int k = 0; k < S; ++k) pv[k] = k < sc ? piv[jb + k] : jb + k;
+  auto source = [&](int i) {   // the row whose old content ends up in row i
+#pragma unroll
+    for (int k = S - 1; k >= 0; --k) {
+      const int a = jb + k;
+      i = i == a ? pv[k] : (i == pv[k] ? a : i);
+    }
+    return i;
+  };
+  const int wave = threadIdx.x >> 6, c = threadIdx.x & 63;
+  for (int k = wave; k < sc; k += 4) s_row[k][c] = pin[(size_t)source(jb + k) * kNb + c];
+  __syncthreads();
+  const int i = blockIdx.x * kStepRows + wave;
+  if (i >= n) return;
+  double2 out;
+  if (c >= c0 && c < c0 + sc) {
+    out = t[(size_t)i * S + c - c0];
+  } else {
+    out = pin[(size_t)source(i) * kNb + c];
+    for (int k = 0; k < sc; ++k) {
+      double2 f = t[(size_t)i * S + k];
+      if (i == jb + k) f.x -= 1.0;
+      const double2 q = s_row[k][c];
+      out.x = fma(-f.y, q.y, fma(f.x, q.x, out.x));
+      out.y = fma(f.y, q.x, fma(f.x, q.y, out.y));
+    }
   }
+  pout[(size_t)i * kNb + c] = out;
 }
 
 // The panel's row interchanges, in order, on the columns outside the panel.
-__global__ void k_row_swaps(double2* __restrict__ a, int n, int j0, int nbp, const int* __restrict__ piv) {
+__global__ void k_row_swaps(double2* __restrict__ a, int n, int j0, int nbp, size_t ws, const int* __restrict__ piv) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n || (c >= j0 && c < j0 + nbp)) return;
+  a = slice(a, ws);
+  piv = slice(piv, ws);
   for (int j = j0; j < j0 + nbp; ++j) {
     const int p = piv[j];
     if (p != j && p >= 0 && p < n) {
@@ -179,12 +355,15 @@ __global__ void k_row_swaps(double2* __restrict__ a, int n, int j0, int nbp, con
   }
 }
 
-// The finished panel T[:, J] back into a, and the operands of the rank-nbp update:
-// bp = T[:, J] - I[:, J] (in place in the panel buffer, n x kNb), tmp = A[J, :] with the
-// panel columns zeroed (kNb x n).
-__global__ void k_panel_operands(double2* __restrict__ a, int n, int j0, int nbp, double2* __restrict__ bp,
+// The finished panel T[:, J] back into a, and the operands of the rank-nbp update, 64 values per row:
+// bp = T[:, J] - I[:, J] (in place in the panel buffer), tmp[col] = conj(A[J, col]), zero for the panel's
+// own columns.
+__global__ void k_panel_operands(double2* __restrict__ a, int n, int j0, int nbp, size_t ws, double2* __restrict__ bp,
                                  double2* __restrict__ tmp) {
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  a = slice(a, ws);
+  bp = slice(bp, ws);
+  tmp = slice(tmp, ws);
   if (e < (size_t)n * kNb) {
     const int i = (int)(e / kNb), c = (int)(e % kNb);
     double2 x{0.0, 0.0};
@@ -195,34 +374,50 @@ __global__ void k_panel_operands(double2* __restrict__ a, int n, int j0, int nbp
     }
     bp[e] = x;
   }
-  if (e < (size_t)kNb * n) {
-    const int c = (int)(e / n), col = (int)(e % n);
-    double2 x{0.0, 0.0};
-    if (c < nbp && (col < j0 || col >= j0 + nbp)) x = a[(size_t)(j0 + c) * n + col];
-    tmp[e] = x;
-  }
-}
-
-__global__ void k_col_perm(const int* __restrict__ piv, int n, int* __restrict__ idx) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  for (int c = 0; c < n; ++c) idx[c] = c;
-  for (int j = n - 1; j >= 0; --j) {
-    const int p = piv[j];
-    if (p != j && p >= 0 && p < n) {
-      const int t = idx[j];
-      idx[j] = idx[p];
-      idx[p] = t;
+  // 8 columns by 8 rows of J per 64 threads: reads of whole 128-byte pieces of a row
+  const int n8 = (n + 7) / 8;
+  if (e < (size_t)n8 * 8 * kNb) {
+    const int g = (int)(e / 64), l = (int)(e % 64);
+    const int col = (g % n8) * 8 + (l & 7), c = (g / n8) * 8 + (l >> 3);
+    if (col < n) {
+      double2 x{0.0, 0.0};
+      if (c < nbp && (col < j0 || col >= j0 + nbp)) {
+        x = a[(size_t)(j0 + c) * n + col];
+        x.y = -x.y;
+      }
+      tmp[(size_t)col * kNb + c] = x;
     }
   }
 }
 
-__global__ void k_gather_cols(const double2* __restrict__ src, const int* __restrict__ idx, int n,
+// out[:, c] = src[:, idx(c)], idx the columns after undoing the interchanges: idx(c) follows position c
+// through the swaps (j, piv[j]), first to last.
+__global__ __launch_bounds__(256) void k_col_perm(const int* __restrict__ piv, int n, size_t ws, int* __restrict__ idx) {
+  __shared__ int s_p[1024];
+  piv = slice(piv, ws);
+  idx = slice(idx, ws);
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  int x = c;
+  for (int b = 0; b < n; b += 1024) {
+    const int m = min(1024, n - b);
+    __syncthreads();
+    for (int k = threadIdx.x; k < m; k += blockDim.x) s_p[k] = piv[b + k];
+    __syncthreads();
+    for (int k = 0; k < m; ++k) {
+      const int p = s_p[k], j = b + k;
+      x = x == j ? p : (x == p ? j : x);
+    }
+  }
+  if (c < n) idx[c] = x;
+}
+
+__global__ void k_gather_cols(const double2* __restrict__ src, const int* __restrict__ idx, int n, size_t ws,
                               double2* __restrict__ dst) {
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (size_t)n * n) return;
   const size_t i = e / n;
   const int c = (int)(e % n);
-  dst[e] = src[i * n + idx[c]];
+  dst[(size_t)blockIdx.y * n * n + e] = slice(src, ws)[i * n + slice(idx, ws)[c]];
 }
 
 // ---------------------------------------------------------------- zgemm
@@ -238,7 +433,10 @@ __device__ __forceinline__ double2 opget(const double2* x, int ld, int r, int k,
 
 __global__ __launch_bounds__(256) void k_zgemm(int m, int n, int kd, double2 alpha, const double2* __restrict__ A,
                                                int lda, int opa, const double2* __restrict__ B, int ldb, int opb,
-                                               double2 beta, double2* __restrict__ C, int ldc) {
+                                               double2 beta, double2* __restrict__ C, int ldc, size_t ws) {
+  A = slice(A, ws);   // a batch (blockIdx.y): the three operands advance by ws bytes
+  B = slice(B, ws);
+  C = slice(C, ws);
   __shared__ double2 sA[ZK][ZT + 1];   // sA[k][row]
   __shared__ double2 sB[ZK][ZT + 1];   // sB[k][col]
   const int tiles_n = (n + ZT - 1) / ZT;
@@ -321,20 +519,22 @@ __global__ __launch_bounds__(256) void k_zgemm(int m, int n, int kd, double2 alp
 // ---------------------------------------------------------------- static inverse by block sweeps
 // For a static chi0 (Hermitian, negative semidefinite) and v > 0, eps~ = I - V^1/2 chi0 V^1/2 is
 // Hermitian positive definite and eps^-1 = V^1/2 eps~^-1 V^-1/2.  The sweep operator on a block K
-// of 64 indices, D = A_KK:
-//   A_ij -= A_iK D^-1 A_Kj (i, j outside K),  A_iK <- A_iK D^-1,  A_Kj <- D^-1 A_Kj,  A_KK <- -D^-1;
+// of 64 indices, D = A_KK, X = A_.K, P = X D^-1:
+//   A_ij -= P_i X_j^H (i, j outside K),  A_iK <- P_i,  A_Kj <- P_j^H,  A_KK <- -D^-1;
 // sweeping every block in turn leaves -A^-1.  The part not yet swept is a Schur complement of
-// eps~, positive definite, so D needs no pivoting: D = L L^H, and the update is the Hermitian
-// rank-64 product A -= C C^H with C = A_.K L^-H, on the lower 64 x 64 tiles only (the float64
-// MFMA contraction tile).  Only the lower triangle is stored.  Half the arithmetic of the
-// pivoted Gauss-Jordan path and four launches per block of 64 instead of about 68.
+// eps~, positive definite, so D needs no pivoting.  Only the lower triangle is stored: half the
+// arithmetic of the pivoted Gauss-Jordan path and three launches per block of 64 (D^-1 in one
+// workgroup, P, the rank-64 update of the lower tiles).
 constexpr int kSw = 64;
 
 // lower triangle a[i][j] = delta_ij - sqrt(v_i) chi_ij sqrt(v_j) (i >= j), identity in the padding
-__global__ void k_sweep_form(const double* __restrict__ v, const double2* __restrict__ chi, int n, int ldp,
+__global__ void k_sweep_form(const double* __restrict__ v, const double2* __restrict__ chi, int n, int ldp, size_t ws,
                              double2* __restrict__ a, int* __restrict__ flag) {
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (size_t)ldp * ldp) return;
+  v += (size_t)blockIdx.y * n;
+  chi += (size_t)blockIdx.y * n * n;
+  a = slice(a, ws);
   const int i = (int)(e / ldp), j = (int)(e % ldp);
   if (j > i) return;
   double2 x{i == j ? 1.0 : 0.0, 0.0};
@@ -352,197 +552,349 @@ __global__ void k_sweep_form(const double* __restrict__ v, const double2* __rest
   a[e] = x;
 }
 
-// one workgroup: D = A_KK (lower) = L L^H in LDS, X = L^-1, then linvT[l][k] = X[k][l] and
-// dinv = X^H X = D^-1 (full 64 x 64).  A pivot that is not positive sets the flag.
-// One barrier per step: step j of the factorisation subtracts the outer product of column j
-// divided by its pivot d_j from the trailing triangle, and scales column j - 1 by 1/sqrt(d_{j-1})
-// (no one reads that column in step j); step j of the inversion (rows of L X = I from the top)
-// subtracts L[i][j] / L[j][j] times row j from the rows below and scales row j - 1 likewise.
-// Threads cover the (row, column) ranges on a fixed 16 x 16 grid (no integer division), and
-// D^-1 is formed in 4 x 4 blocks per thread.  (Measured at NG 8000: 176 us per block with three
-// barriers per factorisation step, divisions in the index arithmetic and the inverse by one
-// thread per column; the 125 blocks were 22 of the 75 ms of the inverse.)
-__global__ __launch_bounds__(256) void k_sweep_diag(const double2* __restrict__ a, int ldp, int k0,
-                                                    double2* __restrict__ linvT, double2* __restrict__ dinv,
-                                                    int* __restrict__ flag) {
-  __shared__ double2 L[kSw][kSw + 1];
-  __shared__ double2 X[kSw][kSw + 1];
-  __shared__ double dv[kSw];   // pivots d_j, then 1 / L[j][j]
-  const int tid = threadIdx.x;
-  const int ty = tid >> 4, tx = tid & 15;
-  for (int e = tid; e < kSw * kSw; e += 256) {
-    const int r = e / kSw, c = e % kSw;
-    L[r][c] = c <= r ? a[(size_t)(k0 + r) * ldp + k0 + c] : double2{0.0, 0.0};
-    X[r][c] = double2{r == c ? 1.0 : 0.0, 0.0};
+// D^-1 of a 64 x 64 Hermitian pivot block by 64 Gauss-Jordan steps, a thread of 256 holding a 4 x 4
+// piece [p][q] of rows ty + 16 p and columns tx + 16 q in registers.  Step j sweeps index j:
+// A_jj <- -1/d, A_ij <- A_ij / d, A_ji <- conj(A_ij) / d, A_ik -= A_ij conj(A_kj) / d, Hermitian throughout,
+// so it needs column j only, which its owners leave in LDS for the next step: one barrier, eight LDS
+// reads and 64 FMAs per step.  Row and column j come out of the same update with the factors -1/d for
+// A_jj / d and -1 for A_jj, from zeroed entries.  A pivot that is not positive sets the flag.  (A Cholesky
+// factor, its inverse and their product, all in LDS, took 126 us per block.)
+__device__ __forceinline__ void diag_inverse(double (&xr)[4][4], double (&xi)[4][4], double2 (*s_col)[kSw],
+                                             double2* __restrict__ dinv, int* __restrict__ flag) {
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  if (tx == 0) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) s_col[0][ty + 16 * p] = double2{xr[p][0], xi[p][0]};
   }
   __syncthreads();
-  // factorisation: L[i][k] -= L[i][j] conj(L[k][j]) / d_j for j < k <= i
-  for (int j = 0; j <= kSw; ++j) {
-    if (j < kSw) {
-      double d = L[j][j].x;
-      if (!(d > 0.0) || !isfinite(d)) {
-        if (tid == 0) atomicOr(flag, 1);
-        d = 1.0;
+  auto block = [&](auto jbc) {   // sixteen steps whose row and column sit in piece jb
+    constexpr int jb = decltype(jbc)::value;
+#pragma unroll 1
+    for (int jt = 0; jt < 16; ++jt) {
+      const int j = 16 * jb + jt;
+      const double2* col = s_col[j & 1];
+      double d = col[j].x;
+      const bool bad = !(d > 0.0) || !isfinite(d);
+      if (bad) d = 1.0;
+      if (bad && tid == 0) atomicOr(flag, 1);
+      const double rd = recip(d);
+      const bool rj = ty == jt, cj = tx == jt;   // this thread's row / column piece jb is row / column j
+      double fr[4], fi[4], cr[4], ci[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const double2 y = col[ty + 16 * p], z = col[tx + 16 * p];
+        fr[p] = y.x * rd;
+        fi[p] = y.y * rd;
+        cr[p] = z.x;
+        ci[p] = z.y;
       }
-      if (tid == 0) dv[j] = d;
-      const double rd = 1.0 / d;
-      for (int i = j + 1 + ty; i < kSw; i += 16) {
-        const double2 x = L[i][j];
-        const double2 xs{x.x * rd, x.y * rd};
-        for (int k = j + 1 + tx; k <= i; k += 16) {
-          const double2 y = L[k][j];
-          L[i][k].x -= xs.x * y.x + xs.y * y.y;
-          L[i][k].y -= xs.y * y.x - xs.x * y.y;
+      fr[jb] = rj ? -rd : fr[jb];
+      fi[jb] = rj ? 0.0 : fi[jb];
+      cr[jb] = cj ? -1.0 : cr[jb];
+      ci[jb] = cj ? 0.0 : ci[jb];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        xr[jb][p] = rj ? 0.0 : xr[jb][p];
+        xi[jb][p] = rj ? 0.0 : xi[jb][p];
+        xr[p][jb] = cj ? 0.0 : xr[p][jb];
+        xi[p][jb] = cj ? 0.0 : xi[p][jb];
+      }
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          xr[p][q] = fma(-fi[p], ci[q], fma(-fr[p], cr[q], xr[p][q]));
+          xi[p][q] = fma(fr[p], ci[q], fma(-fi[p], cr[q], xi[p][q]));
         }
-      }
-    }
-    if (j > 0) {   // column j - 1 is final: scale it, its diagonal becomes sqrt(d)
-      const int c = j - 1;
-      const double sq = sqrt(dv[c]);
-      const double inv = 1.0 / sq;
-      for (int i = c + 1 + tid; i < kSw; i += 256) L[i][c] = double2{L[i][c].x * inv, L[i][c].y * inv};
-      if (tid == 0) L[c][c] = double2{sq, 0.0};
-    }
-    __syncthreads();
-  }
-  if (tid < kSw) dv[tid] = 1.0 / L[tid][tid].x;
-  __syncthreads();
-  // inversion: L X = I by rows; row j of X is final (unscaled) once step j starts
-  for (int j = 0; j <= kSw; ++j) {
-    if (j < kSw) {
-      const double rj = dv[j];
-      for (int i = j + 1 + ty; i < kSw; i += 16) {
-        const double2 l = L[i][j];
-        const double2 f{l.x * rj, l.y * rj};
-        for (int c = tx; c <= j; c += 16) {
-          const double2 x = X[j][c];
-          X[i][c].x -= f.x * x.x - f.y * x.y;
-          X[i][c].y -= f.x * x.y + f.y * x.x;
+      double2* nxt = s_col[(j + 1) & 1];
+      if (jt < 15) {
+        if (tx == jt + 1) {
+#pragma unroll
+          for (int p = 0; p < 4; ++p) nxt[ty + 16 * p] = double2{xr[p][jb], xi[p][jb]};
         }
+      } else if (jb < 3 && tx == 0) {
+        constexpr int nb = jb < 3 ? jb + 1 : 0;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) nxt[ty + 16 * p] = double2{xr[p][nb], xi[p][nb]};
       }
+      __syncthreads();
     }
-    if (j > 0) {
-      const int r = j - 1;
-      const double rr = dv[r];
-      for (int c = tid; c <= r; c += 256) X[r][c] = double2{X[r][c].x * rr, X[r][c].y * rr};
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < kSw * kSw; e += 256) {
-    const int r = e / kSw, c = e % kSw;
-    linvT[(size_t)c * kSw + r] = X[r][c];
-  }
-  // dinv[r][c] = sum_k conj(X[k][r]) X[k][c] over the 4 x 4 block (4 ty.., 4 tx..); X is lower
-  // triangular, so the terms with k below max(r, c) vanish and the sum starts at the block's
-  // larger first index
-  const int r0 = 4 * ty, c0 = 4 * tx;
-  double2 s[4][4];
+  };
+  block(std::integral_constant<int, 0>{});
+  block(std::integral_constant<int, 1>{});
+  block(std::integral_constant<int, 2>{});
+  block(std::integral_constant<int, 3>{});
 #pragma unroll
   for (int p = 0; p < 4; ++p)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) s[p][q] = double2{0.0, 0.0};
-  for (int k = r0 > c0 ? r0 : c0; k < kSw; ++k) {
-    double2 xr[4], xc[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      xr[p] = X[k][r0 + p];
-      xc[p] = X[k][c0 + p];
-    }
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        s[p][q].x += xr[p].x * xc[q].x + xr[p].y * xc[q].y;
-        s[p][q].y += xr[p].x * xc[q].y - xr[p].y * xc[q].x;
-      }
-  }
-#pragma unroll
-  for (int p = 0; p < 4; ++p)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) dinv[(size_t)(r0 + p) * kSw + c0 + q] = s[p][q];
+    for (int q = 0; q < 4; ++q)
+      dinv[(size_t)(ty + 16 * p) * kSw + tx + 16 * q] = double2{-xr[p][q], -xi[p][q]};
 }
 
-// 64 rows i per workgroup: x_i = A_iK from the lower storage, C_i = x_i L^-H into ct[k][i] (zero for
-// i in K, whose tiles the write pass replaces), P_i = x_i D^-1 into pp[i][k]
-__global__ __launch_bounds__(256) void k_sweep_panel(const double2* __restrict__ a, int ldp, int k0,
-                                                     const double2* __restrict__ linvT,
-                                                     const double2* __restrict__ dinv, double2* __restrict__ ct,
+// The first block's D^-1 (the others come out of the preceding update).
+__global__ __launch_bounds__(256) void k_sweep_diag(const double2* __restrict__ a, int ldp, size_t ws,
+                                                    double2* __restrict__ dinv, int* __restrict__ flag) {
+  __shared__ double2 s_col[2][kSw];
+  a = slice(a, ws);
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  double xr[4][4], xi[4][4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = ty + 16 * p, c = tx + 16 * q;
+      const double2 y = a[(size_t)max(r, c) * ldp + min(r, c)];
+      xr[p][q] = y.x;
+      xi[p][q] = r == c ? 0.0 : (r > c ? y.y : -y.y);
+    }
+  diag_inverse(xr, xi, s_col, slice(dinv, ws), flag);
+}
+
+// 64 x 64 tile products on float64 MFMA, four waves of 32 x 32: c += A B^H for operands that hold KC
+// consecutive inner values per row in LDS (odd row stride: the 16 rows of a fragment on different banks).
+constexpr int kTc = 32;            // inner values per LDS stage
+constexpr int kTcLd = kTc + 1;
+template <int KC, int LD>
+__device__ __forceinline__ void tile_abh(const double2* __restrict__ sa, const double2* __restrict__ sb, int ra, int rb,
+                                         f64x4 (&cre)[2][2], f64x4 (&cim)[2][2]) {
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+#pragma unroll 4
+  for (int s = 0; s < KC / 4; ++s) {
+    const int k = 4 * s + lk;
+    double2 a[2], b[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a[i] = sa[(ra + 16 * i + li) * LD + k];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) b[j] = sb[(rb + 16 * j + li) * LD + k];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        cre[i][j] = mfma64(a[i].x, b[j].x, cre[i][j]);
+        cre[i][j] = mfma64(a[i].y, b[j].y, cre[i][j]);
+        cim[i][j] = mfma64(a[i].y, b[j].x, cim[i][j]);
+        cim[i][j] = mfma64(-a[i].x, b[j].y, cim[i][j]);
+      }
+  }
+}
+
+// 16 rows i per workgroup: X_i = A_iK from the lower storage into xx[i][k], P_i = X_i D^-1 into pp[i][k] and
+// into the swept entries of a (A_iK = P_i below the block, A_Ki = P_i^H above it, A_KK = -D^-1).  Each of
+// the four waves forms 16 x 16 of P (16 rows per workgroup, so that also small matrices spread
+// over the chip: one CU takes 7 us for 64 rows).
+constexpr int kPr = 16;
+__global__ __launch_bounds__(256) void k_sweep_panel(double2* __restrict__ a, int ldp, int k0, size_t ws,
+                                                     const double2* __restrict__ dinv, double2* __restrict__ xx,
                                                      double2* __restrict__ pp) {
-  __shared__ double2 xs[4][kSw];
-  __shared__ double2 cs[kSw][kSw + 1];
+  constexpr int LD = kSw + 1;
+  __shared__ double2 sx[kPr * LD];
+  a = slice(a, ws);
+  dinv = slice(dinv, ws);
+  xx = slice(xx, ws);
+  pp = slice(pp, ws);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int i0 = blockIdx.x * kSw;
-  for (int rr = 0; rr < kSw / 4; ++rr) {
-    const int r = rr * 4 + wave;
-    const int i = i0 + r;
-    const bool inK = i >= k0 && i < k0 + kSw;
-    double2 x{0.0, 0.0};
-    if (!inK) {
-      if (i > k0) {
-        x = a[(size_t)i * ldp + k0 + lane];
-      } else {
-        const double2 y = a[(size_t)(k0 + lane) * ldp + i];
-        x = double2{y.x, -y.y};
-      }
+  const int i0 = blockIdx.x * kPr;
+  if (i0 >= k0 && i0 < k0 + kSw) {
+    for (int e = tid; e < kPr * kSw; e += 256) {
+      const int r = i0 - k0 + e / kSw, c = e % kSw;
+      const double2 d = dinv[(size_t)r * kSw + c];
+      if (c <= r) a[(size_t)(k0 + r) * ldp + k0 + c] = double2{-d.x, -d.y};
     }
-    xs[wave][lane] = x;
-    __syncthreads();
-    double2 c{0.0, 0.0}, q{0.0, 0.0};
-    for (int l = 0; l < kSw; ++l) {
-      const double2 xv = xs[wave][l];
-      const double2 li = linvT[(size_t)l * kSw + lane];   // L^-1[lane][l]
-      const double2 d = dinv[(size_t)l * kSw + lane];
-      c.x += xv.x * li.x + xv.y * li.y;   // x conj(li)
-      c.y += xv.y * li.x - xv.x * li.y;
-      q.x += xv.x * d.x - xv.y * d.y;
-      q.y += xv.x * d.y + xv.y * d.x;
-    }
-    cs[r][lane] = c;
-    pp[(size_t)i * kSw + lane] = q;
-    __syncthreads();
+    return;
   }
-  for (int kk = 0; kk < kSw / 4; ++kk) {
-    const int k = kk * 4 + wave;
-    ct[(size_t)k * ldp + i0 + lane] = cs[lane][k];
+  const bool below = i0 > k0;
+  // this wave's 16 columns of D^-1, each value used once (D^-1 is Hermitian: X D^-1 = X (its rows)^H)
+  const int li = lane & 15, lk = lane >> 4;
+  double2 y[kSw / 4];
+#pragma unroll
+  for (int s = 0; s < kSw / 4; ++s) y[s] = dinv[(size_t)(16 * wave + li) * kSw + 4 * s + lk];
+  if (below) {
+#pragma unroll
+    for (int rr = 0; rr < kPr / 4; ++rr) {
+      const int r = 4 * rr + wave;
+      sx[r * LD + lane] = a[(size_t)(i0 + r) * ldp + k0 + lane];
+    }
+  } else {   // rows of the block, columns i0 ..: conj-transposed
+#pragma unroll
+    for (int rr = 0; rr < kPr / 4; ++rr) {
+      const int k = 16 * rr + (tid >> 4), r = tid & 15;
+      const double2 z = a[(size_t)(k0 + k) * ldp + i0 + r];
+      sx[r * LD + k] = double2{z.x, -z.y};
+    }
+  }
+  __syncthreads();
+  f64x4 cre{0, 0, 0, 0}, cim{0, 0, 0, 0};
+#pragma unroll
+  for (int s = 0; s < kSw / 4; ++s) {
+    const double2 x = sx[li * LD + 4 * s + lk];
+    cre = mfma64(x.x, y[s].x, cre);
+    cre = mfma64(x.y, y[s].y, cre);
+    cim = mfma64(x.y, y[s].x, cim);
+    cim = mfma64(-x.x, y[s].y, cim);
+  }
+#pragma unroll
+  for (int rr = 0; rr < kPr / 4; ++rr) {
+    const int r = 4 * rr + wave;
+    xx[(size_t)(i0 + r) * kSw + lane] = sx[r * LD + lane];
+  }
+  __syncthreads();   // sx is read no more: P goes there
+#pragma unroll
+  for (int r = 0; r < 4; ++r) sx[(lk + 4 * r) * LD + 16 * wave + li] = double2{cre[r], cim[r]};
+  __syncthreads();
+#pragma unroll
+  for (int rr = 0; rr < kPr / 4; ++rr) {
+    const int r = 4 * rr + wave;
+    const double2 x = sx[r * LD + lane];
+    pp[(size_t)(i0 + r) * kSw + lane] = x;
+    if (below) a[(size_t)(i0 + r) * ldp + k0 + lane] = x;
+  }
+  if (!below) {
+#pragma unroll
+    for (int rr = 0; rr < kPr / 4; ++rr) {
+      const int k = 16 * rr + (tid >> 4), r = tid & 15;
+      const double2 z = sx[r * LD + k];
+      a[(size_t)(k0 + k) * ldp + i0 + r] = double2{z.x, -z.y};
+    }
   }
 }
 
-// the swept block's new entries in the lower storage: A_iK = P_i (i > K), A_Ki = conj(P_i)
-// (i < K), A_KK = -D^-1
-__global__ void k_sweep_write(double2* __restrict__ a, int ldp, int k0, const double2* __restrict__ pp,
-                              const double2* __restrict__ dinv) {
-  const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (size_t)ldp * kSw) return;
-  const int i = (int)(e / kSw), k = (int)(e % kSw);
-  if (i >= k0 && i < k0 + kSw) {
-    const int r = i - k0;
-    if (k <= r) {
-      const double2 d = dinv[(size_t)r * kSw + k];
-      a[(size_t)i * ldp + k0 + k] = double2{-d.x, -d.y};
-    }
-  } else if (i > k0) {
-    a[(size_t)i * ldp + k0 + k] = pp[e];
+// Rank-64 updates of 64 x 64 tiles, one workgroup per tile, operands with 64 values per row along the inner
+// index, in two LDS stages of 32 (the second in registers while the first runs; 68 KB, two workgroups per CU).
+//   SWEEP: A_ij -= P_i X_j^H on the lower tiles outside the block kt's row and column; the workgroup of the
+//          next diagonal tile goes on to invert it (dinv), beside the other tiles.
+//   else:  A_ij += L_i R_j^H for all i, j < n (leading dimension ld, edges masked).
+template <bool SWEEP>
+__global__ __launch_bounds__(256, 2) void k_rank64(double2* __restrict__ a, int ld, int n, int kt, size_t ws,
+                                                   const double2* __restrict__ left, const double2* __restrict__ right,
+                                                   double2* __restrict__ dinv, int* __restrict__ flag) {
+  __shared__ double2 sl[kSw * kTcLd];
+  __shared__ double2 sr[kSw * kTcLd];
+  __shared__ double2 s_col[2][kSw];
+  const int nt = (n + kSw - 1) / kSw;
+  int ti, tj;
+  bool next = false;
+  if constexpr (SWEEP) {
+    // tile t of the lower triangle of nt - 1 tile rows (the block's own left out), the next diagonal one first
+    const int nl = (nt - 1) * nt / 2;
+    const int first = kt + 1 < nt ? kt * (kt + 3) / 2 : 0;   // (kt, kt) of the reduced numbering
+    const int b = (int)blockIdx.x;
+    const int t = b == 0 ? first : (b <= first ? b - 1 : b);
+    next = b == 0 && kt + 1 < nt;
+    if (t >= nl) return;
+    ti = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
+    while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
+    while (ti * (ti + 1) / 2 > t) --ti;
+    tj = t - ti * (ti + 1) / 2;
+    ti += ti >= kt;
+    tj += tj >= kt;
   } else {
-    const double2 p = pp[e];
-    a[(size_t)(k0 + k) * ldp + i] = double2{p.x, -p.y};
+    ti = (int)blockIdx.x / nt;
+    tj = (int)blockIdx.x % nt;
+  }
+  a = slice(a, ws);
+  left = slice(left, ws) + (size_t)ti * kSw * kSw;
+  right = slice(right, ws) + (size_t)tj * kSw * kSw;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int wr = 32 * (wave >> 1), wc = 32 * (wave & 1), li = lane & 15, lk = lane >> 4;
+  const int r0 = ti * kSw + wr + lk, c0 = tj * kSw + wc + li;
+  // staging: rows sr0 + 8 q, inner value tid % 32
+  const int sk = tid & 31, sr0 = tid >> 5;
+  double2 pl[8], pr[8];
+  auto fetch = [&](int h) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int r = sr0 + 8 * q;
+      const bool okl = SWEEP || ti * kSw + r < n, okr = SWEEP || tj * kSw + r < n;
+      pl[q] = okl ? left[r * kSw + h * kTc + sk] : double2{0.0, 0.0};
+      pr[q] = okr ? right[r * kSw + h * kTc + sk] : double2{0.0, 0.0};
+    }
+  };
+  auto stash = [&] {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      sl[(sr0 + 8 * q) * kTcLd + sk] = pl[q];
+      sr[(sr0 + 8 * q) * kTcLd + sk] = pr[q];
+    }
+  };
+  f64x4 cre[2][2], cim[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) cre[i][j] = cim[i][j] = f64x4{0, 0, 0, 0};
+  fetch(0);
+  stash();
+  __syncthreads();
+  fetch(1);
+  tile_abh<kTc, kTcLd>(sl, sr, wr, wc, cre, cim);
+  __syncthreads();
+  stash();
+  // the tile of A, in flight while the second half runs
+  double2 o[2][2][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = r0 + 16 * i + 4 * r, col = c0 + 16 * j;
+        o[i][j][r] = SWEEP || (row < n && col < n) ? a[(size_t)row * ld + col] : double2{0.0, 0.0};
+      }
+  __syncthreads();
+  tile_abh<kTc, kTcLd>(sl, sr, wr, wc, cre, cim);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = r0 + 16 * i + 4 * r, col = c0 + 16 * j;
+        const double s = SWEEP ? -1.0 : 1.0;
+        const double2 v{fma(s, cre[i][j][r], o[i][j][r].x), fma(s, cim[i][j][r], o[i][j][r].y)};
+        if (SWEEP || (row < n && col < n)) a[(size_t)row * ld + col] = v;
+        o[i][j][r] = v;
+      }
+  if constexpr (SWEEP) {
+    if (next) {   // workgroup-uniform
+      // the updated tile through LDS (sl and sr hold 64 x 33 each: columns 0 .. 31 and 32 .. 63)
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            (wc ? sr : sl)[(wr + lk + 16 * i + 4 * r) * kTcLd + 16 * j + li] = o[i][j][r];
+      __syncthreads();
+      const int tx = tid & 15, ty = tid >> 4;
+      double xr[4][4], xi[4][4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = ty + 16 * p, c = tx + 16 * q;
+          const int hi = max(r, c), lo = min(r, c);   // the lower triangle
+          const double2 y = (lo < 32 ? sl : sr)[hi * kTcLd + (lo & 31)];
+          xr[p][q] = y.x;
+          xi[p][q] = r == c ? 0.0 : (r > c ? y.y : -y.y);
+        }
+      diag_inverse(xr, xi, s_col, slice(dinv, ws), flag);
+    }
   }
 }
 
 // eps^-1[i][j] = sqrt(v_i) (-A)_ij / sqrt(v_j) for i, j < n, A Hermitian from its lower triangle
-__global__ void k_sweep_out(const double* __restrict__ v, const double2* __restrict__ a, int n, int ldp,
+__global__ void k_sweep_out(const double* __restrict__ v, const double2* __restrict__ a, int n, int ldp, size_t ws,
                             double2* __restrict__ out) {
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (size_t)n * n) return;
+  v += (size_t)blockIdx.y * n;
+  a = slice(a, ws);
   const int i = (int)(e / n), j = (int)(e % n);
   double2 x = i >= j ? a[(size_t)i * ldp + j] : a[(size_t)j * ldp + i];
   if (i < j) x.y = -x.y;
+  if (i == j) x.y = 0.0;
   const double s = -sqrt(v[i]) / sqrt(v[j]);
-  out[e] = double2{s * x.x, s * x.y};
-}
-
-__global__ void k_fill_f64_neg(double* __restrict__ w, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) w[i] = -1.0;
+  out[(size_t)blockIdx.y * n * n + e] = double2{s * x.x, s * x.y};
 }
 
 }  // namespace
@@ -551,7 +903,7 @@ hipError_t launch_zgemm_op(int m, int n, int k, double2 alpha, const double2* A,
                            int ldb, int opb, double2 beta, double2* C, int ldc, hipStream_t st) {
   if (m < 1 || n < 1 || k < 1 || opa < kOpN || opa > kOpConj || opb < kOpN || opb > kOpConj) return hipErrorInvalidValue;
   const int tiles = ((m + ZT - 1) / ZT) * ((n + ZT - 1) / ZT);
-  k_zgemm<<<tiles, 256, 0, st>>>(m, n, k, alpha, A, lda, opa, B, ldb, opb, beta, C, ldc);
+  k_zgemm<<<tiles, 256, 0, st>>>(m, n, k, alpha, A, lda, opa, B, ldb, opb, beta, C, ldc, 0);
   return hipGetLastError();
 }
 
@@ -560,15 +912,18 @@ hipError_t launch_zgemm(int m, int n, int k, double2 alpha, const double2* A, in
   return launch_zgemm_op(m, n, k, alpha, A, lda, cta ? kOpC : kOpN, B, ldb, ctb ? kOpC : kOpN, beta, C, ldc, st);
 }
 
+constexpr size_t up256(size_t x) { return (x + 255) / 256 * 256; }
+constexpr size_t sweep_ld(int n) { return (size_t)((n + kSw - 1) / kSw * kSw); }
 constexpr size_t sweep_bytes(int n) {
-  return (size_t)((n + kSw - 1) / kSw * kSw) * ((n + kSw - 1) / kSw * kSw) * sizeof(double2) +
-         2 * (size_t)kSw * ((n + kSw - 1) / kSw * kSw) * sizeof(double2) + 2 * (size_t)kSw * kSw * sizeof(double2) +
-         kSw * sizeof(double) + 4096;
+  return up256(sweep_ld(n) * sweep_ld(n) * sizeof(double2)) + 2 * up256(kSw * sweep_ld(n) * sizeof(double2)) +
+         up256((size_t)kSw * kSw * sizeof(double2));
 }
 
+constexpr size_t gj_cands(int n) { return (size_t)(n + kGjRows - 1) / kGjRows; }
 constexpr size_t gj_bytes(int n) {
-  return (size_t)n * n * sizeof(double2) + 2 * (size_t)n * kNb * sizeof(double2) + 2 * (size_t)n * sizeof(int) +
-         2 * (size_t)((n + kStepRows - 1) / kStepRows) * (sizeof(double) + sizeof(int)) + 1024;
+  return up256((size_t)n * n * sizeof(double2)) + 2 * up256((size_t)n * kNb * sizeof(double2)) +
+         2 * up256((size_t)n * kGjSub * sizeof(double2)) + 2 * up256((size_t)n * sizeof(int)) +
+         2 * up256(gj_cands(n) * sizeof(double)) + 2 * up256(gj_cands(n) * sizeof(int));
 }
 // either route of the inverse (pivoted Gauss-Jordan, or the sweeps of the static form)
 constexpr size_t eps_inv_bytes(int n) { return gj_bytes(n) > sweep_bytes(n) ? gj_bytes(n) : sweep_bytes(n); }
@@ -606,93 +961,109 @@ void* noalloc_scratch(int device) {
 
 size_t noalloc_scratch_bytes() { return kNoAllocBytes; }
 
-hipError_t launch_eps_inv(int n, const double* v, const double2* chi, double2* out, void* ws, int* flag,
-                          hipStream_t st) {
-  const int ncand = (n + kStepRows - 1) / kStepRows;
-  char* w = (char*)ws;
-  double2* a = (double2*)w;   // working matrix
-  w += (size_t)n * n * sizeof(double2);
-  double2* pb[2];              // panel buffers (n x kNb); afterwards the update operands
-  pb[0] = (double2*)w;
-  w += (size_t)n * kNb * sizeof(double2);
-  pb[1] = (double2*)w;
-  w += (size_t)n * kNb * sizeof(double2);
-  int* piv = (int*)w;
-  w += (size_t)n * sizeof(int);
-  int* idx = (int*)w;
-  w += (size_t)n * sizeof(int);
+namespace {
+struct GjWork {
+  double2 *a, *pb[2], *t[2];   // matrix, panel buffers (afterwards the update's operands), sub-panels
+  int *piv, *idx, *ci[2];      // row interchanges, column order, pivot candidates
   double* cm[2];
-  int* ci[2];
-  cm[0] = (double*)w;
-  w += ncand * sizeof(double);
-  cm[1] = (double*)w;
-  w += ncand * sizeof(double);
-  ci[0] = (int*)w;
-  w += ncand * sizeof(int);
-  ci[1] = (int*)w;
-  const size_t nn = (size_t)n * n;
-  const unsigned gnn = (unsigned)((nn + 255) / 256);
-  k_form_eps<<<gnn, 256, 0, st>>>(v, chi, n, a);
+};
+
+// R > 0: sub-panels of S columns in one workgroup with R rows per thread; R = 0: kGjSub columns, a launch
+// per step
+template <int R, int S>
+hipError_t run_gj(int n, int nb, size_t ws, const GjWork& w, int* flag, hipStream_t st) {
+  const unsigned rows = (unsigned)((n + kStepRows - 1) / kStepRows);
+  const unsigned cand = (unsigned)gj_cands(n);
   for (int j0 = 0; j0 < n; j0 += kNb) {
-    const int nbp = n - j0 < kNb ? n - j0 : kNb;
-    k_panel_load<<<ncand, 256, 0, st>>>(a, n, j0, nbp, pb[0], cm[0], ci[0]);
-    for (int jc = 0; jc < nbp; ++jc)
-      k_gj_step<<<ncand, 256, 0, st>>>(pb[jc & 1], pb[(jc + 1) & 1], n, j0, jc, nbp, cm[jc & 1], ci[jc & 1], ncand,
-                                       cm[(jc + 1) & 1], ci[(jc + 1) & 1], piv, flag);
-    double2* fin = pb[nbp & 1];
-    double2* other = pb[(nbp + 1) & 1];
-    if (nbp < n) k_row_swaps<<<(n + 255) / 256, 256, 0, st>>>(a, n, j0, nbp, piv);
-    const size_t nops = (size_t)n * kNb;
-    k_panel_operands<<<(unsigned)((nops + 255) / 256), 256, 0, st>>>(a, n, j0, nbp, fin, other);
+    const int nbp = std::min(n - j0, kNb);
+    k_panel_load<<<dim3(rows, nb), 256, 0, st>>>(w.a, n, j0, nbp, ws, w.pb[0]);
+    int cur = 0;
+    for (int c0 = 0; c0 < nbp; c0 += S) {
+      const int sc = std::min(S, nbp - c0);
+      const double2* t = w.t[0];
+      if constexpr (R > 0) {
+        k_gj_sub<R, S><<<dim3(1, nb), kGjThreads, 0, st>>>(w.pb[cur], n, j0, c0, sc, ws, w.t[0], w.piv, flag);
+      } else {
+        k_gj_load16<<<dim3(cand, nb), 256, 0, st>>>(w.pb[cur], n, j0, c0, sc, ws, w.t[0], w.cm[0], w.ci[0]);
+        for (int jc = 0; jc < sc; ++jc) {
+          const int i = jc & 1, o = i ^ 1;
+          k_gj_step16<<<dim3(cand, nb), 256, 0, st>>>(w.t[i], w.t[o], n, j0 + c0 + jc, jc, (int)cand, ws, w.cm[i],
+                                                      w.ci[i], w.cm[o], w.ci[o], w.piv, flag);
+        }
+        t = w.t[sc & 1];
+      }
+      k_gj_apply<S><<<dim3(rows, nb), 256, 0, st>>>(w.pb[cur], w.pb[cur ^ 1], n, j0, c0, sc, ws, t, w.piv);
+      cur ^= 1;
+    }
+    double2* fin = w.pb[cur];
+    double2* other = w.pb[cur ^ 1];
+    if (nbp < n) k_row_swaps<<<dim3((n + 255) / 256, nb), 256, 0, st>>>(w.a, n, j0, nbp, ws, w.piv);
+    const size_t nops = (size_t)(n + 7) / 8 * 8 * kNb;
+    k_panel_operands<<<dim3((unsigned)((nops + 255) / 256), nb), 256, 0, st>>>(w.a, n, j0, nbp, ws, fin, other);
     if (nbp == n) break;   // a single panel: no other columns to update
-    hipError_t e = launch_zgemm(n, n, kNb, double2{1.0, 0.0}, fin, kNb, false, other, n, false, double2{1.0, 0.0},
-                                a, n, st);
-    if (e != hipSuccess) return e;
+    const unsigned nt = (unsigned)((n + kSw - 1) / kSw);
+    k_rank64<false><<<dim3(nt * nt, nb), 256, 0, st>>>(w.a, n, n, 0, ws, fin, other, nullptr, nullptr);
   }
-  k_col_perm<<<1, 64, 0, st>>>(piv, n, idx);
-  k_gather_cols<<<gnn, 256, 0, st>>>(a, idx, n, out);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_eps_inv(int n, int nb, const double* v, const double2* chi, double2* out, void* wsp, int* flag,
+                          hipStream_t st) {
+  const size_t ws = eps_inv_bytes(n);
+  char* p = (char*)wsp;
+  auto take = [&](size_t bytes) {
+    char* q = p;
+    p += up256(bytes);
+    return q;
+  };
+  GjWork w;
+  w.a = (double2*)take((size_t)n * n * sizeof(double2));
+  for (auto& x : w.pb) x = (double2*)take((size_t)n * kNb * sizeof(double2));
+  for (auto& x : w.t) x = (double2*)take((size_t)n * kGjSub * sizeof(double2));
+  w.piv = (int*)take((size_t)n * sizeof(int));
+  w.idx = (int*)take((size_t)n * sizeof(int));
+  for (auto& x : w.cm) x = (double*)take(gj_cands(n) * sizeof(double));
+  for (auto& x : w.ci) x = (int*)take(gj_cands(n) * sizeof(int));
+  const dim3 gnn((unsigned)(((size_t)n * n + 255) / 256), nb);
+  k_form_eps<<<gnn, 256, 0, st>>>(v, chi, n, ws, w.a);
+  // columns per sub-panel: as many as the registers hold beside R rows per thread
+  const int r = (n + kGjThreads - 1) / kGjThreads;
+  const hipError_t e = r <= 1   ? run_gj<1, 16>(n, nb, ws, w, flag, st)
+                       : r <= 2 ? run_gj<2, 16>(n, nb, ws, w, flag, st)
+                       : r <= 3 ? run_gj<3, 8>(n, nb, ws, w, flag, st)
+                       : r <= 4 ? run_gj<4, 8>(n, nb, ws, w, flag, st)
+                                : run_gj<0, kGjSub>(n, nb, ws, w, flag, st);
+  if (e != hipSuccess) return e;
+  k_col_perm<<<dim3((n + 255) / 256, nb), 256, 0, st>>>(w.piv, n, ws, w.idx);
+  k_gather_cols<<<gnn, 256, 0, st>>>(w.a, w.idx, n, ws, out);
   return hipGetLastError();
 }
 
-hipError_t launch_eps_inv_sweep(int n, const double* v, const double2* chi, double2* out, void* ws, int* flag,
+hipError_t launch_eps_inv_sweep(int n, int nb, const double* v, const double2* chi, double2* out, void* wsp, int* flag,
                                 hipStream_t st) {
-  const int ldp = (n + kSw - 1) / kSw * kSw;
-  char* w = (char*)ws;
-  double2* a = (double2*)w;
-  w += (size_t)ldp * ldp * sizeof(double2);
-  double2* ct = (double2*)w;
-  w += (size_t)kSw * ldp * sizeof(double2);
-  double2* pp = (double2*)w;
-  w += (size_t)kSw * ldp * sizeof(double2);
-  double2* linvT = (double2*)w;
-  w += (size_t)kSw * kSw * sizeof(double2);
-  double2* dinv = (double2*)w;
-  w += (size_t)kSw * kSw * sizeof(double2);
-  double* wneg = (double*)w;
-  w += kSw * sizeof(double);
-  int* counter = (int*)(((uintptr_t)w + 255) / 256 * 256);
+  const size_t ws = eps_inv_bytes(n);
+  const int ldp = (int)sweep_ld(n);
+  char* w = (char*)wsp;
+  auto take = [&](size_t bytes) {
+    char* p = w;
+    w += up256(bytes);
+    return p;
+  };
+  double2* a = (double2*)take((size_t)ldp * ldp * sizeof(double2));
+  double2* xx = (double2*)take((size_t)kSw * ldp * sizeof(double2));
+  double2* pp = (double2*)take((size_t)kSw * ldp * sizeof(double2));
+  double2* dinv = (double2*)take((size_t)kSw * kSw * sizeof(double2));
   const size_t nn = (size_t)ldp * ldp;
-  k_sweep_form<<<(unsigned)((nn + 255) / 256), 256, 0, st>>>(v, chi, n, ldp, a, flag);
-  k_fill_f64_neg<<<1, kSw, 0, st>>>(wneg, kSw);
+  k_sweep_form<<<dim3((unsigned)((nn + 255) / 256), nb), 256, 0, st>>>(v, chi, n, ldp, ws, a, flag);
   const int nt = ldp / kSw;
-  ContractBatch bt{};
-  bt.nprob = 1;
-  bt.item0[0] = 0;
-  bt.item0[1] = (long long)nt * (nt + 1) / 2;
-  bt.p[0] = ContractProb{ct, wneg, a, kSw, ldp, 1, nt * (nt + 1) / 2};
-  const int grid = (int)std::min<long long>(bt.item0[1], 256LL * 8);
-  for (int k0 = 0; k0 < ldp; k0 += kSw) {
-    k_sweep_diag<<<1, 256, 0, st>>>(a, ldp, k0, linvT, dinv, flag);
-    k_sweep_panel<<<nt, 256, 0, st>>>(a, ldp, k0, linvT, dinv, ct, pp);
-    if (nt > 1) {
-      hipError_t e = launch_zero(counter, 256, st);
-      if (e != hipSuccess) return e;
-      e = launch_contract_batch(0, bt, counter, grid, true, st);
-      if (e != hipSuccess) return e;
-    }
-    k_sweep_write<<<(unsigned)(((size_t)ldp * kSw + 255) / 256), 256, 0, st>>>(a, ldp, k0, pp, dinv);
+  k_sweep_diag<<<dim3(1, nb), 256, 0, st>>>(a, ldp, ws, dinv, flag);
+  for (int kt = 0; kt < nt; ++kt) {
+    k_sweep_panel<<<dim3(ldp / kPr, nb), 256, 0, st>>>(a, ldp, kt * kSw, ws, dinv, xx, pp);
+    if (nt > 1)
+      k_rank64<true><<<dim3((nt - 1) * nt / 2, nb), 256, 0, st>>>(a, ldp, ldp, kt, ws, pp, xx, dinv, flag);
   }
-  k_sweep_out<<<(unsigned)(((size_t)n * n + 255) / 256), 256, 0, st>>>(v, a, n, ldp, out);
+  k_sweep_out<<<dim3((unsigned)(((size_t)n * n + 255) / 256), nb), 256, 0, st>>>(v, a, n, ldp, ws, out);
   return hipGetLastError();
 }
 

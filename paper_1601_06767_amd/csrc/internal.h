@@ -252,12 +252,15 @@ constexpr int kNoAllocMaxDevices = 64;
 hipError_t noalloc_scratch_init(int device);   // with the device current; once per device
 void* noalloc_scratch(int device);             // its device address there (nullptr before init)
 size_t noalloc_scratch_bytes();
-hipError_t launch_eps_inv(int n, const double* v, const double2* chi, double2* out, void* ws, int* flag,
+// nb inverses at once (consecutive matrices of v, chi and out), each in its own
+// eps_inv_workspace(n) bytes of ws
+constexpr int kMaxInvBatch = 16;
+hipError_t launch_eps_inv(int n, int nb, const double* v, const double2* chi, double2* out, void* ws, int* flag,
                           hipStream_t st);
 // static chi0 (Hermitian, negative semidefinite) and v > 0: block sweeps of the positive
 // definite I - V^1/2 chi0 V^1/2 (lower triangle of chi read); a pivot block that is not
-// positive definite sets *flag.  Workspace: eps_inv_workspace(n) covers it.
-hipError_t launch_eps_inv_sweep(int n, const double* v, const double2* chi, double2* out, void* ws, int* flag,
+// positive definite sets *flag.
+hipError_t launch_eps_inv_sweep(int n, int nb, const double* v, const double2* chi, double2* out, void* ws, int* flag,
                                 hipStream_t st);
 size_t eps_inv_backward_workspace(int n);
 hipError_t launch_eps_inv_backward(int n, const double* v, const double2* z, const double2* zbar, double2* out,
