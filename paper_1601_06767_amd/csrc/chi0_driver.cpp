@@ -32,7 +32,13 @@ constexpr int kColumnStep = 16;      // conduction columns of a chunk: whole wor
 
 // columns of a chunk beside nvs (padded) valence slots
 int chunk_columns(int nvs) { return std::max(8, (kPairTarget / nvs) / 8 * 8); }
-constexpr int kBandBatch = 32;       // bands per band-transform launch group
+
+// Bands per band-transform launch pair: 32 fill the chip from the 72^3 spheres on; smaller grids take as
+// many more as keep the x3/x2 scratch within 64 MiB (24^3, 240 bands: nine pairs of 15 us each before).
+int band_batch(const Geom& g, bool fp64) {
+  const size_t one = gw::band_scratch_bytes(g, 1, fp64);
+  return (int)std::min<size_t>(256, std::max<size_t>(32, (size_t(64) << 20) / one));
+}
 
 int mode_of(gw_precision p) { return p == GW_FP64 ? 0 : (p == GW_FP32 ? 1 : 2); }
 
@@ -91,12 +97,13 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
     q.nvs = (int)round_up(probs[i].nv, 4);
     q.cc = (int)round_up(std::min<int>(chunk_columns(q.nvs), probs[i].ncol), kColumnStep);
     q.npair = q.nvs * q.cc;
-    const int nt = g.ngp / gw::contract_tile(L.mode);
+    const int nt = (g.ng + gw::contract_tile(L.mode) - 1) / gw::contract_tile(L.mode);   // tiles with a G < ng
     q.ntl = nt * (nt + 1) / 2;
     items += (long long)q.ntl * nomega * L.nparts;
     L.pp.push_back(q);
   }
-  // Split the pair ranges so that (a) the batch has about 8 items per CU and (b) for a
+  // Split the pair ranges, at most 16 ways (24^3 float64: 218 us per build with 16, 232 with 32, 244 with
+  // 8; 72^3 float64: 58.5 / 59.7 / 59.1 ms), so that (a) the batch has about 8 items per CU and (b) for a
   // single job, the rows of M that the items in flight share (one pair range) stay near
   // 32 MB, so they are served from cache instead of HBM (with several jobs the items of one
   // range already share their rows).  Every split costs a float64 partial NG^2 per job, so
@@ -108,14 +115,14 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
   // 256 KB partial per item (one 128^3 / NG 8000 chunk of 32k pairs: 21.1 ms unsplit, 21.8 with
   // 4 splits, 25.6 with 32).
   const long long want = L.images ? 4LL * 256 : 8LL * 256;
-  const int ks_par = items >= want ? 1 : (int)std::min<long long>(32, (want + items - 1) / items);
+  const int ks_par = items >= want ? 1 : (int)std::min<long long>(16, (want + items - 1) / items);
   const int njobs = nomega * L.nparts;
   size_t acc1 = 0;   // partials of all problems with one split each
   for (const auto& q : L.pp) acc1 += (size_t)q.p->geom->g.ngp * q.p->geom->g.ngp * sizeof(double2) * njobs;
   const int ks_mem = (int)std::max<size_t>(1, (size_t(16) << 30) / std::max<size_t>(acc1, 1));
   for (auto& q : L.pp) {
     const size_t mbytes = (size_t)q.npair * q.p->geom->g.ngp * L.csz;
-    const int ks_cache = njobs > 1 || L.images ? 1 : (int)std::min<size_t>(32, (mbytes + (32u << 20) - 1) / (32u << 20));
+    const int ks_cache = njobs > 1 || L.images ? 1 : (int)std::min<size_t>(16, (mbytes + (32u << 20) - 1) / (32u << 20));
     int k = std::min(std::max(ks_par, ks_cache), ks_mem);
     auto it = ctx->tune.find(shape_key(q.p->geom->g, q.p->nv, q.p->ncol, prec));
     if (it != ctx->tune.end()) {
@@ -142,7 +149,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
       q.off_img2 = take(gw::split_image_bytes(q.npair, g.ngp));
     }
     max_psic = std::max(max_psic, (size_t)q.cc * npts * L.csz);
-    max_scr = std::max(max_scr, gw::band_scratch_bytes(g, kBandBatch, L.fp64));
+    max_scr = std::max(max_scr, gw::band_scratch_bytes(g, band_batch(g, L.fp64), L.fp64));
     max_q = std::max(max_q, (size_t)q.npair * g.q_elems() * L.csz);
     max_part = std::max(max_part, gw::adjoint_partial_bytes(q.npair, g.ngp));
     max_np = std::max(max_np, (size_t)q.npair);
@@ -173,7 +180,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
         mb = std::max(mb, (size_t)q.npair * g.ngp * sizeof(double2));
         uc = std::max(uc, (size_t)q.cc * npts * sizeof(double2));
         uv = std::max(uv, (size_t)q.nvs * npts * sizeof(double2));
-        cb = std::max(cb, (size_t)std::max(q.cc, kBandBatch) * g.npw * sizeof(double2));
+        cb = std::max(cb, (size_t)std::max(q.cc, band_batch(g, true)) * g.npw * sizeof(double2));
       }
       L.off_mbar = take(mb);
       L.off_atmp = take(mb);
@@ -190,8 +197,9 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
 gw_status band_to_real(gw_ctx* ctx, const Layout& L, const Geom& g, const double2* coef, int nrows,
                        const int32_t* band_idx, int band0, int nvalid, int nslot, char* ws, char* psi) {
   const size_t npts = g.band_elems(L.fp64);
-  for (int s0 = 0; s0 < nslot; s0 += kBandBatch) {
-    const int ns = std::min(kBandBatch, nslot - s0);
+  const int batch = band_batch(g, L.fp64);
+  for (int s0 = 0; s0 < nslot; s0 += batch) {
+    const int ns = std::min(batch, nslot - s0);
     void* tB = ws + L.off_scr;
     void* out = psi + (size_t)s0 * npts * L.csz;
     gw::StageScope sc(ctx, gw::kStageBand);
@@ -292,7 +300,6 @@ gw_status enqueue_build(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, in
   if (L.total > ws_bytes)
     return gw::fail(ctx, GW_EINVAL, "workspace too small: need " + std::to_string(L.total) + " bytes");
   for (const ProbPlan& q : L.pp) {
-    GW_HIP(ctx, gw::launch_zero(ws + q.off_acc, q.acc_one * nomega * L.nparts, ctx->stream));
     gw_status s = band_to_real(ctx, L, q.p->geom->g, (const double2*)q.p->coef_v, q.p->nv, nullptr, 0, q.p->nv, q.nvs,
                                ws, ws + q.off_psiv);
     if (s != GW_OK) return s;
@@ -369,7 +376,7 @@ gw_status enqueue_build(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, in
       const ProbPlan& q = plans[active[k]];
       bt.item0[k] = item;
       bt.p[k] = gw::ContractProb{ws + q.off_m, (const double*)(ws + q.off_w), (double2*)(ws + q.off_acc), q.npair,
-                                 q.p->geom->g.ngp, q.ksplit, q.ntl};
+                                 q.p->geom->g.ngp, q.ksplit, q.ntl, j == 0};
       if (L.images) {
         bt.p[k].aimg = ws + q.off_img;
         bt.p[k].bimg = ws + q.off_img + (size_t)q.npair / 16 * q.p->geom->g.ngp * 8 * 16;
@@ -451,9 +458,9 @@ gw_status coef_grad_chunk(gw_ctx* ctx, const Layout& L, const ProbPlan& q, const
   GW_HIP(ctx, gw::launch_qbar(g, ws + L.off_mbar, q.npair, ws + L.off_q, ctx->stream));
   if (gcc) {
     GW_HIP(ctx, gw::launch_ubar(g, ws + L.off_q, ws + q.off_psiv, q.nvs, q.cc, true, ws + L.off_ubarc, ctx->stream));
-    const int nvalid = std::min(q.cc, p.ncol - c0);
-    for (int s0 = 0; s0 < nvalid; s0 += kBandBatch) {
-      const int ns = std::min(kBandBatch, nvalid - s0);
+    const int nvalid = std::min(q.cc, p.ncol - c0), batch = band_batch(g, true);
+    for (int s0 = 0; s0 < nvalid; s0 += batch) {
+      const int ns = std::min(batch, nvalid - s0);
       GW_HIP(ctx, gw::launch_band_from_real(g, ws + L.off_ubarc + (size_t)s0 * npts * sizeof(double2), ns,
                                             ws + L.off_scr, ws + L.off_cbar + (size_t)s0 * g.npw * sizeof(double2),
                                             ctx->stream));
@@ -673,8 +680,9 @@ gw_status backward_entry(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, i
     }
     if (gcv) {
       // the valence gradients, from ubar_v summed over every chunk
-      for (int s0 = 0; s0 < p.nv; s0 += kBandBatch) {
-        const int ns = std::min(kBandBatch, p.nv - s0);
+      const int batch = band_batch(g, true);
+      for (int s0 = 0; s0 < p.nv; s0 += batch) {
+        const int ns = std::min(batch, p.nv - s0);
         GW_HIP(ctx, gw::launch_band_from_real(g, ws + L.off_ubarv + (size_t)s0 * npts * sizeof(double2), ns,
                                               ws + L.off_scr, gcv + (size_t)s0 * g.npw, ctx->stream));
       }
@@ -1027,14 +1035,13 @@ gw_status gw_tune(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nome
       bt.item0[0] = 0;
       bt.item0[1] = items_per_job(qk);
       bt.p[0] = gw::ContractProb{ws + qk.off_m, (const double*)(ws + qk.off_w), (double2*)(ws + qk.off_acc), qk.npair,
-                                 p.geom->g.ngp, qk.ksplit, qk.ntl};
+                                 p.geom->g.ngp, qk.ksplit, qk.ntl, true};
       int* counter = (int*)(ws + Lk.off_counter);
       const int grid = (int)std::min<long long>(bt.item0[1], 256LL * 8);
       float t = 0;
       for (int rep = 0; rep < 2 && result == GW_OK; ++rep) {
         result = timed(
             [&]() -> gw_status {
-              GW_HIP(ctx, gw::launch_zero(ws + qk.off_acc, qk.acc_one, ctx->stream));
               GW_HIP(ctx, gw::launch_zero(counter, 256, ctx->stream));
               GW_HIP(ctx, gw::launch_contract_batch(Lk.mode, bt, counter, grid, true, ctx->stream));
               return GW_OK;

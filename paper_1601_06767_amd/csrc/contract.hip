@@ -142,7 +142,7 @@ template <> struct TileGeo<128> {
 // float64 partial sum of one item; rows of block (i, j) start at r0 + 16 i, columns at c0 + 16 j
 template <int MI, int NJ, typename A4>
 __device__ __forceinline__ void store_tile(double2* out, int ngp, int r0, int c0, const A4 (&cre)[MI][NJ],
-                                           const A4 (&cim)[MI][NJ], int li, int lk, bool f64_rows) {
+                                           const A4 (&cim)[MI][NJ], int li, int lk, bool f64_rows, bool fresh) {
   // eight results at a time: their loads first, so that they are in flight together (the
   // compiler cannot tell that the stores do not alias the later loads)
   constexpr int NB = 8;
@@ -156,7 +156,7 @@ __device__ __forceinline__ void store_tile(double2* out, int ngp, int r0, int c0
       for (int q = 0; q < NB; ++q) {
         const int j = (b + q) / 4, r = (b + q) % 4;
         const int row = r0 + 16 * i + (f64_rows ? lk + 4 * r : 4 * lk + r);
-        o[q] = out[(size_t)row * ngp + c0 + 16 * j + li];
+        o[q] = fresh ? double2{0.0, 0.0} : out[(size_t)row * ngp + c0 + 16 * j + li];
       }
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
@@ -189,7 +189,7 @@ __device__ __forceinline__ int range_len(int nk, int ksplit) {
 constexpr int KD = 8;   // pairs per stage of the direct-load tile
 template <typename T, int TILE>
 __device__ void tile_mfma(const cx<T>* __restrict__ m, const double* __restrict__ w, int nk, int ngp, int ksplit,
-                          double2* __restrict__ acc, int t, int ks) {
+                          double2* __restrict__ acc, int t, int ks, bool fresh) {
   using V = cx<T>;
   using A4 = typename Mfma<T>::acc;
   using G = TileGeo<TILE>;
@@ -286,7 +286,7 @@ __device__ void tile_mfma(const cx<T>* __restrict__ m, const double* __restrict_
     if (kk + KD < k1) stage(kk + KD, sA1, sB1, sA0, sB0);
   }
   store_tile<MI, NJ>(acc + (size_t)ks * ngp * ngp, ngp, g0 + 16 * MI * wr, h0 + 16 * NJ * wc, cre, cim, li, lk,
-                     std::is_same<T, double>::value);
+                     std::is_same<T, double>::value, fresh);
 }
 
 // ---------------------------------------------------------------- split-bf16 x3 tile
@@ -310,7 +310,7 @@ constexpr int BROW = 56;
 
 template <int TILE>
 __device__ void tile_bf16x3(const void* __restrict__ mv, const double* __restrict__ w, int nk, int ngp, int ksplit,
-                            double2* __restrict__ acc, int t, int ks) {
+                            double2* __restrict__ acc, int t, int ks, bool fresh) {
   using G = TileGeo<TILE>;
   constexpr int MI = G::MI, NJ = G::NJ;
   const float2* m = (const float2*)mv;
@@ -438,7 +438,8 @@ __device__ void tile_bf16x3(const void* __restrict__ mv, const double* __restric
         cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl[i], ch[j], cim[i][j], 0, 0, 0);
       }
   }
-  store_tile<MI, NJ>(acc + (size_t)ks * ngp * ngp, ngp, g0 + 16 * MI * wr, h0 + 16 * NJ * wc, cre, cim, li, lg, false);
+  store_tile<MI, NJ>(acc + (size_t)ks * ngp * ngp, ngp, g0 + 16 * MI * wr, h0 + 16 * NJ * wc, cre, cim, li, lg, false,
+                     fresh);
 }
 
 // ---------------------------------------------------------------- split-bf16 x3 from row images
@@ -466,7 +467,7 @@ constexpr int IUPL = IUS / INT;                // units per lane per stage
 static_assert(IUPL * INT == IUS && IUA % 64 == 0, "stage units must split into whole wave instructions");
 
 __device__ void tile_bf16x3_img(const uint4* __restrict__ aimg, const uint4* __restrict__ bimg, int nk, int ngp,
-                                 int ksplit, double2* __restrict__ acc, int t, int ks, uint4* sa, uint4* sb,
+                                 int ksplit, double2* __restrict__ acc, int t, int ks, bool fresh, uint4* sa, uint4* sb,
                                  uint4* sc) {
   constexpr int MI = 4, NJ = 2;
   int ti, tj;
@@ -571,7 +572,7 @@ __device__ void tile_bf16x3_img(const uint4* __restrict__ aimg, const uint4* __r
     }
     if (kb < s1) stage(kb, sa, sc);
     if (kb + 1 < s1) stage(kb + 1, sb, sa);
-    store_tile<MI, NJ>(out, ngp, g0 + 16 * MI * wr, h0 + 16 * NJ * wc, cre, cim, li, lg, false);
+    store_tile<MI, NJ>(out, ngp, g0 + 16 * MI * wr, h0 + 16 * NJ * wc, cre, cim, li, lg, false, fresh && s0 == kb0);
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -608,7 +609,7 @@ __global__ __launch_bounds__(INT, 1) void k_contract_img(ContractBatch bt) {
     const int rem = (int)(local % per_job);
     double2* acc = p.acc + (size_t)job * p.ksplit * p.ngp * p.ngp;
     tile_bf16x3_img((const uint4*)p.aimg, (const uint4*)p.bimg, p.nk, p.ngp, p.ksplit, acc, rem % p.ntl,
-                    rem / p.ntl, sa, sb, sc);
+                    rem / p.ntl, p.fresh != 0, sa, sb, sc);
   }
 }
 
@@ -660,11 +661,11 @@ __global__ __launch_bounds__(256) void k_split_ab(const float2* __restrict__ m, 
 template <int MODE, int TILE>   // MODE 0 f64, 1 f32, 2 bf16x3 (register-staged)
 __device__ __forceinline__ void run_item(const ContractProb& p, const double* w, double2* acc, int t, int ks) {
   if constexpr (MODE == 0)
-    tile_mfma<double, TILE>((const double2*)p.m, w, p.nk, p.ngp, p.ksplit, acc, t, ks);
+    tile_mfma<double, TILE>((const double2*)p.m, w, p.nk, p.ngp, p.ksplit, acc, t, ks, p.fresh != 0);
   else if constexpr (MODE == 1)
-    tile_mfma<float, TILE>((const float2*)p.m, w, p.nk, p.ngp, p.ksplit, acc, t, ks);
+    tile_mfma<float, TILE>((const float2*)p.m, w, p.nk, p.ngp, p.ksplit, acc, t, ks, p.fresh != 0);
   else
-    tile_bf16x3<TILE>(p.m, w, p.nk, p.ngp, p.ksplit, acc, t, ks);
+    tile_bf16x3<TILE>(p.m, w, p.nk, p.ngp, p.ksplit, acc, t, ks, p.fresh != 0);
 }
 
 // Persistent grid over all items of a batch; items of problem b occupy

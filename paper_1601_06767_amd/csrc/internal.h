@@ -191,6 +191,7 @@ struct ContractProb {
   const double* w;
   double2* acc;
   int nk, ngp, ksplit, ntl;
+  int fresh = 0;                // the partial sums are written, not added to (a build's first chunk)
   const void* aimg = nullptr;   // mode 3: the bf16 row images of M and w M (launch_split_ab)
   const void* bimg = nullptr;
 };
