@@ -851,7 +851,7 @@ namespace {
 // problems; then the tile partials of every (state block, state block, energy block) pass
 struct GppCohLayout {
   size_t region = 0, off_part = 0, part_pass = 0, total = 0;
-  int nsb = 0, neb = 0, ngp_max = 0;
+  int nsb = 0, neb = 0;
 };
 
 GppCohLayout gpp_coh_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nq, int nenergy) {
@@ -861,7 +861,6 @@ GppCohLayout gpp_coh_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nq, i
     const Geom& g = probs[i].geom->g;
     const size_t r = round_up(L.total, 256) + 2 * round_up((size_t)g.ngp * g.ngp * sizeof(double2), 256);
     c.region = std::max(c.region, r);
-    c.ngp_max = std::max(c.ngp_max, g.ngp);
     c.part_pass = std::max(c.part_pass, gw::gpp_coh_part_bytes(g.ngp));
   }
   const int bs = gw::gpp_coh_states_per_block(), be = gw::gpp_coh_energies_per_pass();
@@ -952,7 +951,7 @@ gw_status gw_sigma_coh_gpp(gw_ctx* ctx, const gw_chi0_problem* probs, int nq, co
   for (int sa = 0; sa < c.nsb; ++sa)
     for (int sb = 0; sb < c.nsb; ++sb)
       for (int eb = 0; eb < c.neb; ++eb)
-        GW_HIP(ctx, gw::launch_gpp_coh_sum(pass_part(sa, sb, eb), c.ngp_max, std::min(be, nenergy - eb * be), ns, sa,
+        GW_HIP(ctx, gw::launch_gpp_coh_sum(pass_part(sa, sb, eb), c.part_pass, std::min(be, nenergy - eb * be), ns, sa,
                                            sb, eb * be, sigma, ctx->stream));
   return GW_OK;
 }

@@ -154,7 +154,7 @@ hipError_t launch_gpp_coh_prep(const void* modes, const double* v, int ng, int n
 hipError_t launch_gpp_coh(const void* b, const void* w, int ngp, const void* m, int cc, int ns, int sa, int sb,
                           int nvalid, const double* e_col, const double* n_col, int c0, const double* energies, int ne,
                           double delta, void* part, hipStream_t st);
-hipError_t launch_gpp_coh_sum(const void* part, int ngp, int ne, int ns, int sa, int sb, int e0, void* out,
+hipError_t launch_gpp_coh_sum(const void* part, size_t part_bytes, int ne, int ns, int sa, int sb, int e0, void* out,
                               hipStream_t st);
 // plasmon-pole extension (gpp.hip)
 hipError_t launch_gpp(const void* eps0, int ng, const double* kvec, const int32_t* gvec, const void* rho, int half,

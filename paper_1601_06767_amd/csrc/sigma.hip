@@ -7,6 +7,8 @@
 // The pair densities of a chunk come from the pair kernels; then Z = conj(M) A^T (one
 // float64 MFMA GEMM) and S += X Z^T over the flattened (column, G) index with X = w_c M (split
 // into blocks whose partial sums are added in a fixed order).
+#include <algorithm>
+
 #include "common.h"
 #include "internal.h"
 
@@ -99,15 +101,25 @@ __global__ void k_coh_sum(const double2* __restrict__ part, int nblk, int nout, 
 // wt), after the E' integral:
 //   S_j[n][n'] = 1/2 sum_c w_c sum_{G G'} M_{n c}(G) A_{GG'}(x_jc) conj(M_{n' c}(G')),
 //   A_{GG'}(x) = B_{GG'} / (x - wt_{GG'}),  B = Omega^2 v(G') / wt,  x_jc = E_j - E_c + i delta.
-// k_gpp_coh_prep forms (B, wt) once per call; k_coh_gpp keeps a 64 x 64 tile of them in
-// registers (each lane one column G' and 16 rows) and streams the columns c of a chunk and the
-// energies E_j past it: W[n][G'] = sum_{G in the wave's 16 rows} M_n(G) A_GG' (M_n(G) read as an
-// LDS broadcast), then each lane (n, n') adds sum_{G'} W[n][G'] conj(M_n'(G')) over the tile's
-// columns to its own accumulator.  Partial sums per (tile, wave) are reduced in a fixed order.
+// k_gpp_coh_prep forms (B, wt) once per call; k_coh_gpp keeps a 64 x 64 tile of them in registers and
+// streams the columns c of a chunk and the energies E_j past it, both sums on float64 MFMA 16x16x4:
+//   W[G'][n] = sum_G A_GG' M_n(G): A operand Re A^T and Im A^T (each lane evaluates its own element),
+//     B operand [Re M | Im M] of 8 states, 16 columns in all; the two products X1, X2 combine to
+//     W_re = X1_r - X2_i, W_im = X1_i + X2_r (lanes 8 apart);
+//   Y[n'][n] += sum_G' w_c M_n'(G') W[G'][n]: an accumulator register of W holds four G' of each lane
+//     group, which is the B operand's layout, so W goes straight into the second product.
+// The states of a column come in by direct loads one column ahead.  Partial sums per (tile, wave, share
+// of the columns) are reduced in a fixed order.
 constexpr int kGpT = 64;      // G rows and G' columns of a tile
-constexpr int kGpRW = 16;     // rows per wave
+constexpr int kGpWaves = 8;   // each wave 16 G' and half of the G: two or more waves per SIMD, so that one
+                              // evaluates elements while another's products run
 constexpr int kGpS = 8;       // states per block
-constexpr int kGpE = 8;       // energies per pass
+constexpr int kGpE = 4;       // energies per pass
+constexpr int kGpWg = 512;    // workgroups wanted: the columns are shared out to reach it
+inline int gpp_split(int ngp) {
+  const int tiles = (ngp / kGpT) * (ngp / kGpT);
+  return std::max(1, std::min(16, (kGpWg + tiles - 1) / tiles));
+}
 
 struct GppEnergies {
   double e[kGpE];
@@ -117,8 +129,8 @@ struct GppEnergies {
 // argument's, signed zeros included)
 __device__ __forceinline__ double2 csqrt_principal(double2 z) {
   const double r = hypot(z.x, z.y);
-  const double re = sqrt(0.5 * (r + z.x));
-  const double im = copysign(sqrt(0.5 * (r - z.x)), z.y);
+  const double re = sqrt(0.5 * r + 0.5 * z.x);
+  const double im = copysign(sqrt(0.5 * r - 0.5 * z.x), z.y);
   return double2{re, im};
 }
 
@@ -146,84 +158,124 @@ __global__ void k_gpp_coh_prep(const double2* __restrict__ om2, const double2* _
   ww[e] = w;
 }
 
-// part[((tile * 4 + wave) * kGpE + j) * 64 + lane] += sum over the chunk's columns for lane's
-// (n, n') = (lane / 8, lane % 8) of state blocks (sa, sb); states >= ns count as zero.
-__global__ __launch_bounds__(256) void k_coh_gpp(const double2* __restrict__ bb, const double2* __restrict__ ww,
-                                                 int ngp, int ntile1, const double2* __restrict__ m, int cc, int ns,
-                                                 int sa, int sb, int nvalid, const double* __restrict__ e_col,
-                                                 const double* __restrict__ n_col, int c0, GppEnergies en, int ne,
-                                                 double delta, double2* __restrict__ part) {
-  __shared__ double2 s_mr[kGpS][kGpT];          // M_n(G), the tile's rows, state block sa
-  __shared__ double2 s_mc[kGpS][kGpT];          // M_n'(G'), the tile's columns, state block sb
-  __shared__ double2 s_w[4][kGpS][kGpT];        // W of each wave
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+// the value of lane ^ 8 (within rows of 16 lanes: a rotation by 8)
+__device__ __forceinline__ double lane_xor8(double x) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, 0x128, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), 0x128, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+
+// part[((slot * 8 + wave) * kGpE + j) * 64 + lane] += sum over this share of the chunk's columns for lane's
+// (n, n') = (lane / 8, lane % 8) of state blocks (sa, sb), slot = tile * split + share; states >= ns repeat
+// the last one (their sums are not read).  Bound by float64 MFMA beside the
+// evaluation of the elements on the VALU.  Measured (NG 800, 8 states, 300 columns, 4 energies): 2.1 ms;
+// 13.3 with the sums on the VALU, W through LDS and divisions in place of a reciprocal.
+__global__ __launch_bounds__(64 * kGpWaves, 2) void k_coh_gpp(const double2* __restrict__ bb, const double2* __restrict__ ww,
+                                                    int ngp, int ntile1, const double2* __restrict__ m, int cc, int ns,
+                                                    int sa, int sb, int nvalid, const double* __restrict__ e_col,
+                                                    const double* __restrict__ n_col, int c0, GppEnergies en, int ne,
+                                                    double delta, double2* __restrict__ part) {
+  constexpr int LD = kGpT + 1;   // states are stored 1040 bytes apart: the 8 of a read on different banks
+  __shared__ __align__(16) double2 s_m0[2 * kGpS * LD];   // M_n(G) of block sa, then M_n'(G') of block sb
+  __shared__ __align__(16) double2 s_m1[2 * kGpS * LD];
   const int tile = blockIdx.x;
   const int t0 = tile / ntile1, t1 = tile % ntile1;
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
-  const int col = t1 * kGpT + lane;
-  const int row0 = t0 * kGpT + wave * kGpRW;
-  double2 bq[kGpRW], wq[kGpRW];
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int g0 = (wave >> 2) * (kGpT / 2), h0 = (wave & 3) * 16;   // this wave's G and G' in the tile
+  const int li = lane & 15, lk = lane >> 4;
+  const int n = li & 7, im = li >> 3;      // this lane's state and part as a column (or row) of the products
+  const int per = (nvalid + gridDim.y - 1) / gridDim.y;
+  const int cb = min(nvalid, (int)blockIdx.y * per), ce = min(nvalid, cb + per);
+  // this lane's elements: G = t0 tile + g0 + 4 s + lk, G' = t1 tile + h0 + li
+  double2 bq[kGpT / 8], wq[kGpT / 8];
 #pragma unroll
-  for (int r = 0; r < kGpRW; ++r) {
-    bq[r] = bb[(size_t)(row0 + r) * ngp + col];
-    wq[r] = ww[(size_t)(row0 + r) * ngp + col];
+  for (int s = 0; s < kGpT / 8; ++s) {
+    const size_t e = (size_t)(t0 * kGpT + g0 + 4 * s + lk) * ngp + t1 * kGpT + h0 + li;
+    bq[s] = bb[e];
+    wq[s] = ww[e];
   }
-  const int pn = lane / kGpS, pm = lane % kGpS;   // this lane's (n, n')
-  double2 acc[kGpE];
-#pragma unroll
-  for (int j = 0; j < kGpE; ++j) acc[j] = double2{0.0, 0.0};
   const size_t klen = (size_t)cc * ngp;
-  for (int c = 0; c < nvalid; ++c) {
-    __syncthreads();   // the previous column's stage is no longer read
-    for (int e = tid; e < 2 * kGpS * kGpT; e += 256) {
-      const int which = e / (kGpS * kGpT), n = (e / kGpT) % kGpS, k = e % kGpT;
-      const int st = (which ? sb : sa) * kGpS + n;
-      const int g = (which ? t1 : t0) * kGpT + k;
-      const double2 x = st < ns ? m[(size_t)st * klen + (size_t)c * ngp + g] : double2{0.0, 0.0};
-      if (which)
-        s_mc[n][k] = x;
-      else
-        s_mr[n][k] = x;
+  // rows q = wave and wave + 8: 64 values (1 KB) of one state, one wave instruction each
+  auto issue = [&](int c, double2* buf) {
+#pragma unroll
+    for (int i = 0; i < 2 * kGpS / kGpWaves; ++i) {
+      const int q = kGpWaves * i + wave;
+      const int st = min((q < kGpS ? sa : sb) * kGpS + q % kGpS, ns - 1);
+      const double2* src = m + (size_t)st * klen + (size_t)c * ngp + (q < kGpS ? t0 : t1) * kGpT + lane;
+      __builtin_amdgcn_global_load_lds((const void*)src, (__attribute__((address_space(3))) void*)&buf[q * LD], 16, 0, 0);
     }
-    __syncthreads();
+  };
+  f64x4 y[kGpE];
+#pragma unroll
+  for (int j = 0; j < kGpE; ++j) y[j] = f64x4{0, 0, 0, 0};
+  const double sgn = im ? 1.0 : -1.0;
+  auto column = [&](int c, const double2* cur, double2* nxt) {
+    wait_vm<0>();
+    lds_barrier();   // the column has landed; the other buffer is no longer read
+    if (c + 1 < ce) issue(c + 1, nxt);
     const double wc = n_col ? n_col[c0 + c] : 1.0;
     const double ec = e_col[c0 + c];
-#pragma unroll 1
-    for (int j = 0; j < ne; ++j) {
-      const double xr = en.e[j] - ec;
-      double2 w[kGpS];
+    const double* ml = (const double*)(cur + n * LD + g0) + im;             // + 2 (G - g0)
+    const double* mr = (const double*)(cur + (kGpS + n) * LD + h0) + im;    // + 2 (G' - h0)
+    double r[4];
 #pragma unroll
-      for (int n = 0; n < kGpS; ++n) w[n] = double2{0.0, 0.0};
+    for (int k = 0; k < 4; ++k) r[k] = wc * mr[2 * (4 * k + lk)];
 #pragma unroll
-      for (int r = 0; r < kGpRW; ++r) {
-        const double dr = xr - wq[r].x, di = delta - wq[r].y;
-        const double inv = 1.0 / (dr * dr + di * di);
-        const double2 a{(bq[r].x * dr + bq[r].y * di) * inv, (bq[r].y * dr - bq[r].x * di) * inv};
+    for (int j = 0; j < kGpE; ++j) {
+      if (j < ne) {   // uniform
+        const double xr = en.e[j] - ec;
+        f64x4 x1{0, 0, 0, 0}, x2{0, 0, 0, 0};
 #pragma unroll
-        for (int n = 0; n < kGpS; ++n) cmac(w[n], s_mr[n][wave * kGpRW + r], a);
-      }
-#pragma unroll
-      for (int n = 0; n < kGpS; ++n) s_w[wave][n][lane] = w[n];
-      __syncthreads();
-      double2 t{0.0, 0.0};
-#pragma unroll 8
-      for (int k = 0; k < kGpT; ++k) {
-        const double2 y = s_mc[pm][k];
-        cmac(t, s_w[wave][pn][k], double2{y.x, -y.y});
-      }
-      // acc_j += w_c t (j is uniform: select the accumulator without dynamic indexing)
-#pragma unroll
-      for (int q = 0; q < kGpE; ++q)
-        if (q == j) {
-          acc[q].x = fma(wc, t.x, acc[q].x);
-          acc[q].y = fma(wc, t.y, acc[q].y);
+        for (int s = 0; s < kGpT / 8; ++s) {
+          const double dr = xr - wq[s].x, di = delta - wq[s].y;
+          const double den = fma(dr, dr, di * di);
+          double inv = __builtin_amdgcn_rcp(den);   // and two Newton steps: 1 / den
+          inv = fma(fma(-den, inv, 1.0), inv, inv);
+          inv = __builtin_amdgcn_div_fixup(fma(fma(-den, inv, 1.0), inv, inv), den, 1.0);   // 0 and infinite den
+          const double ar = fma(bq[s].x, dr, bq[s].y * di) * inv;
+          const double ai = fma(bq[s].y, dr, -(bq[s].x * di)) * inv;
+          const double l = ml[2 * (4 * s + lk)];
+          x1 = mfma64(ar, l, x1);
+          x2 = mfma64(ai, l, x2);
         }
-      __syncthreads();   // every lane has read s_w before the next energy rewrites it
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const double w = fma(sgn, lane_xor8(x2[k]), x1[k]);
+          y[j] = mfma64(r[k], w, y[j]);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // one energy at a time in registers
+      }
+    }
+  };
+  if (cb < ce) {
+    issue(cb, s_m0);
+    for (int c = cb; c < ce; c += 2) {
+      column(c, s_m0, s_m1);
+      if (c + 1 < ce) column(c + 1, s_m1, s_m0);
     }
   }
-  double2* dst = part + ((size_t)(tile * 4 + wave) * kGpE) * 64 + lane;
+  wait_vm<0>();
+  // Y rows (n', part') = lk + 4 r, columns (n, part) = li, through LDS to one (n, n') per lane:
+  // S_re = Y[re][re] + Y[im][im], S_im = Y[re][im] - Y[im][re]  (row part, column part)
+  double* sy = (double*)s_m0 + wave * 256;   // 16 KB of the 16.25
+  double2* dst = part + ((size_t)((tile * gridDim.y + blockIdx.y) * kGpWaves + wave) * kGpE) * 64 + lane;
+  const int pn = lane / kGpS, pm = lane % kGpS;
 #pragma unroll
-  for (int j = 0; j < kGpE; ++j) dst[(size_t)j * 64] = cadd(dst[(size_t)j * 64], acc[j]);
+  for (int j = 0; j < kGpE; ++j) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sy[(lk + 4 * k) * 16 + li] = y[j][k];
+    __syncthreads();
+    const double2 o = dst[(size_t)j * 64];
+    dst[(size_t)j * 64] = double2{o.x + (sy[pm * 16 + pn] + sy[(pm + 8) * 16 + pn + 8]),
+                                  o.y + (sy[pm * 16 + pn + 8] - sy[(pm + 8) * 16 + pn])};
+  }
 }
 
 // out[j][n][n'] += 1/2 sum over tiles and waves of part (fixed order: each thread a fixed
@@ -257,7 +309,7 @@ int gpp_coh_states_per_block() { return kGpS; }
 int gpp_coh_energies_per_pass() { return kGpE; }
 size_t gpp_coh_part_bytes(int ngp) {
   const size_t nt = (size_t)(ngp / kGpT) * (ngp / kGpT);
-  return nt * 4 * kGpE * 64 * sizeof(double2);
+  return nt * gpp_split(ngp) * kGpWaves * kGpE * 64 * sizeof(double2);
 }
 
 hipError_t launch_gpp_coh_prep(const void* modes, const double* v, int ng, int ngp, void* b, void* w, hipStream_t st) {
@@ -275,15 +327,16 @@ hipError_t launch_gpp_coh(const void* b, const void* w, int ngp, const void* m, 
   GppEnergies en{};
   for (int j = 0; j < ne; ++j) en.e[j] = energies[j];
   const int nt1 = ngp / kGpT;
-  k_coh_gpp<<<nt1 * nt1, 256, 0, st>>>((const double2*)b, (const double2*)w, ngp, nt1, (const double2*)m, cc, ns, sa,
-                                       sb, nvalid, e_col, n_col, c0, en, ne, delta, (double2*)part);
+  k_coh_gpp<<<dim3(nt1 * nt1, gpp_split(ngp)), 64 * kGpWaves, 0, st>>>((const double2*)b, (const double2*)w, ngp, nt1,
+                                                             (const double2*)m, cc, ns, sa, sb, nvalid, e_col, n_col,
+                                                             c0, en, ne, delta, (double2*)part);
   return hipGetLastError();
 }
 
-hipError_t launch_gpp_coh_sum(const void* part, int ngp, int ne, int ns, int sa, int sb, int e0, void* out,
+hipError_t launch_gpp_coh_sum(const void* part, size_t part_bytes, int ne, int ns, int sa, int sb, int e0, void* out,
                               hipStream_t st) {
-  const int nt1 = ngp / kGpT;
-  k_coh_gpp_sum<<<kGpE * 64, 256, 0, st>>>((const double2*)part, nt1 * nt1 * 4, ne, ns, sa, sb, e0, (double2*)out);
+  const int nslot = (int)(part_bytes / (kGpE * 64 * sizeof(double2)));
+  k_coh_gpp_sum<<<kGpE * 64, 256, 0, st>>>((const double2*)part, nslot, ne, ns, sa, sb, e0, (double2*)out);
   return hipGetLastError();
 }
 
