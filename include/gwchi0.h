@@ -267,22 +267,19 @@ gw_status gw_chi0_backward_ksum(gw_ctx* ctx, const gw_chi0_problem* probs, int n
  * Needs a context on a non-null stream.  Disabling drops the cached graphs. */
 gw_status gw_ctx_set_graph(gw_ctx* ctx, int enable);
 
-/* Launch-shape tuner: on the first conduction chunk of each problem, times the
- * forms of the pair kernel and the contraction with
- * 1..32 pair-range splits, and keeps the fastest per problem shape in the context.
+/* Launch-shape tuner: on the first conduction chunk of each problem, times the contraction with
+ * 1..32 pair-range splits and keeps the fastest per problem shape in the context.
  * Later gw_chi0_workspace_size / gw_chi0_build calls use the tuned shapes (query the
  * workspace size again after tuning).  Synchronises the stream; workspace as for
  * gw_chi0_build. */
 gw_status gw_tune(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nomega, gw_precision prec,
                   void* workspace, size_t ws_bytes);
-/* The tuned shapes for prob's problem shape: pair-kernel form (float32 up to max|n_chi| = 7:
- * 1 = 4 valence x 16 conduction bands per workgroup, 2 = 4 x 8 with two row quads per step and each
- * line's x3 sum shared by two waves, on grids up to 52 points, 3 = the same for any grid; elsewhere,
- * and for forms not built for the sphere, the one form there is) and the number of pair-range
- * splits of the contraction; both 0 if the shape was not tuned. */
+/* The tuned shapes for prob's problem shape: pair-kernel form (there is one, 1) and the number of
+ * pair-range splits of the contraction; both 0 if the shape was not tuned. */
 gw_status gw_tune_get(gw_ctx* ctx, const gw_chi0_problem* prob, gw_precision prec, int* pair_variant, int* ksplit);
 /* Sets the shapes for prob's problem shape, e.g. to restore what gw_tune_get reported in
- * an earlier process: pair_variant 0..7 (0 = automatic), ksplit 0..32 (0 = automatic);
+ * an earlier process: pair_variant 0..7 (0 = automatic; every value
+ * runs the one form), ksplit 0..32 (0 = automatic);
  * both 0 forgets the shape.  GW_EINVAL outside those ranges. */
 gw_status gw_tune_set(gw_ctx* ctx, const gw_chi0_problem* prob, gw_precision prec, int pair_variant, int ksplit);
 

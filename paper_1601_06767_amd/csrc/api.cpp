@@ -350,22 +350,16 @@ gw_status gw_geom_create(gw_ctx* ctx, const int n_fft[3], const double* cell, co
     }
   std::vector<float> fac32(fac64.begin(), fac64.end());
   const size_t nfac = fac32.size();
-  // MFMA blocks of a quad: groups of four frequencies of even C, odd C, even S, odd S; of quad 0:
-  // even C and odd C (ones), the second even C, odd S
-  const int ne = hk / 2 + 1, no = (hk + 1) / 2, ns = hk / 2;
-  const int ge = (ne + 3) / 4, go = (no + 3) / 4, gs = (ns + 3) / 4;
-  fac32.resize(nfac + (size_t)nq * 64, 0.f);
+  // slots of the MFMA forms (Slots of fold.h), 32 floats per quad
+  const int ngr = hk >= 8 ? 2 : 1;
+  fac32.resize(nfac + (size_t)nq * 32, 0.f);
   for (int j = 0; j < nq; ++j) {
     const double* f = &fac64[(size_t)j * 2 * (hk + 1)];
-    float* a = &fac32[nfac + (size_t)j * 64];
-    for (int i = 0; i < ne; ++i) a[i] = j == 0 ? 1.f : (float)f[2 * i];
-    for (int i = 0; i < no; ++i) a[4 * ge + i] = j == 0 ? 1.f : (float)f[2 * i + 1];
-    if (j == 0) {
-      for (int i = 0; i < ne; ++i) a[4 * (ge + go) + i] = (float)f[2 * i];
-      for (int i = 0; i < no; ++i) a[4 * (2 * ge + go) + i] = (float)f[2 * i + 1];
-    } else {
-      for (int i = 0; i < ns; ++i) a[4 * (ge + go) + i] = (float)f[hk + 1 + 2 * i + 2];
-      for (int i = 0; i < no; ++i) a[4 * (ge + go + gs) + i] = (float)f[hk + 1 + 2 * i + 1];
+    float* a = &fac32[nfac + (size_t)j * 32];
+    for (int n = 0; n <= hk; ++n) {
+      float* c = a + 4 * (((n % 2) * ngr + n / 8) * 2) + n / 2 % 4;   // S: the next slot
+      c[0] = j == 0 ? 1.f : (float)f[n];
+      c[4] = j == 0 ? (float)f[n] : (float)f[hk + 1 + n];
     }
   }
   gw_geom* gg = new (std::nothrow) gw_geom();

@@ -50,7 +50,7 @@ std::string shape_key(const Geom& g, int nv, int ncol, gw_precision prec) {
 
 struct ProbPlan {
   const gw_chi0_problem* p = nullptr;
-  int nvs = 0, cc = 0, npair = 0, ksplit = 1, ntl = 0, minb = 0;
+  int nvs = 0, cc = 0, npair = 0, ksplit = 1, ntl = 0;
   size_t off_psiv = 0, off_m = 0, off_w = 0, off_acc = 0, acc_one = 0;
   size_t off_m2 = 0, off_w2 = 0;   // second pair-density / weight buffers of the forward build
   size_t off_img = 0, off_img2 = 0;   // static split-bf16 x3: bf16 row images of M and w M per buffer
@@ -126,7 +126,6 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
     int k = std::min(std::max(ks_par, ks_cache), ks_mem);
     auto it = ctx->tune.find(shape_key(q.p->geom->g, q.p->nv, q.p->ncol, prec));
     if (it != ctx->tune.end()) {
-      q.minb = it->second.first;
       if (it->second.second > 0) k = it->second.second;
     }
     if (force_ksplit) k = force_ksplit;
@@ -218,9 +217,9 @@ gw_status pair_block(gw_ctx* ctx, const Layout& L, const ProbPlan& q, char* ws) 
   hipError_t e;
   {
     gw::StageScope sc(ctx, gw::kStagePlanes);
-    e = L.fp64 ? gw::launch_pair_planes<double>(g, ws + q.off_psiv, ws + L.off_psic, q.nvs, q.cc, ws + L.off_q, q.minb,
+    e = L.fp64 ? gw::launch_pair_planes<double>(g, ws + q.off_psiv, ws + L.off_psic, q.nvs, q.cc, ws + L.off_q,
                                                 ctx->stream)
-               : gw::launch_pair_planes<float>(g, ws + q.off_psiv, ws + L.off_psic, q.nvs, q.cc, ws + L.off_q, q.minb,
+               : gw::launch_pair_planes<float>(g, ws + q.off_psiv, ws + L.off_psic, q.nvs, q.cc, ws + L.off_q,
                                                ctx->stream);
   }
   GW_HIP(ctx, e);
@@ -986,33 +985,14 @@ gw_status gw_tune(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nome
   for (int ip = 0; ip < nprob && result == GW_OK; ++ip) {
     const gw_chi0_problem& p = probs[ip];
     const std::string key = shape_key(p.geom->g, p.nv, p.ncol, prec);
-    int best_minb = 0, best_ks = 0;
+    int best_ks = 0;
     float best = 1e30f;
-    // pair kernel: 256 threads with one or two resident workgroups per CU, or the 512-thread split-line form
     Layout L = make_layout(ctx, &p, 1, std::max(1, nomega), false, prec, false);
     if (L.total > ws_bytes) {
       result = gw::fail(ctx, GW_EINVAL, "workspace too small for tuning");
       break;
     }
-    ProbPlan q = L.pp[0];
-    GW_HIP(ctx, gw::launch_weights(p.e_v, 0, p.nv, q.nvs, p.e_col, p.n_col, 0, p.ncol, q.cc, 0.0, 0.0, 1,
-                                   (double*)(ws + q.off_w), ctx->stream));
-    result = band_to_real(ctx, L, p.geom->g, (const double2*)p.coef_v, p.nv, nullptr, 0, p.nv, q.nvs, ws, ws + q.off_psiv);
-    if (result == GW_OK)
-      result = band_to_real(ctx, L, p.geom->g, (const double2*)p.coef_c, p.nband, p.col_band, 0, p.ncol, q.cc, ws,
-                            ws + L.off_psic);
-    for (int minb = 1; minb <= gw::kPairVariants && result == GW_OK; ++minb) {
-      q.minb = minb;
-      float t0 = 0, t1 = 0;
-      result = timed([&] { return pair_block(ctx, L, q, ws); }, &t0);   // warm-up
-      if (result == GW_OK) result = timed([&] { return pair_block(ctx, L, q, ws); }, &t1);
-      if (result == GW_OK && t1 < best) {
-        best = t1;
-        best_minb = minb;
-      }
-    }
     // contraction: pair-range splits
-    best = 1e30f;
     for (int ks : {1, 2, 4, 8, 16, 32}) {
       if (result != GW_OK) break;
       Layout Lk = make_layout(ctx, &p, 1, std::max(1, nomega), false, prec, false, ks);
@@ -1052,7 +1032,7 @@ gw_status gw_tune(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nome
         best_ks = ks;
       }
     }
-    if (result == GW_OK && best_minb && best_ks) ctx->tune[key] = std::make_pair(best_minb, best_ks);
+    if (result == GW_OK && best_ks) ctx->tune[key] = std::make_pair(1, best_ks);   // the pair kernel has one form
   }
   ctx->timing = timing;
   (void)hipEventDestroy(a);

@@ -37,8 +37,6 @@ template <typename V> __device__ __forceinline__ Fold<V> fold_quad0(const V (&p)
 // Frequencies 0 .. RC of a line: NE even ones from 0, NO odd ones, NS = NE - 1 even ones from 2.
 template <int RC> struct Freq {
   static constexpr int NE = RC / 2 + 1, NO = (RC + 1) / 2, NS = RC / 2;
-  // groups of four rows of each sum, for the MFMA form
-  static constexpr int GE = (NE + 3) / 4, GO = (NO + 3) / 4, GS = (NS + 3) / 4;
 };
 
 // Running sums of one line on the vector units.  Factors: row of quad j of the table written by
@@ -88,54 +86,86 @@ template <typename T, int RC> struct LineSums {
 
 typedef float fold_f32x4 __attribute__((ext_vector_type(4)));
 
-// The same in float32 on the matrix cores: v_mfma_f32_4x4x1 forms, in each of 16 blocks of four
-// lanes, D[4 rows][4 columns] += A[4 rows] B[4 columns].  Each lane is one column (its own line)
-// and holds four frequencies per accumulator; A holds the factors of the quad in the blocks of one
-// register (block b: group b of even C, odd C, even S, odd S; lane 4 b + r: row r), and cbsz = 4 with
-// abid = b broadcasts block b to all lanes, so one 4-byte register per lane serves a whole quad.
-// Four FMAs per lane in 8 cycles of the matrix core, beside the products and folds on the VALU.
+// Slots of the MFMA forms: four frequencies of one sum each, those of a line's C and S paired so that
+// one lane holds both.  Slot (odd, part, g), part 0 = C, 1 = S: n = 2 (4 g + i) + odd, i = 0 .. 3
+// (S of n = 0 has zero factors).  Factors of a quad: 32 floats, four of each slot in order; of quad 0,
+// S even holds the second even sum of C.
+template <int RC> struct Slots {
+  using F = Freq<RC>;
+  static constexpr int NG = RC >= 8 ? 2 : 1;
+  static constexpr int N = 4 * NG;
+  static constexpr int at(int odd, int part, int g) { return (odd * NG + g) * 2 + part; }
+  static constexpr bool used(int i) { return 4 * (i / 2 % NG) < (i / 2 / NG ? F::NO : F::NE); }
+  // the combination that slot i sums
+  template <typename V> static __device__ __forceinline__ V part(const Fold<V>& q, int i) {
+    return i / 2 / NG == 0 ? (i % 2 == 0 ? q.ce : q.se) : (i % 2 == 0 ? q.co : q.so);
+  }
+};
+
+// Running sums of one line per lane in float32 on the matrix cores.  v_mfma_f32_4x4x1 forms, in each of
+// 16 blocks of four lanes, D[4 rows][4 columns] += A[4 rows] B[4 columns].  Here each lane is one column
+// (its own line) and holds four frequencies per accumulator; A holds the factors (lane 4 b + r: row r of
+// slot b), and cbsz = 4 with abid = b broadcasts block b to all lanes, so one 4-byte register per lane
+// serves a whole quad.  Four FMAs per lane in 8 cycles of the matrix core, beside the VALU.
 template <int RC> struct MfmaSums {
   using V = float2;
-  using F = Freq<RC>;
-  fold_f32x4 ce[F::GE][2], co[F::GO][2], se[F::GS > 0 ? F::GS : 1][2], so[F::GO][2];
+  using S = Slots<RC>;
+  fold_f32x4 a[S::N][2];
   __device__ __forceinline__ void clear() {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-#pragma unroll
-      for (int g = 0; g < F::GE; ++g) ce[g][k] = fold_f32x4{0, 0, 0, 0};
-#pragma unroll
-      for (int g = 0; g < F::GO; ++g) co[g][k] = so[g][k] = fold_f32x4{0, 0, 0, 0};
-#pragma unroll
-      for (int g = 0; g < F::GS; ++g) se[g][k] = fold_f32x4{0, 0, 0, 0};
+    for (int i = 0; i < S::N; ++i) a[i][0] = a[i][1] = fold_f32x4{0, 0, 0, 0};
+  }
+  template <int I> __device__ __forceinline__ void mac(fold_f32x4 (&d)[2], float f, V x) {
+    d[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, x.x, d[0], 4, I, 0);
+    d[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, x.y, d[1], 4, I, 0);
+  }
+  template <int I = 0> __device__ __forceinline__ void add(const Fold<V>& q, float f) {
+    if constexpr (I < S::N) {
+      if constexpr (S::used(I)) mac<I>(a[I], f, S::part(q, I));
+      add<I + 1>(q, f);
     }
   }
-  template <int B, int G> static __device__ __forceinline__ void mac(fold_f32x4 (*a)[2], float f, V x) {
-    if constexpr (G > 0) {
-      a[0][0] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, x.x, a[0][0], 4, B, 0);
-      a[0][1] = __builtin_amdgcn_mfma_f32_4x4x1f32(f, x.y, a[0][1], 4, B, 0);
-      mac<B + 1, G - 1>(a + 1, f, x);
+  // quad 0: slots S even go to C even
+  template <int I = 0> __device__ __forceinline__ void add0(const Fold<V>& q, float f) {
+    if constexpr (I < S::N) {
+      if constexpr (S::used(I)) mac<I>(a[I < S::N / 2 ? I & ~1 : I], f, S::part(q, I));
+      add0<I + 1>(q, f);
     }
   }
-  __device__ __forceinline__ void add(const Fold<V>& q, float f) {
-    mac<0, F::GE>(ce, f, q.ce);
-    mac<F::GE, F::GO>(co, f, q.co);
-    mac<F::GE + F::GO, F::GS>(se, f, q.se);
-    mac<F::GE + F::GO + F::GS, F::GO>(so, f, q.so);
+  __device__ __forceinline__ V get(int part, int n) const {
+    const int i = S::at(n % 2, part, n / 8);
+    return V{a[i][0][n / 2 % 4], a[i][1][n / 2 % 4]};
   }
-  // quad 0: the blocks are even C (ones), odd C (ones), the second even C, odd S
-  __device__ __forceinline__ void add0(const Fold<V>& q, float f) {
-    mac<0, F::GE>(ce, f, q.ce);
-    mac<F::GE, F::GO>(co, f, q.co);
-    mac<F::GE + F::GO, F::GE>(ce, f, q.se);
-    mac<2 * F::GE + F::GO, F::GO>(so, f, q.so);
+  __device__ __forceinline__ V c(int n) const { return get(0, n); }
+  __device__ __forceinline__ V s(int n) const { return get(1, n); }
+};
+
+// The same sums with the roles exchanged: A holds the data of the block's four lanes (four lines), B the
+// factors of a slot (blgp broadcasts one 16-lane section to all four: lane 16 s + 4 x + i holds factor i of
+// slot s), so that lane 4 b + i receives frequency i of all four lines of its block in one accumulator.
+template <int RC> struct MfmaTranspose {
+  using V = float2;
+  using S = Slots<RC>;
+  fold_f32x4 a[S::N][2];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int i = 0; i < S::N; ++i) a[i][0] = a[i][1] = fold_f32x4{0, 0, 0, 0};
   }
-  __device__ __forceinline__ V c(int n) const {
-    const int i = n / 2;
-    return n % 2 == 0 ? V{ce[i / 4][0][i % 4], ce[i / 4][1][i % 4]} : V{co[i / 4][0][i % 4], co[i / 4][1][i % 4]};
+  template <int I> __device__ __forceinline__ void mac(fold_f32x4 (&d)[2], const float (&f)[S::NG], V x) {
+    d[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(x.x, f[I / 4], d[0], 0, 0, 4 + I % 4);
+    d[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(x.y, f[I / 4], d[1], 0, 0, 4 + I % 4);
   }
-  __device__ __forceinline__ V s(int n) const {
-    const int i = n % 2 == 0 ? n / 2 - 1 : n / 2;
-    return n % 2 == 0 ? V{se[i / 4][0][i % 4], se[i / 4][1][i % 4]} : V{so[i / 4][0][i % 4], so[i / 4][1][i % 4]};
+  template <int I = 0> __device__ __forceinline__ void add(const Fold<V>& q, const float (&f)[S::NG]) {
+    if constexpr (I < S::N) {
+      if constexpr (S::used(I)) mac<I>(a[I], f, S::part(q, I));
+      add<I + 1>(q, f);
+    }
+  }
+  template <int I = 0> __device__ __forceinline__ void add0(const Fold<V>& q, const float (&f)[S::NG]) {
+    if constexpr (I < S::N) {
+      if constexpr (S::used(I)) mac<I>(a[I < S::N / 2 ? I & ~1 : I], f, S::part(q, I));
+      add0<I + 1>(q, f);
+    }
   }
 };
 

@@ -109,7 +109,7 @@ struct Geom {
   double2* d_tw64 = nullptr;     // exp(+2 pi i k / nt), k < nt (behind d_pts64)
   double* d_fac64 = nullptr;     // [j][n <= rchi] cos, then sin; quad 0: cos or sin(n pi/2)
   float* d_fac32 = nullptr;
-  float* d_amat = nullptr;       // [j][64] the same as MFMA blocks (behind d_fac32)
+  float* d_amat = nullptr;       // [j][32] the same as slots of the MFMA forms (behind d_fac32)
   bool has_q = false;            // cell and q given: the dielectric sphere's order was checked
   double q[3] = {0.0, 0.0, 0.0}; // reciprocal-lattice units
   double cell[9] = {};           // lattice vectors as rows (bohr)
@@ -159,13 +159,12 @@ hipError_t launch_gpp_coh_sum(const void* part, size_t part_bytes, int ne, int n
 // plasmon-pole extension (gpp.hip)
 hipError_t launch_gpp(const void* eps0, int ng, const double* kvec, const int32_t* gvec, const void* rho, int half,
                       const double* omega, int nomega, double eta, void* modes, void* out, hipStream_t st);
-constexpr int kPairVariants = 7;   // forms of the pair kernel a tuned shape may name
+constexpr int kPairVariants = 7;   // pair-kernel numbers that a tuned shape may name (all the one form)
 // Pair planes: Q[pair][x1][line] for pairs (v, c), v < nvs (multiple of 4), c < ncs (multiple of 8),
-// pair = v * ncs + c.  form: 0 automatic; a form that is not built for the sphere runs the
-// automatic one.
+// pair = v * ncs + c.
 template <typename T>
 hipError_t launch_pair_planes(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q,
-                              int form, hipStream_t st);
+                              hipStream_t st);
 // Pair finish: x1 transforms, 1/N, gather to the chi sphere: m[pair][ngp] (zero padded).
 template <typename T>
 hipError_t launch_pair_finish(const Geom& g, const void* q, int npair, void* m, hipStream_t st);

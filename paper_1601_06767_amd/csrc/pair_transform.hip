@@ -4,12 +4,9 @@
 // that only produces the K = 2 RC + 1 frequencies per axis the sphere needs, on the smallest
 // alias-free grid (fold.h).
 //
-// k_pair_planes (one x1 plane, TV valence x TC conduction bands per workgroup) walks the plane's
-// quads of x2 rows:
-//   stage 1, per lane one (pair, x2 row): the product along x3 and the folded x3 sums ->
-//     Z[pair][row][n3] in LDS;
-//   stage 2, per lane (pair, n3): the folded x2 sums over the quad's four rows, accumulated over
-//     the quads in registers;
+// k_pair_planes (float64) and k_pair_planes_mfma (float32), per x1 plane and TV valence x TC conduction
+//   bands: over the plane's quads of x2 rows, the product along x3 and its folded x3 sums, then the folded
+//   x2 sums over the quad's four rows, accumulated over the quads in registers;
 //   output Q[pair][x1][l] for the lines l = (n2, n3) that hold a G of the sphere.
 // k_pair_finish (one pair per workgroup): the folded x1 sums of Q's lines, the 1/N, and the
 //   gather onto the sphere order: M[pair][G] (zero padded to ngp).
@@ -24,7 +21,365 @@ namespace gw {
 
 namespace {
 
-// Shape of a planes workgroup.  HS: waves that share a line's x3 quads (partial sums added in LDS);
+// Order of the planes' work: each XCD (workgroup b runs on XCD b mod 8) takes a contiguous run of the
+// plane-major order; within a plane, strips of kStrip column tiles, their valence tiles in turn, so that the
+// workgroups in flight on an XCD share their bands in its L2 (a plane of every band would not fit).
+// False where index i of the XCD's run is past its end.
+constexpr int kStrip = 8;
+__device__ __forceinline__ bool plane_item(int i, int nt, int nbc, int nbv, int& x1, int& bc, int& bv) {
+  const int total = nt * nbc * nbv;
+  const int per = (total + 7) / 8;
+  const int item = (int)(blockIdx.x % 8) * per + i;
+  if (i >= per || item >= total) return false;
+  x1 = item / (nbc * nbv);
+  const int pb = item % (nbc * nbv);
+  const int strip = pb / (kStrip * nbv), in = pb % (kStrip * nbv);
+  const int wide = min(kStrip, nbc - strip * kStrip);
+  bc = strip * kStrip + in % wide;
+  bv = in / wide;
+  return true;
+}
+
+// ---------------------------------------------------------------------------------------------
+// float32: both sums on the matrix cores, without an exchange through LDS.
+//
+// A wave takes PW = 16 / QL pairs and QL quads of x2 rows; lane 4 b + t is row t of a quad of a pair (b:
+// the quad in the high bits).  Stage 1 (MfmaTranspose) leaves in lane 4 b + i, per slot, the x3 sums of
+// frequency i for the four rows of the quad: the fold of the rows is within the lane.  The C and S sums
+// stay apart (x2 sums are linear); they meet at the end as C' +- i S' = Q(n2, +-n3).  With QL > 1
+// v_permlane32_swap and v_permlane16_swap trade slots for quads between the lanes of one pair: each keeps
+// NL = N / QL slots, for all the quads.  Stage 2 (MfmaSums) adds a quad's folded rows to the lane's
+// running x2 sums.
+// Rows come in by direct loads, a chunk of x3 quads of the QL row quads at a time into two buffers; the
+// only barrier is the one per chunk.
+template <int RC, int QL_, int WV_, int TV_, int TC_, int NU_, int MINW_> struct MfmaShape {
+  using S = Slots<RC>;
+  static constexpr int QL = QL_, WV = WV_, TV = TV_, TC = TC_, MINW = MINW_;
+  static constexpr int NU = NU_;                       // 16-byte units of a buffer
+  static constexpr int NT = 64 * WV;
+  static constexpr int PW = 16 / QL;                   // pairs per wave, all of one valence band
+  static constexpr int NL = S::N / QL;                 // slots a lane keeps
+  static constexpr int NR = 4 * QL;                    // rows of a band in a step
+  static constexpr int NQM = 32;                       // quads of the largest grid
+  static constexpr int NF = 16 * S::NG;                // factors of a quad
+  static constexpr int ND = (NU / 64 + WV - 1) / WV;   // direct loads of a wave per chunk
+  static constexpr int NST = NL * (2 * RC + 1);        // stores of a wave per item
+  static_assert(NST < 64, "stores in flight");
+  static_assert(TV * TC == WV * PW && TC % PW == 0 && NL % 2 == 0, "planes shape");
+  static_assert(2 * (NU + 2) * 16 + (NQM + 1) * NF * 4 + ND * NT * 4 + 124 <= 160 * 1024, "planes workgroup exceeds the LDS");
+  // units of a row in LDS: an odd number of 64-byte groups, and one unit more per band, so that the 16
+  // lanes of four rows and four bands read different banks
+  static __host__ __device__ int row_units(int cq) { return 2 * cq + (12 - 2 * cq % 8) % 8; }
+  static __host__ __device__ int band_units(int cq) { return NR * row_units(cq) + 1; }
+  static __host__ __device__ int part_units(int nb, int cq) { return (nb * band_units(cq) + 63) / 64 * 64; }
+  // chunks of x3 quads per row: an even number (two buffers in fixed roles) of equal size that fit a buffer
+  static __host__ int chunks(int nq) {
+    for (int n = 2; n <= nq; n += 2) {
+      const int cq = (nq + n - 1) / n;
+      if (part_units(TC, cq) + part_units(TV, cq) <= NU) return n;
+    }
+    return 0;
+  }
+};
+
+// swap between lane halves: a = (a's, b's lower half), b = (a's, b's upper half)
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                  false, false);
+  const unsigned x = r[0], y = r[1];   // an element of a vector cannot be bit-cast in place
+  a = __builtin_bit_cast(float, x);
+  b = __builtin_bit_cast(float, y);
+}
+// the same between the even and odd 16-lane rows
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                  false, false);
+  const unsigned x = r[0], y = r[1];   // an element of a vector cannot be bit-cast in place
+  a = __builtin_bit_cast(float, x);
+  b = __builtin_bit_cast(float, y);
+}
+
+template <int RC, typename P>
+__device__ __forceinline__ void planes_mfma(const float2* __restrict__ psi_v, const float2* __restrict__ psi_c, int nvs,
+                                            int ncs, int nt, int nl, int nch, unsigned inv_r, unsigned inv_b,
+                                            const int32_t* __restrict__ rowtab, const float* __restrict__ fac,
+                                            float2* __restrict__ q) {
+  using V = float2;
+  using S = Slots<RC>;
+  constexpr int NT = P::NT, TV = P::TV, TC = P::TC, QL = P::QL, NR = P::NR, NL = P::NL, N = S::N;
+  // the TC columns, then the TV valence bands: [band][row][units of the chunk]
+  __shared__ __align__(16) uint4 s_u0[P::NU + 2];   // the last quad's prefetch reads one quad on
+  __shared__ __align__(16) uint4 s_u1[P::NU + 2];
+  __shared__ __align__(16) float s_f[(P::NQM + 1) * P::NF];   // per quad [slot % 4][4 factors][slot / 4]
+  __shared__ int s_row[2 * RC + 1];   // per n2: lowest n3, number of n3 << 8, (first line - lowest n3) << 16
+  int it = blockIdx.x / 8, x1, c0, v0;
+  if (!plane_item(it, nt, ncs / TC, nvs / TV, x1, c0, v0)) return;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // What a lane stands for is formed anew where it is needed: the accumulators leave no registers to keep it.
+  struct Lane {
+    int lane, ti, ql, pc;   // row of the quad, or frequency of the slot; quad of the step; column band
+  };
+  const int pc0 = wave % (TC / P::PW) * P::PW, pv = wave / (TC / P::PW);
+  auto who = [&] {
+    int l = tid & 63;
+    asm volatile("" : "+v"(l));
+    return Lane{l, l & 3, (l >> 2) / P::PW, pc0 + (l >> 2) % P::PW};
+  };
+
+  const int row = nt + 2;                       // stored row length
+  const int nq = nt / 4;
+  const int nrs = (nq + QL - 1) / QL;           // row steps
+  const int cq = (nq + nch - 1) / nch;          // x3 quads per chunk (the last ones may have fewer)
+  const int lr = P::row_units(cq), lb = P::band_units(cq);
+  const int nc = P::part_units(TC, cq), nslot = (nc + P::part_units(TV, cq)) / 64;
+  const size_t band = (size_t)nt * nt * row;
+  // Direct loads: slot s (64 units) of a chunk is loaded by wave s % WV from an offset per lane that is the
+  // same for every chunk (no address arithmetic per chunk) plus a wave-uniform one.  Units that pad a row
+  // or band, and rows and units past the end, are loaded and not used; the buffers' bounds end at the bands.
+  const auto buffer = [&](const float2* psi, int nbands, int b0, int x) {
+    const size_t first = (size_t)b0 * band + (size_t)x * nt * row;
+    const size_t bytes = min(((size_t)nbands * band - first) * sizeof(V), (size_t)0xfffffff0u);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(psi + first), 0, (int)(unsigned)bytes, 0x00020000);
+  };
+  auto rsrc_c = buffer(psi_c, ncs, c0 * TC, x1);
+  auto rsrc_v = buffer(psi_v, nvs, v0 * TV, x1);
+  // The offsets are kept in LDS: the accumulators leave no registers for them.
+  __shared__ int s_off[P::ND * NT];
+#pragma unroll 1
+  for (int i = 0; i < P::ND; ++i) {
+    const int s = wave + i * P::WV;
+    const unsigned u = (64 * s >= nc ? 64 * s - nc : 64 * s) + (tid & 63);
+    const unsigned b = min((unsigned)__umulhi(u, inv_b), (unsigned)((64 * s >= nc ? TV : TC) - 1));
+    const unsigned in = min(u - b * lb, (unsigned)lb - 2);
+    const unsigned y = __umulhi(in, inv_r);
+    s_off[i * NT + tid] = (int)(b * (unsigned)(band * sizeof(V)) + y * (unsigned)(row * sizeof(V)) + (in - y * lr) * 16);
+  }
+  auto store = [](auto rsrc, unsigned at, V x) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__builtin_bit_cast(unsigned, x.x), __builtin_bit_cast(unsigned, x.y)},
+                                          rsrc, (int)at, 0, 0);
+  };
+  auto issue = [&](int rs, int ch, uint4* dst) {
+    const int at = rs * NR * row * (int)sizeof(V) + ch * cq * 32;
+    const Lane w = who();
+    int off[P::ND];
+#pragma unroll
+    for (int i = 0; i < P::ND; ++i) off[i] = s_off[i * NT + wave * 64 + w.lane];
+#pragma unroll
+    for (int i = 0; i < P::ND; ++i) {
+      const int s = wave + i * P::WV;
+      auto* to = (__attribute__((address_space(3))) void*)(dst + 64 * s);
+      if (64 * s < nc)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_c, to, 16, off[i], at, 0, 0);
+      else if (s < nslot)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_v, to, 16, off[i], at, 0, 0);
+    }
+  };
+  constexpr int NF = P::NF;
+  for (int i = tid; i < nq * NF; i += NT) {                 // visible after the first barrier
+    const int j = i / NF, e = i % NF / S::NG, g = i % S::NG;
+    s_f[i] = fac[32 * j + 16 * g + e];
+  }
+  if (tid < 2 * RC + 1) {   // rowtab: first line minus lowest n3, lowest and highest n3 (from 0)
+    const int32_t* e = rowtab + 3 * tid;
+    s_row[tid] = (int)((unsigned)e[0] << 16) | max(e[2] - e[1] + 1, 0) << 8 | e[1];
+  }
+
+  MfmaSums<RC> acc[NL];
+
+  // one chunk: wait for it, start the next one (after the item's last, the next item's first), add its quads
+  int nx1, nc0, nv0;
+  bool more = false;
+  auto chunk = [&](int rs, int ch, auto q0, auto first, MfmaTranspose<RC>& sm, const uint4* cur, uint4* nxt) {
+    wait_vm<decltype(first)::value ? P::NST : 0>();   // an item's first chunk: its stores came after the loads
+    lds_barrier();   // the chunk has landed; every wave is done with the other buffer
+    const bool wrap = ch + 1 == nch, last = wrap && rs + 1 == nrs;
+    if (last) {
+      it += gridDim.x / 8;
+      more = plane_item(it, nt, ncs / TC, nvs / TV, nx1, nc0, nv0);
+      if (more) {
+        rsrc_c = buffer(psi_c, ncs, nc0 * TC, nx1);
+        rsrc_v = buffer(psi_v, nvs, nv0 * TV, nx1);
+      }
+    }
+    if (!last || more) issue(last ? 0 : wrap ? rs + 1 : rs, wrap ? 0 : ch + 1, nxt);
+    const Lane w = who();
+    const V* rc = (const V*)(cur + w.pc * lb + (w.ql * 4 + w.ti) * lr);
+    const V* rv = (const V*)(cur + nc + pv * lb + (w.ql * 4 + w.ti) * lr);
+    const float* ff = s_f + (4 * (w.lane >> 4) + w.ti) * S::NG + ch * cq * NF;   // 16-lane section = slot
+    const int ne = min(cq, nq - ch * cq);
+    if (ne <= 0) return;
+    // The MFMAs of a quad run beside the folds of the next one, with the operands of the one after in flight.
+    V na[4], nb[4], p[4];
+    auto load = [&](int j) {
+      __builtin_memcpy(na, __builtin_assume_aligned(rv + 4 * j, 16), 4 * sizeof(V));
+      __builtin_memcpy(nb, __builtin_assume_aligned(rc + 4 * j, 16), 4 * sizeof(V));
+      asm volatile("" ::: "memory");   // the reads stay here, a quad ahead of their use
+    };
+    auto factors = [&](int j, float (&f)[S::NG]) {
+#pragma unroll
+      for (int g = 0; g < S::NG; ++g) f[g] = ff[NF * j + g];
+    };
+    auto product = [&] {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) p[k] = cmulc(na[k], nb[k]);
+      // the operands' registers are free: the next reads go out before the MFMAs
+      asm volatile("" : "+v"(p[0].x), "+v"(p[0].y), "+v"(p[1].x), "+v"(p[1].y), "+v"(p[2].x), "+v"(p[2].y), "+v"(p[3].x),
+                   "+v"(p[3].y)::"memory");
+    };
+    load(0);
+    product();
+    load(1);
+    Fold<V> h;
+    int j = 0;
+    if constexpr (decltype(q0)::value) {
+      h = fold_quad0(p);
+      float f[S::NG];
+      factors(0, f);
+      if (ne > 1) product();
+      load(2);
+      sm.clear();
+      sm.add0(h, f);
+      if (ne == 1) return;
+      j = 1;
+    }
+    h = fold_quad(p);
+    auto quad = [&](int j, const Fold<V>& x) {
+      float f[S::NG];
+      factors(j, f);
+      product();
+      load(j + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      const Fold<V> y = fold_quad(p);
+      sm.add(x, f);
+      return y;
+    };
+    // two quads per turn: no copies, half of the address arithmetic
+#pragma unroll 1
+    for (; j + 2 < ne; j += 2) {
+      const Fold<V> g = quad(j, h);
+      h = quad(j + 1, g);
+    }
+    if (j + 1 < ne) h = quad(j++, h);
+    float f[S::NG];
+    factors(j, f);
+    sm.add(h, f);
+  };
+  auto step = [&](int rs, auto first) {
+    constexpr bool kFirst = decltype(first)::value;
+    MfmaTranspose<RC> sm;
+    chunk(rs, 0, std::true_type{}, first, sm, s_u0, s_u1);
+    chunk(rs, 1, std::false_type{}, std::false_type{}, sm, s_u1, s_u0);
+#pragma unroll 1
+    for (int ch = 2; ch < nch; ch += 2) {
+      chunk(rs, ch, std::false_type{}, std::false_type{}, sm, s_u0, s_u1);
+      chunk(rs, ch + 1, std::false_type{}, std::false_type{}, sm, s_u1, s_u0);
+    }
+    const Lane w = who();
+    const float* f2 = s_f + (w.lane & 15) * S::NG + (w.lane >> 4) % S::NG;   // four lanes = slot
+    // slots for quads: afterwards a[q NL + l] is slot l of this lane for quad q
+    if constexpr (QL >= 2) {
+#pragma unroll
+      for (int i = 0; i < N / 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            float x = sm.a[i][k][t], y = sm.a[i + N / 2][k][t];
+            swap32(x, y);
+            sm.a[i][k][t] = x;
+            sm.a[i + N / 2][k][t] = y;
+          }
+    }
+    if constexpr (QL == 4) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < N / 4; ++i)
+#pragma unroll
+          for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              float x = sm.a[h * (N / 2) + i][k][t], y = sm.a[h * (N / 2) + i + N / 4][k][t];
+              swap16(x, y);
+              sm.a[h * (N / 2) + i][k][t] = x;
+              sm.a[h * (N / 2) + i + N / 4][k][t] = y;
+            }
+    }
+#pragma unroll
+    for (int k = 0; k < QL; ++k) {
+      if (kFirst && k == 0)
+#pragma unroll
+        for (int l = 0; l < NL; ++l) acc[l].clear();
+      const int j2 = rs * QL + k;
+      if (j2 < nq) {
+        const float f = f2[NF * j2];
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+          const fold_f32x4 x = sm.a[k * NL + l][0], y = sm.a[k * NL + l][1];
+          const V p[4] = {V{x[0], y[0]}, V{x[1], y[1]}, V{x[2], y[2]}, V{x[3], y[3]}};
+          if (kFirst && k == 0)
+            acc[l].add0(fold_quad0(p), f);
+          else
+            acc[l].add(fold_quad(p), f);
+        }
+      }
+    }
+  };
+  issue(0, 0, s_u0);
+  wait_vm<0>();
+  for (;;) {
+    step(0, std::true_type{});
+#pragma unroll 1
+    for (int rs = 1; rs < nrs; ++rs) step(rs, std::false_type{});
+    const Lane w = who();
+    // Q's lines; every wave issues the same number of stores (lanes out of range: beyond the buffer's bounds)
+    const size_t first = (((size_t)(v0 * TV + pv) * ncs + c0 * TC) * nt + x1) * (size_t)nl;
+    const size_t bytes = min(((size_t)nvs * ncs * nt * nl - first) * sizeof(V), (size_t)0xfffffff0u);
+    const auto rsrc_q = __builtin_amdgcn_make_buffer_rsrc(q + first, 0, (int)(unsigned)bytes, 0x00020000);
+#pragma unroll
+    for (int l = 0; l < NL; l += 2) {
+      const int sp = w.ql * (NL / 2) + l / 2;             // the (C, S) pair of slots
+      const int n3 = 2 * (4 * (sp % S::NG) + w.ti) + sp / S::NG;
+      const int jp = RC + n3, jm = n3 > 0 ? RC - n3 : -1;
+      const unsigned at = (unsigned)(w.pc * nt) * (unsigned)(nl * sizeof(V));
+      auto put = [&](int n2, V c, V s) {
+        const int e = __builtin_amdgcn_readfirstlane(s_row[n2 + RC]);
+        const int lo = e & 255, cnt = e >> 8 & 255, off = (e >> 16) * (int)sizeof(V);
+        store(rsrc_q, (unsigned)(jp - lo) < (unsigned)cnt ? at + off + 8 * jp : 0xfffffff8u, plus_i(c, s));
+        store(rsrc_q, (unsigned)(jm - lo) < (unsigned)cnt ? at + off + 8 * jm : 0xfffffff8u, minus_i(c, s));
+      };
+      put(0, acc[l].c(0), acc[l + 1].c(0));
+#pragma unroll
+      for (int n = 1; n <= RC; ++n) {
+        put(n, plus_i(acc[l].c(n), acc[l].s(n)), plus_i(acc[l + 1].c(n), acc[l + 1].s(n)));
+        put(-n, minus_i(acc[l].c(n), acc[l].s(n)), minus_i(acc[l + 1].c(n), acc[l + 1].s(n)));
+      }
+    }
+    if (!more) break;
+    x1 = nx1;
+    c0 = nc0;
+    v0 = nv0;
+  }
+}
+
+template <int RC, typename P>
+__global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes_mfma(const float2* __restrict__ psi_v,
+                                                                     const float2* __restrict__ psi_c, int nvs,
+                                                                     int ncs, int nt, int nl, int nch, unsigned inv_r,
+                                                                     unsigned inv_b, const int32_t* __restrict__ rowtab,
+                                                                     const float* __restrict__ fac,
+                                                                     float2* __restrict__ q) {
+  planes_mfma<RC, P>(psi_v, psi_c, nvs, ncs, nt, nl, nch, inv_r, inv_b, rowtab, fac, q);
+}
+
+// ---------------------------------------------------------------------------------------------
+// float64, on the vector units: per step and lane one (pair, x2 row), the folded x3 sums of the product
+// -> Z[pair][row][n3] in LDS; then per lane (pair, n3) the folded x2 sums over the quad's four rows,
+// accumulated over the quads in registers.
+//
+// Shape of a workgroup.  HS: waves that share a line's x3 quads (partial sums added in LDS);
 // QS: quads of x2 rows per step; NM: largest grid (the LDS row buffers).
 template <typename T, int RC, int HS_, int QS_, int TV_, int TC_, int NM_, int MINW_>
 struct PlaneShape {
@@ -38,16 +393,11 @@ struct PlaneShape {
   // row buffer: per band its QS quads of rows and one 16-byte unit (an odd stride between bands)
   static constexpr int NU = (TC + TV) * (QS * 4 * (NM + PADE) / PADE + 1);
   static constexpr int NZ = QS * NP * PS;
-  static constexpr size_t lds0 = (size_t)NU * 16 + (size_t)NZ * sizeof(cx<T>);
-  // the MFMA factors of every quad in LDS too, where they fit
-  static constexpr int NF = sizeof(T) == 4 && lds0 + NM / 4 * 256 <= 160 * 1024 ? NM / 4 * 64 : 0;
-  static constexpr size_t lds = lds0 + 4 * NF;
+  static constexpr size_t lds = (size_t)NU * 16 + (size_t)NZ * sizeof(cx<T>);
   static constexpr int NITEM = NP * K;
   static constexpr int IPL = (NITEM + NT - 1) / NT;
   static_assert(lds <= 160 * 1024, "planes workgroup exceeds the LDS");
 };
-
-template <typename T, int RC> using Sums = std::conditional_t<std::is_same<T, float>::value, MfmaSums<RC>, LineSums<T, RC>>;
 
 template <typename T, int RC, typename P>
 __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __restrict__ psi_v,
@@ -55,24 +405,15 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
                                                                 int nt, int nl, const int32_t* __restrict__ rowtab,
                                                                 const T* __restrict__ fac, cx<T>* __restrict__ q) {
   using V = cx<T>;
-  constexpr bool kMfma = std::is_same<T, float>::value;
   constexpr int K = P::K, NT = P::NT, TV = P::TV, TC = P::TC, HS = P::HS, QS = P::QS, PS = P::PS;
   constexpr int EPU = P::PADE;   // complex values per 16-byte unit
   __shared__ __align__(16) uint4 s_u[P::NU];   // [band: TC columns, TV valence][quad][t][row], band stride odd
   __shared__ __align__(16) V s_z[P::NZ];   // [quad][pair][t][n3]
-  __shared__ float s_f[P::NF > 0 ? P::NF : 1];
 
-  // The workgroups of one x1 plane read the same bands, so each XCD (workgroup b runs on XCD
-  // b mod 8) takes a contiguous run of the plane-major order and its L2 holds about one plane.
-  const int nbc = ncs / TC, nbv = nvs / TV;
-  const int total = nt * nbc * nbv;
-  const int per = (total + 7) / 8;
-  const int item = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if ((int)(blockIdx.x / 8) >= per || item >= total) return;
-  const int x1 = item / (nbc * nbv);
-  const int pb = item % (nbc * nbv);
-  const int c0 = (pb % nbc) * TC;
-  const int v0 = (pb / nbc) * TV;
+  int x1, c0, v0;
+  if (!plane_item(blockIdx.x / 8, nt, ncs / TC, nvs / TV, x1, c0, v0)) return;
+  c0 *= TC;
+  v0 *= TV;
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -113,19 +454,9 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
       ch += NT / 64;
     }
   };
-  // factors of quad j: one register per lane (MFMA blocks), or a wave-uniform row
-  if constexpr (P::NF > 0)
-    for (int i = tid; i < nq * 64; i += NT) s_f[i] = fac[i];   // visible after the first step's barrier
-  auto factors = [&](int j) {
-    if constexpr (P::NF > 0)
-      return s_f[64 * j + lane];
-    else if constexpr (kMfma)
-      return fac[64 * j + lane];
-    else
-      return fac + (size_t)j * (2 * RC + 2);
-  };
+  auto factors = [&](int j) { return fac + (size_t)j * (2 * RC + 2); };   // wave-uniform row of quad j
 
-  Sums<T, RC> qa[P::IPL];
+  LineSums<T, RC> qa[P::IPL];
 #pragma unroll
   for (int r = 0; r < P::IPL; ++r) qa[r].clear();
 
@@ -143,7 +474,7 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
     wait_vm<0>();
     lds_barrier();   // the step's rows have landed; stage 2 of the previous step is done with Z
     const bool live = QS == 1 || st * QS + qs < nq;
-    Sums<T, RC> sm;
+    LineSums<T, RC> sm;
     if (live) {
       sm.clear();
       // the operands of the next quad are read while the current one is summed
@@ -299,38 +630,45 @@ template <typename T, int RC, typename P>
 hipError_t run_shape(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q, hipStream_t st) {
   if (nvs % P::TV != 0 || ncs % P::TC != 0 || g.nt > P::NM) return hipErrorInvalidValue;
   const int total = g.nt * (nvs / P::TV) * (ncs / P::TC);
-  const T* fac = std::is_same<T, float>::value ? (const T*)g.d_amat : (const T*)g.d_fac64;
   k_pair_planes<T, RC, P><<<(total + 7) / 8 * 8, P::NT, 0, st>>>((const cx<T>*)psi_v, (const cx<T>*)psi_c, nvs, ncs,
-                                                                 g.nt, g.nl, g.d_rowtab, fac, (cx<T>*)q);
+                                                                 g.nt, g.nl, g.d_rowtab, (const T*)g.d_fac64,
+                                                                 (cx<T>*)q);
   return hipGetLastError();
 }
 
-// Shape of the planes kernel, per 32k-pair launch on one MI355X (before: the radix-split kernels
-// on the stated grid).  float32 up to RC = 7: with a grid of at most 52 points two workgroups of
-// eight waves share a CU (four waves per SIMD, form 2): RC 7 on 44^3 2.6 ms, 3.0 for form 1, 4.0 for
-// form 3 (72^3 before: 8.7); on larger grids its rows would not leave room for a second workgroup,
-// and the 64 pairs of form 1, with a whole line per lane, take over.  From RC = 8 the 64 accumulators
-// per (pair, n3) item allow two waves per SIMD and one item for half the threads only with 32
-// pairs per eight waves: RC 9 on 60^3 10.3 ms (96^3 before: 23), RC 12 on 80^3 22 ms (128^3
-// before: 61).  float64: four waves, half a line per lane; RC 7 on 44^3 4.7 ms (72^3 before: 17.4),
-// RC 9 on 60^3 20.3 (96^3 before: 68; one wave per SIMD beyond RC 7).
+template <int RC, typename P>
+hipError_t run_mfma(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q, hipStream_t st) {
+  const int nq = g.nt / 4, nch = P::chunks(nq);
+  if (nvs % P::TV != 0 || ncs % P::TC != 0 || nq > P::NQM || nch < 1) return hipErrorInvalidValue;
+  const int total = g.nt * (nvs / P::TV) * (ncs / P::TC);
+  const int cq = (nq + nch - 1) / nch;
+  auto inv = [](int d) { return (unsigned)((0x100000000ull + d - 1) / d); };   // u / d = mulhi(u, inv), u < 2^16
+  // a fixed grid of one workgroup per CU where only one fits (the next item's rows load under the end of the
+  // last one: 16.3 ms against 17.2); where several share a CU, one workgroup per item is as fast
+  const int all = (total + 7) / 8 * 8;
+  const int blocks = P::WV == 8 ? std::min(all, 256) : all;
+  k_pair_planes_mfma<RC, P><<<blocks, P::NT, 0, st>>>((const float2*)psi_v, (const float2*)psi_c, nvs,
+                                                                   ncs, g.nt, g.nl, nch, inv(P::row_units(cq)),
+                                                                   inv(P::band_units(cq)), g.d_rowtab, g.d_amat,
+                                                                   (float2*)q);
+  return hipGetLastError();
+}
+
+// Shapes, per 32k-pair launch on one MI355X (before: both sums' partial results exchanged through LDS).
+// float32, up to RC = 7: two row quads per wave, 64 accumulators, three waves per SIMD, workgroups of four
+// waves: RC 7 on 44^3 2.06 ms (before 2.6; with one row quad per wave and two waves per SIMD 2.3, with
+// workgroups of eight waves 2.5).  From RC = 8 a slot pair has twice the accumulators: four row quads per
+// wave, two waves per SIMD, one workgroup of eight waves per CU over a fixed grid: RC 9 on 60^3 8.1 ms
+// (before 10.3; workgroups of four waves 8.8), RC 12 on 80^3 16.2 ms (before 22; 17.9).
+// float64: four waves, half a line per lane; RC 7 on 44^3 4.7 ms, RC 9 on 60^3 20.3 (one wave per SIMD
+// beyond RC 7).
 template <typename T, int RC>
-hipError_t run_planes(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q, int form,
-                      hipStream_t st) {
+hipError_t run_planes(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q, hipStream_t st) {
   if constexpr (std::is_same<T, float>::value) {
-    if constexpr (RC <= 7) {
-      if (g.nt <= 52 && form != 1 && form != 3)
-        return run_shape<T, RC, PlaneShape<T, RC, 2, 2, 4, 8, 52, 4>>(g, psi_v, psi_c, nvs, ncs, q, st);
-      if (form != 3 && ncs % 16 == 0) {
-        if (g.nt <= 68)
-          return run_shape<T, RC, PlaneShape<T, RC, 1, 1, 4, 16, 68, 2>>(g, psi_v, psi_c, nvs, ncs, q, st);
-        return run_shape<T, RC, PlaneShape<T, RC, 1, 1, 4, 16, 128, 1>>(g, psi_v, psi_c, nvs, ncs, q, st);
-      }
-    }
-    if constexpr (RC == 15) {   // the two-quad buffers of 128 points would not fit the LDS
-      if (g.nt > 124) return run_shape<T, RC, PlaneShape<T, RC, 2, 1, 4, 8, 128, 1>>(g, psi_v, psi_c, nvs, ncs, q, st);
-    }
-    return run_shape<T, RC, PlaneShape<T, RC, 2, 2, 4, 8, RC == 15 ? 124 : 128, 2>>(g, psi_v, psi_c, nvs, ncs, q, st);
+    if constexpr (RC <= 7)
+      return run_mfma<RC, MfmaShape<RC, 2, 4, 4, 8, 1280, 3>>(g, psi_v, psi_c, nvs, ncs, q, st);
+    else
+      return run_mfma<RC, MfmaShape<RC, 4, 8, 4, 8, 4032, 2>>(g, psi_v, psi_c, nvs, ncs, q, st);
   } else {
     if constexpr (RC <= 7) {
       if (g.nt <= 64)
@@ -354,11 +692,11 @@ hipError_t run_finish(const Geom& g, const void* q, int npair, void* m, hipStrea
 }  // namespace
 
 template <typename T>
-hipError_t launch_pair_planes(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q, int form,
+hipError_t launch_pair_planes(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q,
                               hipStream_t st) {
   switch (g.rchi) {
 #define X(rc) \
-  case rc: return run_planes<T, rc>(g, psi_v, psi_c, nvs, ncs, q, form, st);
+  case rc: return run_planes<T, rc>(g, psi_v, psi_c, nvs, ncs, q, st);
     GW_RC_CASES(X)
 #undef X
   }
@@ -376,10 +714,8 @@ hipError_t launch_pair_finish(const Geom& g, const void* q, int npair, void* m, 
   return hipErrorInvalidValue;
 }
 
-template hipError_t launch_pair_planes<double>(const Geom&, const void*, const void*, int, int, void*, int,
-                                               hipStream_t);
-template hipError_t launch_pair_planes<float>(const Geom&, const void*, const void*, int, int, void*, int,
-                                              hipStream_t);
+template hipError_t launch_pair_planes<double>(const Geom&, const void*, const void*, int, int, void*, hipStream_t);
+template hipError_t launch_pair_planes<float>(const Geom&, const void*, const void*, int, int, void*, hipStream_t);
 template hipError_t launch_pair_finish<double>(const Geom&, const void*, int, void*, hipStream_t);
 template hipError_t launch_pair_finish<float>(const Geom&, const void*, int, void*, hipStream_t);
 
