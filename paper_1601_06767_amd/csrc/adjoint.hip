@@ -10,6 +10,12 @@
 // with the row dot sum_G conj(M[p][G]) Y[p][G] over the tile's 64 G; the per-tile
 // partial sums are reduced in float64 in fixed order by k_adjoint_pairs.
 // k_adjoint_bf16x3: the same product for the split-bf16 mode on bf16 MFMA, 128 x 128 tiles.
+//
+// Without broadening the weights are real and only Re s_p enters: Re s_p = Re m_p^H L m_p with L the lower
+// triangle of chibar + chibar^H, its diagonal halved, so a tile of G needs the G' up to its end only: half of
+// the products (96^3 split-bf16, 32k pairs, NG 4000: 9.0 -> 5.2 ms).  Where the coefficient gradients follow,
+// their full product M (chibar + chibar^H)^T gives Re s_p as well (k_weight_dot): one product where three
+// were formed (72^3, 16k pairs, NG 2000: 28 -> 10 ms).
 #include <algorithm>
 #include <type_traits>
 
@@ -58,11 +64,62 @@ __device__ __forceinline__ void adj_tile(int t, int npt, int ntg, int* pt, int* 
   *tg = cb * BG + w / nr;
 }
 
+// out = chibar + chibar^H (rows by 32 x 32 tiles, the transposed one through LDS); lower: its lower triangle
+// with the diagonal halved, zero above; ldo x ldo, zero beyond ng
+__global__ __launch_bounds__(256) void k_hermitian(const double2* __restrict__ x, int ng, int lower, int ldo,
+                                                   double2* __restrict__ out) {
+  __shared__ double2 s[32][33];
+  const int nt = (ldo + 31) / 32;
+  const int r0 = (int)(blockIdx.x / nt) * 32, c0 = (int)(blockIdx.x % nt) * 32;
+  const int tx = threadIdx.x % 32, ty = threadIdx.x / 32;
+  const bool above = lower && c0 > r0;
+  if (!above)
+    for (int i = ty; i < 32; i += 8)
+      s[i][tx] = c0 + i < ng && r0 + tx < ng ? x[(size_t)(c0 + i) * ng + r0 + tx] : double2{0.0, 0.0};
+  __syncthreads();
+  for (int i = ty; i < 32; i += 8) {
+    const int r = r0 + i, c = c0 + tx;
+    if (r >= ldo || c >= ldo) continue;
+    double2 y{0.0, 0.0};
+    if (!above && !(lower && c > r) && r < ng && c < ng) {
+      const double2 a = x[(size_t)r * ng + c], b = s[tx][i];
+      y = r == c ? double2{lower ? a.x : 2.0 * a.x, 0.0} : double2{a.x + b.x, a.y - b.y};
+    }
+    out[(size_t)r * ldo + c] = y;
+  }
+}
+
+// mbar[p][G] (+)= w_p y[p][G] and part[p] = 1/2 Re sum_G conj(m[p][G]) y[p][G]; zero in the padding
+__global__ __launch_bounds__(256) void k_weight_dot(const double2* __restrict__ m, const double2* __restrict__ y,
+                                                    const double* __restrict__ w, int ng, int ngp, int add,
+                                                    double2* __restrict__ mbar, double2* __restrict__ part) {
+  __shared__ double red[4];
+  const size_t p = blockIdx.x, row = p * ngp;
+  const double wp = w[p];
+  double d = 0.0;
+  for (int g = threadIdx.x; g < ngp; g += 256) {
+    double2 o = add ? mbar[row + g] : double2{0.0, 0.0};
+    if (g < ng) {
+      const double2 a = m[row + g], b = y[row + g];
+      d += a.x * b.x + a.y * b.y;
+      o.x = fma(wp, b.x, o.x);
+      o.y = fma(wp, b.y, o.y);
+    }
+    mbar[row + g] = o;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) d += __shfl_xor(d, o, 64);
+  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = d;
+  __syncthreads();
+  if (threadIdx.x == 0) part[p] = double2{0.5 * ((red[0] + red[1]) + (red[2] + red[3])), 0.0};
+}
+
 constexpr int AT = 64, AK = 16;
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_adjoint(const cx<T>* __restrict__ m, int npair, int ng, int ngp,
-                                                 const double2* __restrict__ gbar, double2* __restrict__ part) {
+                                                 const double2* __restrict__ gbar, int lower,
+                                                 double2* __restrict__ part) {
   using V = cx<T>;
   using A4 = typename AMfma<T>::acc;
   __shared__ V sA[AK][AT + 1];   // M[p0 + i][G' = k]
@@ -86,7 +143,8 @@ __global__ __launch_bounds__(256) void k_adjoint(const cx<T>* __restrict__ m, in
       cre[i][j] = A4{0, 0, 0, 0};
       cim[i][j] = A4{0, 0, 0, 0};
     }
-  for (int k0 = 0; k0 < ng; k0 += AK) {
+  const int kend = lower ? min(ng, q0 + AT) : ng;   // lower triangle: zero from there on
+  for (int k0 = 0; k0 < kend; k0 += AK) {
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < (AK * AT) / 256; ++r) {
@@ -183,28 +241,43 @@ constexpr int BMI = 4, BNJ = 2;
 // 96 bf16 = hi [re | im | -im] then lo [re | im | -im] (zero beyond ng), so that the tiles
 // stage chibar with plain 16-byte copies instead of converting it once per pair tile.
 constexpr int GSPLIT = 96;   // bf16 per (row, 16-G' block)
-__global__ void k_split_gbar(const double2* __restrict__ gbar, int ng, int nkb, unsigned short* __restrict__ out) {
-  const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;   // (row, block, G' in block)
-  if (e >= (size_t)ng * nkb * 16) return;
-  const int i = (int)(e % 16);
-  const size_t rb = e / 16;   // row * nkb + kb
-  const int kb = (int)(rb % nkb), row = (int)(rb / nkb);
-  const int col = kb * 16 + i;
-  float re = 0.f, im = 0.f;
-  if (col < ng) {
-    const double2 x = gbar[(size_t)row * ng + col];
-    re = (float)x.x;
-    im = (float)x.y;
+// lower: the image is that of the lower triangle of chibar + chibar^H, its diagonal halved (see above); its
+// sums are formed in float64.  A workgroup takes 64 rows of a block; the transposed 16 x 64 piece comes
+// through LDS.
+__global__ __launch_bounds__(256) void k_split_gbar(const double2* __restrict__ gbar, int ng, int nkb, int lower,
+                                                    unsigned short* __restrict__ out) {
+  __shared__ double2 s_t[16][65];
+  const int kb = (int)(blockIdx.x % nkb), r0 = (int)(blockIdx.x / nkb) * 64;
+  const bool above = lower && kb * 16 > r0 + 63;
+  if (lower && !above)
+    for (int e = threadIdx.x; e < 16 * 64; e += 256) {
+      const int c = kb * 16 + e / 64, r = r0 + e % 64;
+      s_t[e / 64][e % 64] = c < ng && r < ng ? gbar[(size_t)c * ng + r] : double2{0.0, 0.0};
+    }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 64 * 16; e += 256) {
+    const int i = e % 16, row = r0 + e / 16, col = kb * 16 + i;
+    if (row >= ng) continue;
+    float re = 0.f, im = 0.f;
+    if (col < ng && !(lower && col > row)) {
+      double2 x = gbar[(size_t)row * ng + col];
+      if (lower) {
+        const double2 y = s_t[i][e / 16];
+        x = row == col ? double2{x.x, 0.0} : double2{x.x + y.x, x.y - y.y};
+      }
+      re = (float)x.x;
+      im = (float)x.y;
+    }
+    const unsigned short rh = bf16_rne(re), ih = bf16_rne(im);
+    const unsigned short rl = bf16_rne(re - bf16_val(rh)), il = bf16_rne(im - bf16_val(ih));
+    unsigned short* o = out + ((size_t)row * nkb + kb) * GSPLIT;
+    o[i] = rh;
+    o[16 + i] = ih;
+    o[32 + i] = ih ^ 0x8000;
+    o[48 + i] = rl;
+    o[64 + i] = il;
+    o[80 + i] = il ^ 0x8000;
   }
-  const unsigned short rh = bf16_rne(re), ih = bf16_rne(im);
-  const unsigned short rl = bf16_rne(re - bf16_val(rh)), il = bf16_rne(im - bf16_val(ih));
-  unsigned short* o = out + rb * GSPLIT;
-  o[i] = rh;
-  o[16 + i] = ih;
-  o[32 + i] = ih ^ 0x8000;
-  o[48 + i] = rl;
-  o[64 + i] = il;
-  o[80 + i] = il ^ 0x8000;
 }
 
 // The pair densities split the same way, once per chunk: for pair row p and block kb of 16 G',
@@ -252,7 +325,7 @@ constexpr int UPL = UST / 512;                            // units per lane per 
 static_assert(UPL * 512 == UST && UM % 64 == 0, "stage units must split into whole wave instructions");
 __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict__ m, int npair, int ng, int ngp,
                                                            const uint4* __restrict__ msplit,
-                                                           const uint4* __restrict__ gsplit,
+                                                           const uint4* __restrict__ gsplit, int lower,
                                                            double2* __restrict__ part) {
   __shared__ __align__(16) uint4 sa[UST];
   __shared__ __align__(16) uint4 sb[UST];
@@ -272,6 +345,7 @@ __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict
   const int wr = wave / 4, wc = wave % 4;
   const int li = lane & 15, lg = lane >> 4;
   const int nkb = (ng + BKS - 1) / BKS;
+  const int nke = lower ? min(nkb, (q0 + BT) / BKS) : nkb;   // stages: a lower triangle ends with its tile
 
   // this lane's source of unit 64 (8 i + wave) + lane, for every stage (block kb adds
   // 8 kb or 12 kb pieces; the block of 64 units, and so the operand, is wave-uniform)
@@ -316,7 +390,7 @@ __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict
     // the end: the last stage again, into a buffer not read), so the wait count is a constant.
     wait_vm<UPL>();
     lds_barrier();
-    issue(min(kb + 2, nkb - 1), next);
+    issue(min(kb + 2, nke - 1), next);
     const uint4* sm = cur;
     const uint4* sg = cur + UM;
     bf16x8 xh[BMI], xl[BMI], reh[BNJ], rel[BNJ], imh[BNJ], iml[BNJ];
@@ -348,18 +422,18 @@ __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict
       }
   };
   issue(0, sa);
-  issue(min(1, nkb - 1), sb);
+  issue(min(1, nke - 1), sb);
   // Whole triples in the loop and the remainder after it: with the second and third stages
   // conditional, the compiler's wait tracking would merge paths on which another buffer's loads
   // are the newest and wait for every load before the LDS reads.
   int kb = 0;
-  for (; kb + 3 <= nkb; kb += 3) {
+  for (; kb + 3 <= nke; kb += 3) {
     stage(kb, sa, sc);
     stage(kb + 1, sb, sa);
     stage(kb + 2, sc, sb);
   }
-  if (kb < nkb) stage(kb, sa, sc);
-  if (kb + 1 < nkb) stage(kb + 1, sb, sa);
+  if (kb < nke) stage(kb, sa, sc);
+  if (kb + 1 < nke) stage(kb + 1, sb, sa);
   wait_vm<0>();   // no direct load may still be writing LDS when the epilogue's barrier passes
   // epilogue: per pair row, sum over this tile's G of conj(M[p][G]) Y[p][G]; result rows of
   // the bf16 16x16x32 MFMA are 4 (lane / 16) + r, columns lane % 16
@@ -491,28 +565,40 @@ hipError_t launch_split_m(const void* m, int npair, int ng, int ngp, void* mspli
 }
 
 hipError_t launch_adjoint_bf16x3(const void* m, const void* msplit, int npair, int ng, int ngp, const double2* gbar,
-                                 void* gsplit, double2* part, hipStream_t st) {
+                                 bool lower, void* gsplit, double2* part, hipStream_t st) {
   if (ngp % BT != 0) return hipErrorInvalidValue;
   const int nkb = (ng + BKS - 1) / BKS;
-  const size_t ne = (size_t)ng * nkb * 16;
-  k_split_gbar<<<(unsigned)((ne + 255) / 256), 256, 0, st>>>(gbar, ng, nkb, (unsigned short*)gsplit);
+  k_split_gbar<<<(unsigned)((ng + 63) / 64 * nkb), 256, 0, st>>>(gbar, ng, nkb, lower ? 1 : 0, (unsigned short*)gsplit);
   const int ntg = ngp / BT;
   const int nb = ((npair + BT - 1) / BT) * ntg;
-  k_adjoint_bf16x3<<<(nb + 7) / 8 * 8, 512, 0, st>>>((const float2*)m, npair, ng, ngp, (const uint4*)msplit, (const uint4*)gsplit,
-                                       part);
+  k_adjoint_bf16x3<<<(nb + 7) / 8 * 8, 512, 0, st>>>((const float2*)m, npair, ng, ngp, (const uint4*)msplit,
+                                                     (const uint4*)gsplit, lower ? 1 : 0, part);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_adjoint(const void* m, int npair, int ng, int ngp, const double2* gbar, double2* part,
+hipError_t launch_adjoint(const void* m, int npair, int ng, int ngp, const double2* gbar, bool lower, double2* part,
                           hipStream_t st) {
   const int ntg = ngp / AT;
   const int nb = ((npair + AT - 1) / AT) * ntg;
-  k_adjoint<T><<<(nb + 7) / 8 * 8, 256, 0, st>>>((const cx<T>*)m, npair, ng, ngp, gbar, part);
+  k_adjoint<T><<<(nb + 7) / 8 * 8, 256, 0, st>>>((const cx<T>*)m, npair, ng, ngp, gbar, lower ? 1 : 0, part);
   return hipGetLastError();
 }
-template hipError_t launch_adjoint<double>(const void*, int, int, int, const double2*, double2*, hipStream_t);
-template hipError_t launch_adjoint<float>(const void*, int, int, int, const double2*, double2*, hipStream_t);
+template hipError_t launch_adjoint<double>(const void*, int, int, int, const double2*, bool, double2*, hipStream_t);
+template hipError_t launch_adjoint<float>(const void*, int, int, int, const double2*, bool, double2*, hipStream_t);
+
+hipError_t launch_hermitian(const double2* gbar, int ng, bool lower, int ldo, double2* out, hipStream_t st) {
+  const unsigned nt = (unsigned)(ldo + 31) / 32;
+  k_hermitian<<<nt * nt, 256, 0, st>>>(gbar, ng, lower ? 1 : 0, ldo, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_weight_dot(const void* m, const void* y, const double* w, int npair, int ng, int ngp, bool add,
+                             void* mbar, double2* part, hipStream_t st) {
+  k_weight_dot<<<npair, 256, 0, st>>>((const double2*)m, (const double2*)y, w, ng, ngp, add ? 1 : 0, (double2*)mbar,
+                                      part);
+  return hipGetLastError();
+}
 
 hipError_t launch_adjoint_pairs(const double2* part, int ntg, const double* e_v, int nv, int nvs, const double* e_col,
                                 const double* n_col, int c0, int ncol, int cc, double omega, double delta, double* dx,

@@ -67,6 +67,7 @@ struct Layout {
   size_t off_msplit = 0;   // and the chunk's pair densities, split the same way
   // coefficient gradients (backward, float64): mbar and a weighted copy of M per chunk,
   // ubar of the chunk's columns and of the valence slots, column gradients of a chunk
+  size_t off_herm = 0;     // backward without broadening: chibar + chibar^H
   size_t off_mbar = 0, off_atmp = 0, off_ubarc = 0, off_ubarv = 0, off_cbar = 0;
   int max_cc = 0;
 };
@@ -159,6 +160,11 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
   L.off_q = take(max_q);
   if (backward) {
     L.off_part = take(max_part);
+    if (!complex_w && L.mode != 2) {
+      size_t hs = 0;
+      for (const auto& q : L.pp) hs = std::max(hs, (size_t)q.p->geom->g.ngp * q.p->geom->g.ngp * sizeof(double2));
+      L.off_herm = take(hs);
+    }
     if (L.mode == 2) {
       size_t gs = 0;
       size_t ms = 0;
@@ -429,14 +435,11 @@ gw_status enqueue_build_all(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob
   return GW_OK;
 }
 
-// Coefficient gradients of one conduction chunk (float64; M of the chunk in the
-// workspace): mbar = sum_w [conj(w) chi0bar m + w chi0bar^H m], its transpose through the
-// finish stage into the Q buffer, then the column gradients of the chunk (added into gcc
-// through col_band) and, with want_v, the chunk's share of ubar_v.
-gw_status coef_grad_chunk(gw_ctx* ctx, const Layout& L, const ProbPlan& q, const Geom& g, const double* omega,
-                          int nomega, double delta, const double2* gbar, int c0, char* ws, double2* gcc, bool want_v) {
+// mbar of one conduction chunk (float64; M of the chunk in the workspace) with broadening:
+// sum_w [conj(w) chi0bar m + w chi0bar^H m]
+gw_status mbar_chunk(gw_ctx* ctx, const Layout& L, const ProbPlan& q, const Geom& g, const double* omega, int nomega,
+                     double delta, const double2* gbar, int c0, char* ws) {
   const gw_chi0_problem& p = *q.p;
-  const size_t npts = g.band_elems(true);
   double* w = (double*)(ws + q.off_w);
   GW_HIP(ctx, gw::launch_fill_c128(ws + L.off_mbar, (size_t)q.npair * g.ngp, ctx->stream));
   for (int iw = 0; iw < nomega; ++iw) {
@@ -454,6 +457,34 @@ gw_status coef_grad_chunk(gw_ctx* ctx, const Layout& L, const ProbPlan& q, const
                                     gw::kOpN, gb, g.ng, gw::kOpConj, double2{1.0, 0.0}, (double2*)(ws + L.off_mbar),
                                     g.ngp, ctx->stream));
   }
+  return GW_OK;
+}
+
+// The same of one frequency without broadening, where w is real: y = M (chi0bar + chi0bar^H)^T gives both
+// mbar (+)= w y and Re s_p (part, one value per pair): one product instead of three.
+gw_status mbar_real(gw_ctx* ctx, const Layout& L, const ProbPlan& q, const Geom& g, double omega, const double2* gb,
+                    int c0, char* ws, bool add, double2* part) {
+  const gw_chi0_problem& p = *q.p;
+  double* w = (double*)(ws + q.off_w);
+  double2* herm = (double2*)(ws + L.off_herm);
+  GW_HIP(ctx, gw::launch_weights(p.e_v, 0, p.nv, q.nvs, p.e_col, p.n_col, c0, p.ncol, q.cc, omega, 0.0, 1, w,
+                                 ctx->stream));
+  GW_HIP(ctx, gw::launch_hermitian(gb, g.ng, false, g.ngp, herm, ctx->stream));
+  GW_HIP(ctx, gw::launch_zgemm_op(q.npair, g.ngp, (int)round_up(g.ng, 16), double2{1.0, 0.0},
+                                  (const double2*)(ws + q.off_m), g.ngp, gw::kOpN, herm, g.ngp, gw::kOpT, double2{0.0, 0.0}, (double2*)(ws + L.off_atmp), g.ngp,
+                                  ctx->stream));
+  GW_HIP(ctx, gw::launch_weight_dot(ws + q.off_m, ws + L.off_atmp, w, q.npair, g.ng, g.ngp, add, ws + L.off_mbar, part,
+                                    ctx->stream));
+  return GW_OK;
+}
+
+// Coefficient gradients of one conduction chunk from its mbar: the transpose through the finish stage into
+// the Q buffer, then the column gradients of the chunk (added into gcc through col_band) and, with want_v,
+// the chunk's share of ubar_v.
+gw_status coef_grad_chunk(gw_ctx* ctx, const Layout& L, const ProbPlan& q, const Geom& g, int c0, char* ws,
+                          double2* gcc, bool want_v) {
+  const gw_chi0_problem& p = *q.p;
+  const size_t npts = g.band_elems(true);
   GW_HIP(ctx, gw::launch_qbar(g, ws + L.off_mbar, q.npair, ws + L.off_q, ctx->stream));
   if (gcc) {
     GW_HIP(ctx, gw::launch_ubar(g, ws + L.off_q, ws + q.off_psiv, q.nvs, q.cc, true, ws + L.off_ubarc, ctx->stream));
@@ -660,20 +691,35 @@ gw_status backward_entry(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, i
       GW_HIP(ctx, gw::launch_fill_f64(dn, q.npair, 0.0, ctx->stream));
       if (L.mode == 2)
         GW_HIP(ctx, gw::launch_split_m(ws + q.off_m, q.npair, g.ng, g.ngp, ws + L.off_msplit, ctx->stream));
+      const bool real_w = !(delta > 0.0);
       for (int iw = 0; iw < nomega; ++iw) {
         const double2* gb = (const double2*)gin + (size_t)iw * g.ng * g.ng;
-        hipError_t e =
-            L.fp64        ? gw::launch_adjoint<double>(ws + q.off_m, q.npair, g.ng, g.ngp, gb, part, ctx->stream)
-            : L.mode == 2 ? gw::launch_adjoint_bf16x3(ws + q.off_m, ws + L.off_msplit, q.npair, g.ng, g.ngp, gb,
-                                                      ws + L.off_gsplit, part, ctx->stream)
-                          : gw::launch_adjoint<float>(ws + q.off_m, q.npair, g.ng, g.ngp, gb, part, ctx->stream);
-        GW_HIP(ctx, e);
-        GW_HIP(ctx, gw::launch_adjoint_pairs(part, g.ngp / gw::adjoint_tile(L.mode), p.e_v, p.nv, q.nvs, p.e_col,
-                                             p.n_col, c0, p.ncol, q.cc, omega[iw], delta, dx, dn, ctx->stream));
+        int ntg = g.ngp / gw::adjoint_tile(L.mode);
+        if (real_w && want_coef) {
+          s = mbar_real(ctx, L, q, g, omega[iw], gb, c0, ws, iw > 0, part);
+          if (s != GW_OK) return s;
+          ntg = 1;
+        } else if (L.mode == 2) {
+          GW_HIP(ctx, gw::launch_adjoint_bf16x3(ws + q.off_m, ws + L.off_msplit, q.npair, g.ng, g.ngp, gb, real_w,
+                                                ws + L.off_gsplit, part, ctx->stream));
+        } else {
+          if (real_w) {
+            GW_HIP(ctx, gw::launch_hermitian(gb, g.ng, true, g.ng, (double2*)(ws + L.off_herm), ctx->stream));
+            gb = (const double2*)(ws + L.off_herm);
+          }
+          GW_HIP(ctx, L.fp64 ? gw::launch_adjoint<double>(ws + q.off_m, q.npair, g.ng, g.ngp, gb, real_w, part, ctx->stream)
+                             : gw::launch_adjoint<float>(ws + q.off_m, q.npair, g.ng, g.ngp, gb, real_w, part, ctx->stream));
+        }
+        GW_HIP(ctx, gw::launch_adjoint_pairs(part, ntg, p.e_v, p.nv, q.nvs, p.e_col, p.n_col, c0, p.ncol, q.cc,
+                                             omega[iw], delta, dx, dn, ctx->stream));
       }
       GW_HIP(ctx, gw::launch_adjoint_reduce(dx, dn, p.nv, q.cc, c0, p.ncol, gev, gec, gn, ctx->stream));
+      if (want_coef && !real_w) {
+        s = mbar_chunk(ctx, L, q, g, omega, nomega, delta, (const double2*)gin, c0, ws);
+        if (s != GW_OK) return s;
+      }
       if (want_coef) {
-        s = coef_grad_chunk(ctx, L, q, g, omega, nomega, delta, (const double2*)gin, c0, ws, gcc, gcv != nullptr);
+        s = coef_grad_chunk(ctx, L, q, g, c0, ws, gcc, gcv != nullptr);
         if (s != GW_OK) return s;
       }
     }

@@ -271,7 +271,7 @@ hipError_t launch_flag_clear(int* flag, hipStream_t st);
 size_t adjoint_partial_bytes(int npair, int ngp);   // enough for every tile width
 int adjoint_tile(int mode);                          // G per partial sum in this mode (64 or 128)
 template <typename T>
-hipError_t launch_adjoint(const void* m, int npair, int ng, int ngp, const double2* gbar, double2* part,
+hipError_t launch_adjoint(const void* m, int npair, int ng, int ngp, const double2* gbar, bool lower, double2* part,
                           hipStream_t st);
 // split-bf16 x3 form over float pair densities (ngp a multiple of 128): msplit holds the pair
 // densities split into bf16 row images (m_split_bytes(npair, ng), written by launch_split_m once
@@ -280,7 +280,14 @@ size_t gbar_split_bytes(int ng);
 size_t m_split_bytes(int npair, int ng);
 hipError_t launch_split_m(const void* m, int npair, int ng, int ngp, void* msplit, hipStream_t st);
 hipError_t launch_adjoint_bf16x3(const void* m, const void* msplit, int npair, int ng, int ngp, const double2* gbar,
-                                 void* gsplit, double2* part, hipStream_t st);
+                                 bool lower, void* gsplit, double2* part, hipStream_t st);
+// Without broadening only Re s_p enters: lower = true computes it from the lower triangle of chibar + chibar^H
+// with the diagonal halved (launch_adjoint takes that matrix, written by launch_hermitian; the split-bf16
+// form takes chibar itself).  out: ldo x ldo, zero beyond ng.
+hipError_t launch_hermitian(const double2* gbar, int ng, bool lower, int ldo, double2* out, hipStream_t st);
+// mbar = w y (added with add) and part[p] = 1/2 Re sum_G conj(m) y, for y = m (chibar + chibar^H)^T
+hipError_t launch_weight_dot(const void* m, const void* y, const double* w, int npair, int ng, int ngp, bool add,
+                             void* mbar, double2* part, hipStream_t st);
 // ntg = ngp / adjoint_tile(mode) partial sums per pair
 hipError_t launch_adjoint_pairs(const double2* part, int ntg, const double* e_v, int nv, int nvs, const double* e_col,
                                 const double* n_col, int c0, int ncol, int cc, double omega, double delta, double* dx,
