@@ -880,7 +880,7 @@ gw_status gw_sigma_coh_static(gw_ctx* ctx, const gw_chi0_problem* prob, const do
     s = pair_block(ctx, L, q, ws);
     if (s != GW_OK) return s;
     // Z = conj(M) A^T over the padded sphere (zero rows and columns beyond ng)
-    GW_HIP(ctx, gw::launch_zgemm_op(q.npair, g.ngp, g.ngp, double2{1.0, 0.0}, (const double2*)(ws + q.off_m), g.ngp,
+    GW_HIP(ctx, gw::launch_zgemm_op(q.npair, g.ngp, (int)round_up(g.ng, 16), double2{1.0, 0.0}, (const double2*)(ws + q.off_m), g.ngp,
                                     gw::kOpConj, (const double2*)(ws + c.off_a), g.ngp, gw::kOpN, double2{0.0, 0.0},
                                     (double2*)(ws + c.off_z), g.ngp, ctx->stream));
     const int nvalid = std::min(q.cc, p.ncol - c0);
