@@ -16,9 +16,10 @@
 //               band, summed over the partners (conduction gradient: over the valence
 //               bands; valence gradient: over the columns of the chunk, added up over chunks)
 //   k_bandT_*   transpose of the band transform (x1, then x2 and x3, sphere gather)
-// Every inverse line transform of k_qbar and k_ubar uses the radix split of the forward
-// kernels, conjugated: conj(sum_n conj(t_n) e^{+2 pi i n x / N}) = sum_n t_n e^{-2 pi i n x / N}.
+// The inverse line transforms of k_qbar and k_ubar use the folded sums of fold.h, conjugated:
+// conj(sum_n conj(t_n) e^{+2 pi i n x / N}) = sum_n t_n e^{-2 pi i n x / N}.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "fold.h"
@@ -107,113 +108,197 @@ __global__ __launch_bounds__(256) void k_qbar(const double2* __restrict__ mbar, 
   }
 }
 
-// Threads of a k_ubar workgroup and quads of a row that a thread sums at once.
-constexpr int kUt = 256, kUq = 2;
+// Shape of a k_ubar workgroup: UQ x3 quads per wave, ROWS x2 rows and their U 16-byte units of the partner's
+// plane (two buffers).  SMALL: two own bands share the partner's rows (twelve waves).
+template <int RC, bool SMALL, int UQ_> struct UbarShape {
+  static constexpr int K = 2 * RC + 1, UQ = UQ_, OWN = SMALL ? 2 : 1, ROWS = SMALL ? 48 : 64;
+  static constexpr int NW = SMALL ? 6 : 8, QUADS = NW * UQ;           // waves per own band
+  static constexpr int NT = 64 * NW * OWN;
+  static constexpr int rest = OWN * (K * K + ROWS * K) + (RC + 1) * QUADS;   // lines, rows, factors
+  static constexpr int U = SMALL ? 48 * 49 : (10240 - rest) / 2 / 64 * 64;
+  static_assert(2 * U + rest <= 10240, "k_ubar workgroup exceeds the LDS");
+  static bool fits(int nt, int row, int rq) {
+    return 4 * rq <= ROWS && 4 * rq * row <= U && nt / 4 <= QUADS;
+  }
+};
 
-// One workgroup per (x1 plane, part of its x2 quads, own band).  For every partner band: h of the
-// pair on this plane from qbar (x2 transform into LDS, then x3 transform per (row, quads) task), times
-// the partner's plane, accumulated in registers; the plane of ubar is written (COND) or
-// added (valence, accumulated over conduction chunks) at the end.  TPT tasks per thread.
+// One workgroup per (OWN own bands, part of the x2 quads, x1 plane).  For every partner band: h of the pair on this
+// plane from qbar (x2 transform into LDS, then the x3 transform), times the partner's plane, accumulated in
+// registers; the plane of ubar is written (COND) or added (valence, accumulated over conduction chunks) at
+// the end.
 //   COND:  own = column c < ncs (pairs v * ncs + c, v < nvs), ubar_c += h_vc u_v
 //   !COND: own = valence slot v < nvs (pairs v * ncs + c, c < ncs), ubar_v += conj(h_vc) u_c
 // The inverse sums run on the conjugates (conj h), so that the factors are the forward ones.
-template <int RC, int TPT, bool COND>
-__global__ __launch_bounds__(kUt) void k_ubar(const double2* __restrict__ qbar, const double2* __restrict__ partner,
-                                              int nvs, int ncs, int nt, int nl, int row, int nparts, int rq,
-                                              const int32_t* __restrict__ rowtab, const double2* __restrict__ pts,
-                                              double2* __restrict__ ubar) {
-  constexpr int K = 2 * RC + 1;
+// A wave takes UQ x3 quads (uniform: factors by scalar loads), a lane one row: the frequencies and the
+// partner's rows are read from LDS at an odd stride.  The partner's rows come by direct loads and the pair's
+// lines through registers, one partner ahead.  Lines and rows are kept folded over +-n3: slot n = sum,
+// RC + n = difference.  Measured (RC 7 on 44^3, 64 x 256 pairs): conduction 3.9 ms, valence 4.1 (5.8 with
+// one own band per workgroup: the direct loads of the rows bound it); 8.6 and 9.2 with the
+// partner's rows read from memory by lanes a row apart and nothing in flight across partners.
+template <int RC, bool COND, typename P>
+__global__ __launch_bounds__(P::NT) void k_ubar(const double2* __restrict__ qbar, const double2* __restrict__ partner,
+                                             int nvs, int ncs, int nt, int nl, int row, int nparts, int rq,
+                                             const int32_t* __restrict__ rowtab, const double2* __restrict__ pts,
+                                             double2* __restrict__ ubar) {
+  constexpr int K = P::K, UQ = P::UQ;
+  constexpr int NLD = 2;                          // (n2, n3 >= 0) entries per thread
   const int nq = nt / 4;
-  extern __shared__ __align__(16) unsigned char s_raw[];
-  double2* s_q = (double2*)s_raw;                 // [n2][n3] conj of the pair's lines, K x K
-  double2* s_f = s_q + K * K;                     // [n][j] factors, (RC + 1) x nq
-  double2* s_t = s_f + (RC + 1) * nq;             // [row of the part][n3], 4 rq x (K + 1)
-  constexpr int KS = K + 1;                       // even: rows of n3 folded in place below
-  const int x1 = blockIdx.x % nt;
-  const int part = (blockIdx.x / nt) % nparts;
-  const int own = blockIdx.x / (nt * nparts);
-  const int q0 = part * rq;                       // x2 quads [q0, q1)
-  const int q1 = min(nq, q0 + rq);
-  const int nrow = 4 * (q1 - q0);
-  const int ngq = (nq + kUq - 1) / kUq;           // x3 quad groups of a row
-  const int ntask = nrow * ngq;
-  const int tid = threadIdx.x;
+  // arrays of their own: reads of one do not wait for the direct loads into another
+  __shared__ __align__(16) double2 s_u0[P::U], s_u1[P::U];
+  __shared__ double2 s_qs[P::OWN * K * K];        // [n2][slot] conj of the pair's lines
+  __shared__ double2 s_ts[P::OWN * P::ROWS * K];  // [row][slot]
+  __shared__ double2 s_f[(RC + 1) * P::QUADS];    // [n][j] factors
+  const int nown = ((COND ? ncs : nvs) + P::OWN - 1) / P::OWN;
+  const int total = nt * nparts * nown, per = (total + 7) / 8;
+  const int id = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+  if ((int)(blockIdx.x / 8) >= per || id >= total) return;
+  const int own0 = id % nown * P::OWN, part = id / nown % nparts, x1 = id / (nown * nparts);
+  const int q0 = part * rq, q1 = min(nq, q0 + rq), nrow = 4 * (q1 - q0);   // x2 quads [q0, q1)
+  const int nu = nrow * row;
+  // the waves of one own band (tid, wave) and all of them
+  const int lane = threadIdx.x & 63, nth = blockDim.x / P::OWN;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int band = P::OWN == 1 ? 0 : wave_all / (nth / 64), wave = wave_all - band * (nth / 64), tid = wave * 64 + lane;
+  const int own = min(own0 + band, (COND ? ncs : nvs) - 1);
+  double2* s_q = s_qs + band * K * K;
+  double2* s_t = s_ts + band * P::ROWS * K;
   const int npart = COND ? nvs : ncs;
-  for (int i = tid; i < K * K; i += kUt) s_q[i] = double2{0.0, 0.0};   // outside the lines: zero
-  for (int i = tid; i < (RC + 1) * nq; i += kUt) s_f[i] = pts[i];
-  double2 acc[TPT][kUq][4];
+  const int j0 = wave * UQ;
+  // this thread's line entries: offsets of (n2, n3) and (n2, -n3) in the lines, -1 outside
+  int lp[NLD], lm[NLD];
 #pragma unroll
-  for (int k = 0; k < TPT; ++k)
-#pragma unroll
-    for (int a = 0; a < kUq; ++a)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) acc[k][a][c] = double2{0.0, 0.0};
-#pragma unroll 1
-  for (int q = 0; q < npart; ++q) {
-    const size_t pair = COND ? (size_t)q * ncs + own : (size_t)own * ncs + q;
-    const double2* src = qbar + (pair * nt + x1) * (size_t)nl;
-    __syncthreads();   // the previous partner's s_q / s_t are consumed
-    for (int i = tid; i < K * K; i += kUt) {
-      const int j2 = i / K, j3 = i % K;
-      const int32_t* e = rowtab + 3 * j2;
-      if (j3 >= e[1] && j3 <= e[2]) s_q[i] = conjd(src[e[0] + j3]);
-    }
-    __syncthreads();
-    // x2: the four rows of a quad for one n3
-    for (int task = tid; task < K * (q1 - q0); task += kUt) {
-      const int j3 = task % K, ql = task / K, j = q0 + ql;
-      double2 y[1][4];
-      points_of_quads<double2, 1>(
-          RC, j == 0, [&](int n) { return s_q[(n + RC) * K + j3]; }, [&](int n, int) { return s_f[n * nq + j]; }, y);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) s_t[(4 * ql + a) * KS + j3] = y[0][a];
-    }
-    __syncthreads();
-    // x3: quads of a row, times the partner's values
-    const double2* up = partner + ((size_t)q * nt + x1) * (size_t)nt * row;
-#pragma unroll
-    for (int k = 0; k < TPT; ++k) {
-      const int task = tid + kUt * k;
-      if (task < ntask) {
-        const int rl = task % nrow, jq = task / nrow;
-        const int j0 = min(jq * kUq, nq - kUq);
-        double2 y[kUq][4];
-        const double2* tr = s_t + rl * KS + RC;
-        points_of_quads<double2, kUq>(
-            RC, j0 == 0, [&](int n) { return tr[n]; }, [&](int n, int a) { return s_f[n * nq + j0 + a]; }, y);
-        const double2* u = up + (size_t)(4 * q0 + rl) * row + 4 * j0;
-#pragma unroll
-        for (int a = 0; a < kUq; ++a)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const double2 v = u[4 * a + c];
-            // y = conj h
-            acc[k][a][c] = COND ? cadd(acc[k][a][c], cmulc(y[a][c], v)) : cadd(acc[k][a][c], cmul(y[a][c], v));
-          }
-      }
+  for (int i = 0; i < NLD; ++i) {
+    const int e = tid + nth * i;
+    lp[i] = lm[i] = -1;
+    if (e < K * (RC + 1)) {
+      const int32_t* t = rowtab + 3 * (e / (RC + 1));
+      const int n = e % (RC + 1);
+      if (RC + n >= t[1] && RC + n <= t[2]) lp[i] = t[0] + RC + n;
+      if (RC - n >= t[1] && RC - n <= t[2]) lm[i] = t[0] + RC - n;
     }
   }
-  double2* out = ubar + ((size_t)own * nt + x1) * (size_t)nt * row;
+  for (int i = threadIdx.x; i < (RC + 1) * nq; i += blockDim.x) s_f[i] = pts[i];
+  double2 gp[NLD], gm[NLD];
+  auto fetch = [&](int q, double2* u) {
+    const size_t pair = COND ? (size_t)q * ncs + own : (size_t)own * ncs + q;
+    const double2* src = qbar + (pair * nt + x1) * (size_t)nl;
 #pragma unroll
-  for (int k = 0; k < TPT; ++k) {
-    const int task = tid + kUt * k;
-    if (task < ntask) {
-      const int rl = task % nrow, jq = task / nrow;
-      const int j0 = min(jq * kUq, nq - kUq);
-      // an overlapping last group repeats the quads of its neighbour: written by the group that owns them
-      double2* o = out + (size_t)(4 * q0 + rl) * row + 4 * j0;
+    for (int i = 0; i < NLD; ++i) {
+      gp[i] = lp[i] >= 0 ? src[lp[i]] : double2{0.0, 0.0};
+      gm[i] = lm[i] >= 0 ? src[lm[i]] : double2{0.0, 0.0};
+    }
+    const double2* up = partner + (((size_t)q * nt + x1) * nt + 4 * q0) * (size_t)row;
+    for (int u0 = wave_all * 64; u0 < nu; u0 += blockDim.x)
+      if (u0 + lane < nu)
+        __builtin_amdgcn_global_load_lds((const void*)(up + u0 + lane),
+                                         (__attribute__((address_space(3))) void*)(u + u0), 16, 0, 0);
+  };
+  double2 acc[UQ][4];
 #pragma unroll
-      for (int a = 0; a < kUq; ++a)
-        if (j0 + a >= jq * kUq) {
+  for (int a = 0; a < UQ; ++a)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            if (COND)
-              o[4 * a + c] = acc[k][a][c];
-            else
-              o[4 * a + c] = cadd(o[4 * a + c], acc[k][a][c]);
+    for (int c = 0; c < 4; ++c) acc[a][c] = double2{0.0, 0.0};
+  auto mac = [](double2& a, double f, double2 x) {
+    a.x = fma(f, x.x, a.x);
+    a.y = fma(f, x.y, a.y);
+  };
+  auto one = [&](int q, const double2* u, double2* unext) {
+    wait_vm<0>();
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int e = tid + nth * i;
+      if (e < K * (RC + 1)) {
+        const int n2 = e / (RC + 1), n = e % (RC + 1);
+        const double2 x = conjd(gp[i]), y = conjd(gm[i]);
+        s_q[n2 * K + n] = n == 0 ? x : cadd(x, y);
+        if (n > 0) s_q[n2 * K + RC + n] = csub(x, y);
+      }
+    }
+    lds_barrier();   // the lines are folded, the partner's rows have landed, its other buffer is free
+    if (q + 1 < npart) fetch(q + 1, unext);
+    // x2: the four rows of a quad for one slot
+    for (int task = tid; task < K * (q1 - q0); task += nth) {
+      const int sl = task % K, ql = task / K, j = q0 + ql;
+      double2 y[1][4];
+      points_of_quads<double2, 1>(
+          RC, j == 0, [&](int n) { return s_q[(n + RC) * K + sl]; }, [&](int n, int) { return s_f[n * nq + j]; }, y);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) s_t[(4 * ql + a) * K + sl] = y[0][a];
+    }
+    lds_barrier();
+    // x3: this wave's quads of the lane's row, times the partner's values
+    auto sums = [&](auto zero) {
+      constexpr bool Z = decltype(zero)::value;   // quad 0 is among them
+      const double2* tr = s_t + lane * K;
+      double2 ae[UQ], ao[UQ], be[UQ], bo[UQ];
+      const double2 t0 = tr[0];
+#pragma unroll
+      for (int a = 0; a < UQ; ++a) {
+        ae[a] = t0;
+        ao[a] = bo[a] = double2{0.0, 0.0};
+        be[a] = Z && a == 0 ? t0 : double2{0.0, 0.0};
+      }
+#pragma unroll
+      for (int n = 1; n <= RC; ++n) {
+        const double2 e = tr[n], o = tr[RC + n];
+#pragma unroll
+        for (int a = 0; a < UQ; ++a) {
+          const double2 f = pts[n * nq + min(j0 + a, nq - 1)];   // wave-uniform
+          mac(n % 2 ? ao[a] : ae[a], f.x, e);
+          mac(n % 2 ? bo[a] : be[a], f.y, n % 2 == 0 && Z && a == 0 ? e : o);
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < UQ; ++a) {
+        const double2 x = cadd(ae[a], ao[a]), y = csub(ae[a], ao[a]);
+        double2 h[4];   // conj h
+        if (Z && a == 0) {
+          h[0] = x;
+          h[1] = plus_i(be[a], bo[a]);
+          h[2] = y;
+          h[3] = minus_i(be[a], bo[a]);
+        } else {
+          const double2 sx = cadd(be[a], bo[a]), sy = csub(bo[a], be[a]);
+          h[0] = plus_i(x, sx);
+          h[1] = plus_i(y, sy);
+          h[2] = minus_i(y, sy);
+          h[3] = minus_i(x, sx);
+        }
+        const double2* v = u + lane * row + 4 * min(j0 + a, nq - 1);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (COND) {
+            acc[a][c].x = fma(h[c].x, v[c].x, fma(h[c].y, v[c].y, acc[a][c].x));
+            acc[a][c].y = fma(h[c].x, v[c].y, fma(-h[c].y, v[c].x, acc[a][c].y));
+          } else {
+            cmac(acc[a][c], h[c], v[c]);
           }
         }
+      }
+    };
+    if (lane < nrow) {
+      if (wave == 0)
+        sums(std::true_type{});
+      else
+        sums(std::false_type{});
     }
+  };
+  fetch(0, s_u0);
+  for (int q = 0; q < npart; q += 2) {
+    one(q, s_u0, s_u1);
+    if (q + 1 < npart) one(q + 1, s_u1, s_u0);
+  }
+  double2* out = ubar + (((size_t)own * nt + x1) * nt + 4 * q0 + lane) * (size_t)row;
+  if (lane < nrow && own == own0 + band) {   // a repeated last band is not written
+#pragma unroll
+    for (int a = 0; a < UQ; ++a)
+      if (j0 + a < nq) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          double2* o = out + 4 * (j0 + a) + c;
+          *o = COND ? acc[a][c] : cadd(*o, acc[a][c]);
+        }
+      }
   }
 }
 
@@ -339,37 +424,32 @@ hipError_t run_qbar(const Geom& g, const void* mbar, int npair, void* qbar, hipS
   return hipGetLastError();
 }
 
-template <int RC, int TPT, bool COND>
-hipError_t run_ubar_tpt(const Geom& g, const void* qbar, const void* partner, int nvs, int ncs, int nparts, int rq,
-                        void* ubar, hipStream_t st) {
-  constexpr int K = 2 * RC + 1;
-  const size_t lds = ((size_t)K * K + (RC + 1) * (g.nt / 4) + (size_t)4 * rq * (K + 1)) * sizeof(double2);
-  static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ubar<RC, TPT, COND>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (allowed != hipSuccess) return allowed;
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  const unsigned grid = (unsigned)(g.nt * nparts * (COND ? ncs : nvs));
-  k_ubar<RC, TPT, COND><<<grid, kUt, lds, st>>>((const double2*)qbar, (const double2*)partner, nvs, ncs, g.nt, g.nl,
-                                                g.row(true), nparts, rq, g.d_rowtab, g.d_pts64, (double2*)ubar);
+// The plane's x2 quads in the fewest parts whose rows fit.
+template <int RC, typename P>
+hipError_t run_ubar_shape(const Geom& g, const void* qbar, const void* partner, int nvs, int ncs, bool cond, void* ubar,
+                          hipStream_t st) {
+  const int nq = g.nt / 4, row = g.row(true);
+  int rq = nq;
+  for (int n = 1; !P::fits(g.nt, row, rq); rq = (nq + n - 1) / n)
+    if (++n > nq) return hipErrorInvalidValue;
+  const int nparts = (nq + rq - 1) / rq;
+  const int total = g.nt * nparts * (((cond ? ncs : nvs) + P::OWN - 1) / P::OWN);
+  const auto f = cond ? k_ubar<RC, true, P> : k_ubar<RC, false, P>;
+  f<<<(total + 7) / 8 * 8, 64 * P::OWN * ((nq + P::UQ - 1) / P::UQ), 0, st>>>((const double2*)qbar, (const double2*)partner, nvs,
+                                                                     ncs, g.nt, g.nl, row, nparts, rq, g.d_rowtab,
+                                                                     g.d_pts64, (double2*)ubar);
   return hipGetLastError();
 }
 
-// A thread holds kUq quads (8 complex accumulators) per task; the plane's x2 quads are split over
-// parts so that a thread has at most two tasks.
 template <int RC>
 hipError_t run_ubar(const Geom& g, const void* qbar, const void* partner, int nvs, int ncs, bool cond, void* ubar,
                     hipStream_t st) {
-  const int nq = g.nt / 4, ngq = (nq + kUq - 1) / kUq;
-  const int rq_max = std::max(1, 2 * kUt / (4 * ngq));   // x2 quads whose tasks fit two per thread
-  const int nparts = (nq + rq_max - 1) / rq_max;
-  const int rq = (nq + nparts - 1) / nparts;
-  const int ntask = 4 * rq * ngq;
-  if (ntask > 2 * kUt) return hipErrorInvalidValue;
-  if (ntask <= kUt)
-    return cond ? run_ubar_tpt<RC, 1, true>(g, qbar, partner, nvs, ncs, nparts, rq, ubar, st)
-                : run_ubar_tpt<RC, 1, false>(g, qbar, partner, nvs, ncs, nparts, rq, ubar, st);
-  return cond ? run_ubar_tpt<RC, 2, true>(g, qbar, partner, nvs, ncs, nparts, rq, ubar, st)
-              : run_ubar_tpt<RC, 2, false>(g, qbar, partner, nvs, ncs, nparts, rq, ubar, st);
+  if constexpr (RC <= 7) {   // whole planes of up to 48 points
+    if (UbarShape<RC, true, 2>::fits(g.nt, g.row(true), g.nt / 4))
+      return run_ubar_shape<RC, UbarShape<RC, true, 2>>(g, qbar, partner, nvs, ncs, cond, ubar, st);
+  }
+  if (g.nt <= 64) return run_ubar_shape<RC, UbarShape<RC, false, 2>>(g, qbar, partner, nvs, ncs, cond, ubar, st);
+  return run_ubar_shape<RC, UbarShape<RC, false, 4>>(g, qbar, partner, nvs, ncs, cond, ubar, st);
 }
 
 hipError_t allow_bandT_lds() {
