@@ -115,10 +115,16 @@ constexpr int kGpWaves = 8;   // each wave 16 G' and half of the G: two or more 
                               // evaluates elements while another's products run
 constexpr int kGpS = 8;       // states per block
 constexpr int kGpE = 4;       // energies per pass
-constexpr int kGpWg = 512;    // workgroups wanted: the columns are shared out to reach it
+// Shares of the columns: one workgroup runs per CU, so of 1 .. 16 shares the fewest whose rounds over 256 CUs,
+// as a part of a workgroup's columns, are least (169 tiles of NG 800: three shares in two rounds, 2.0 ms; four
+// in three rounds 2.3).
 inline int gpp_split(int ngp) {
   const int tiles = (ngp / kGpT) * (ngp / kGpT);
-  return std::max(1, std::min(16, (kGpWg + tiles - 1) / tiles));
+  int best = 1;
+  auto rounds = [&](int s) { return (tiles * s + 255) / 256; };
+  for (int s = 2; s <= 16; ++s)
+    if (rounds(s) * best < rounds(best) * s) best = s;
+  return best;
 }
 
 struct GppEnergies {
