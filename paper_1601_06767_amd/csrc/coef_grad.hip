@@ -15,7 +15,7 @@
 //   k_ubar      transposes of the x2 and x3 stages of the pair kernel, times the partner
 //               band, summed over the partners (conduction gradient: over the valence
 //               bands; valence gradient: over the columns of the chunk, added up over chunks)
-//   k_bandT_*   transpose of the band transform (x1, then x2 and x3, sphere gather)
+//   k_bandT_*   transpose of the band transform (x1, then x2 and x3, sphere gather), folded sums
 // The inverse line transforms of k_qbar and k_ubar use the folded sums of fold.h, conjugated:
 // conj(sum_n conj(t_n) e^{+2 pi i n x / N}) = sum_n t_n e^{-2 pi i n x / N}.
 #include <algorithm>
@@ -302,98 +302,112 @@ __global__ __launch_bounds__(P::NT) void k_ubar(const double2* __restrict__ qbar
   }
 }
 
-constexpr int kJB = 8;   // outputs per thread of the transposed band passes
+constexpr int kJn = 4;   // frequencies |n| per thread of the transposed band passes: n and -n share the sums
 
-// transpose of the x1 pass: tB[slot][j1][p23] = sum_{x1} e^{-2 pi i n1 x1 / N} ubar[slot][x1][p23]
-__global__ __launch_bounds__(256) void k_bandT_c(const double2* __restrict__ ubar, int rw, int nd, int row,
-                                                 const double2* __restrict__ tw, double2* __restrict__ tB) {
-  __shared__ double2 s_tw[128];
-  for (int i = threadIdx.x; i < nd; i += blockDim.x) s_tw[i] = conjd(tw[i]);
-  __syncthreads();
-  const int W = 2 * rw + 1;
-  const int nblk = (W + kJB - 1) / kJB;
-  const size_t plane = (size_t)nd * row;
-  const int slot = blockIdx.y;
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long long)nblk * (long long)plane) return;
-  const int p23 = (int)(t % (long long)plane);
-  const int jb = (int)(t / (long long)plane);
-  const double2* src = ubar + (size_t)slot * nd * plane + p23;
-  double2 acc[kJB];
-  int idx[kJB], step[kJB];
+// Frequencies +-n, n = n0 .. n0 + kJn - 1, of a line with the conjugate factors: the folded sums of fold.h,
+// F(-n) of the forward transform.  load(p): point at position p of the quad order; s_p[n][j]: (cos, sin)(n j theta),
+// quad 0 as fold.h.  out(k, plus, minus) for n = n0 + k.
+template <typename Load, typename Out>
+__device__ __forceinline__ void conj_freqs(int n0, int nmax, int nq, const double2* s_p, Load load, Out out) {
+  double2 c[kJn], s[kJn];
 #pragma unroll
-  for (int k = 0; k < kJB; ++k) {
-    acc[k] = double2{0.0, 0.0};
-    step[k] = wrap(jb * kJB + k - rw, nd);   // n1 mod N; x1 advances the twiddle index by n1
-    idx[k] = 0;
-  }
-  for (int x1 = 0; x1 < nd; ++x1) {
-    const double2 v = src[(size_t)x1 * plane];
+  for (int k = 0; k < kJn; ++k) c[k] = s[k] = double2{0.0, 0.0};
+  auto mac = [](double2& a, double f, double2 x) {
+    a.x = fma(f, x.x, a.x);
+    a.y = fma(f, x.y, a.y);
+  };
+  for (int j = 0; j < nq; ++j) {
+    const double2 p[4] = {load(4 * j), load(4 * j + 1), load(4 * j + 2), load(4 * j + 3)};
+    const Fold<double2> h = j == 0 ? fold_quad0(p) : fold_quad(p);
 #pragma unroll
-    for (int k = 0; k < kJB; ++k) {
-      cmac(acc[k], v, s_tw[idx[k]]);
-      idx[k] += step[k];
-      if (idx[k] >= nd) idx[k] -= nd;
+    for (int k = 0; k < kJn; ++k) {   // n0 is even: the parity of n is that of k
+      const double2 f = s_p[min(n0 + k, nmax) * nq + j];
+      mac(c[k], f.x, k % 2 == 0 ? h.ce : h.co);
+      if (k % 2 == 0 && j == 0)
+        mac(c[k], f.y, h.se);
+      else
+        mac(s[k], f.y, k % 2 == 0 ? h.se : h.so);
     }
   }
-  double2* dst = tB + (size_t)slot * W * plane + p23;
 #pragma unroll
-  for (int k = 0; k < kJB; ++k)
-    if (jb * kJB + k < W) dst[(size_t)(jb * kJB + k) * plane] = acc[k];
+  for (int k = 0; k < kJn; ++k) out(k, minus_i(c[k], s[k]), plus_i(c[k], s[k]));
+}
+
+// transpose of the x1 pass: tB[slot][j1][p23] = sum_{x1} e^{-2 pi i n1 x1 / N} ubar[slot][x1][p23]; the planes are in
+// natural x1 order
+__global__ __launch_bounds__(256) void k_bandT_c(const double2* __restrict__ ubar, int rw, int nt, int row,
+                                                 const double2* __restrict__ pts, double2* __restrict__ tB) {
+  extern __shared__ __align__(16) unsigned char s_raw[];
+  double2* s_p = (double2*)s_raw;   // (rw + 1) x nq
+  const int nq = nt / 4, W = 2 * rw + 1;
+  for (int i = threadIdx.x; i < (rw + 1) * nq; i += blockDim.x) s_p[i] = pts[i];
+  __syncthreads();
+  const size_t plane = (size_t)nt * row;
+  const int slot = blockIdx.y, n0 = blockIdx.z * kJn;
+  const int p23 = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p23 >= (int)plane) return;
+  const double2* src = ubar + (size_t)slot * nt * plane + p23;
+  double2* dst = tB + ((size_t)slot * W + rw) * plane + p23;
+  conj_freqs(
+      n0, rw, nq, s_p, [&](int p) { return src[(size_t)quad_x(p, nt) * plane]; },
+      [&](int k, double2 a, double2 b) {
+        const int n = n0 + k;
+        if (n > rw) return;
+        dst[(ptrdiff_t)n * (ptrdiff_t)plane] = a;
+        if (n > 0) dst[-(ptrdiff_t)n * (ptrdiff_t)plane] = b;
+      });
 }
 
 // transposes of the x2 and x3 passes for one (slot, j1) slab, then the sphere gather:
-// cbar[slot][ig] for ig = wf_map[j1][j2][j3] >= 0
-__global__ __launch_bounds__(256) void k_bandT_ab(const double2* __restrict__ tB, int rw, int nd, int row,
+// cbar[slot][ig] for ig = wf_map[j1][j2][j3] >= 0.  ld: stride between the lines of s_t (odd where it fits); TL:
+// the factors in LDS too.
+template <bool TL>
+__global__ __launch_bounds__(256) void k_bandT_ab(const double2* __restrict__ tB, int rw, int nt, int row, int ld,
                                                   const int32_t* __restrict__ wf_map, int npw,
-                                                  const double2* __restrict__ tw, double2* __restrict__ cbar) {
+                                                  const double2* __restrict__ pts, double2* __restrict__ cbar) {
   extern __shared__ __align__(16) unsigned char s_raw[];
-  double2* s_tw = (double2*)s_raw;   // conj twiddles, nd
-  double2* s_t = s_tw + 128;         // [j2][p3], W x nd
-  const int W = 2 * rw + 1;
-  const int nblk = (W + kJB - 1) / kJB;
+  const int W = 2 * rw + 1, nq = nt / 4;
+  double2* s_t = (double2*)s_raw;           // [j2][p3], W x ld
+  double2* s_tab = s_t + (size_t)W * ld;    // (rw + 1) x nq
+  const double2* s_p = TL ? s_tab : pts;
+  const int nblk = (rw + kJn) / kJn;        // groups of |n|
   const int j1 = blockIdx.x;
   const int slot = blockIdx.y;
-  for (int i = threadIdx.x; i < nd; i += blockDim.x) s_tw[i] = conjd(tw[i]);
-  __syncthreads();
-  const double2* slab = tB + ((size_t)slot * W + j1) * nd * row;
+  if constexpr (TL) {
+    for (int i = threadIdx.x; i < (rw + 1) * nq; i += blockDim.x) s_tab[i] = pts[i];
+    __syncthreads();
+  }
+  const double2* slab = tB + ((size_t)slot * W + j1) * nt * row;
   // x2: s_t[j2][p3] = sum_{x2} e^{-2 pi i n2 x2 / N} slab[p2(x2)][p3]
-  for (int task = threadIdx.x; task < nd * nblk; task += blockDim.x) {
-    const int p3 = task % nd, jb = task / nd;
-    double2 acc[kJB];
-#pragma unroll
-    for (int k = 0; k < kJB; ++k) acc[k] = double2{0.0, 0.0};
-    for (int p2 = 0; p2 < nd; ++p2) {
-      const int x2 = quad_x(p2, nd);
-      const double2 v = slab[(size_t)p2 * row + p3];
-#pragma unroll
-      for (int k = 0; k < kJB; ++k) cmac(acc[k], v, s_tw[wrap((jb * kJB + k - rw) * x2, nd)]);
-    }
-#pragma unroll
-    for (int k = 0; k < kJB; ++k)
-      if (jb * kJB + k < W) s_t[(size_t)(jb * kJB + k) * nd + p3] = acc[k];
+  for (int task = threadIdx.x; task < nt * nblk; task += blockDim.x) {
+    const int p3 = task % nt, n0 = task / nt * kJn;
+    conj_freqs(
+        n0, rw, nq, s_p, [&](int p) { return slab[(size_t)p * row + p3]; },
+        [&](int k, double2 a, double2 b) {
+          const int n = n0 + k;
+          if (n > rw) return;
+          s_t[(size_t)(rw + n) * ld + p3] = a;
+          if (n > 0) s_t[(size_t)(rw - n) * ld + p3] = b;
+        });
   }
   __syncthreads();
   // x3: cbar(j1, j2, j3) = sum_{x3} e^{-2 pi i n3 x3 / N} s_t[j2][p3(x3)]
   for (int task = threadIdx.x; task < W * nblk; task += blockDim.x) {
-    const int j2 = task % W, jb = task / W;
-    double2 acc[kJB];
-#pragma unroll
-    for (int k = 0; k < kJB; ++k) acc[k] = double2{0.0, 0.0};
-    for (int p3 = 0; p3 < nd; ++p3) {
-      const int x3 = quad_x(p3, nd);
-      const double2 v = s_t[(size_t)j2 * nd + p3];
-#pragma unroll
-      for (int k = 0; k < kJB; ++k) cmac(acc[k], v, s_tw[wrap((jb * kJB + k - rw) * x3, nd)]);
-    }
-#pragma unroll
-    for (int k = 0; k < kJB; ++k) {
-      const int j3 = jb * kJB + k;
-      if (j3 < W) {
-        const int ig = wf_map[((size_t)j1 * W + j2) * W + j3];
-        if (ig >= 0) cbar[(size_t)slot * npw + ig] = acc[k];
-      }
-    }
+    const int j2 = task % W, n0 = task / W * kJn;
+    const double2* line = s_t + (size_t)j2 * ld;
+    const int32_t* map = wf_map + ((size_t)j1 * W + j2) * W + rw;   // index by n3
+    auto put = [&](int n, double2 x) {
+      const int ig = map[n];
+      if (ig >= 0) cbar[(size_t)slot * npw + ig] = x;
+    };
+    conj_freqs(
+        n0, rw, nq, s_p, [&](int p) { return line[p]; },
+        [&](int k, double2 a, double2 b) {
+          const int n = n0 + k;
+          if (n > rw) return;
+          put(n, a);
+          if (n > 0) put(-n, b);
+        });
   }
 }
 
@@ -452,8 +466,9 @@ hipError_t run_ubar(const Geom& g, const void* qbar, const void* partner, int nv
   return run_ubar_shape<RC, UbarShape<RC, false, 4>>(g, qbar, partner, nvs, ncs, cond, ubar, st);
 }
 
+template <bool TL>
 hipError_t allow_bandT_lds() {
-  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bandT_ab),
+  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bandT_ab<TL>),
                                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   return e;
 }
@@ -490,19 +505,22 @@ hipError_t launch_ubar(const Geom& g, const void* qbar, const void* partner, int
 }
 
 hipError_t launch_band_from_real(const Geom& g, const void* ubar, int nslot, void* tB, void* cbar, hipStream_t st) {
-  const int nd = g.nt, W = g.W, row = g.row(true);
-  const size_t lds = (size_t)(128 + W * nd) * sizeof(double2);
-  if (nd > 128 || lds > 160 * 1024) return hipErrorInvalidValue;
-  const hipError_t ea = allow_bandT_lds();
+  const int nt = g.nt, W = g.W, row = g.row(true);
+  constexpr int kUnits = 160 * 1024 / (int)sizeof(double2);
+  if (nt > 128 || 128 + W * nt > kUnits) return hipErrorInvalidValue;
+  const int tab = (g.rw + 1) * (nt / 4);
+  const bool tl = W * (nt + 1) + tab <= kUnits;
+  const int ld = W * (nt + 1) <= kUnits ? nt + 1 : nt;
+  const hipError_t ea = tl ? allow_bandT_lds<true>() : allow_bandT_lds<false>();
   if (ea != hipSuccess) return ea;
-  const int nblk = (W + kJB - 1) / kJB;
-  const long long n = (long long)nblk * nd * row;
-  k_bandT_c<<<dim3((unsigned)((n + 255) / 256), nslot), 256, 0, st>>>((const double2*)ubar, g.rw, nd, row, g.d_tw64,
-                                                                       (double2*)tB);
-  hipError_t e = hipGetLastError();
+  const unsigned groups = (unsigned)((g.rw + kJn) / kJn);
+  k_bandT_c<<<dim3((nt * row + 255) / 256, nslot, groups), 256, tab * sizeof(double2), st>>>(
+      (const double2*)ubar, g.rw, nt, row, g.d_pts64, (double2*)tB);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_bandT_ab<<<dim3(W, nslot), 256, lds, st>>>((const double2*)tB, g.rw, nd, row, g.d_wf_map, g.npw, g.d_tw64,
-                                                (double2*)cbar);
+  const auto f = tl ? k_bandT_ab<true> : k_bandT_ab<false>;
+  f<<<dim3(W, nslot), 256, (W * ld + (tl ? tab : 0)) * sizeof(double2), st>>>(
+      (const double2*)tB, g.rw, nt, row, ld, g.d_wf_map, g.npw, g.d_pts64, (double2*)cbar);
   return hipGetLastError();
 }
 
