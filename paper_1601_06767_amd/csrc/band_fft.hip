@@ -32,8 +32,10 @@ constexpr int kBandAbThreads = 512;
 constexpr int kBq = 4;   // quads per thread: the four share one pass over the line's frequencies
 
 // One workgroup per (band slot, j1).  tab[n][j]: the factors (cos, sin)(n j theta), quad 0 as fold.h;
-// in LDS beside the slab when both fit (TL).
-template <typename T, bool TL>
+// in LDS beside the slab when both fit (TL).  Where the LDS has room for them (CL), the slab's coefficients are
+// gathered into it first, all at once: a thread that sums a line would wait for two dependent loads per
+// frequency (72^3: float64, 56 bands 52 us, 58 before; float32, 4000 bands with the x1 pass 4.0 ms, 5.3 before).
+template <typename T, bool TL, bool CL>
 __global__ __launch_bounds__(kBandAbThreads) void k_band_ab(const double2* __restrict__ coef, int npw,
                                                             const int32_t* __restrict__ band_idx, int band0,
                                                             int nvalid, int nrows, const int32_t* __restrict__ wf_map,
@@ -44,6 +46,7 @@ __global__ __launch_bounds__(kBandAbThreads) void k_band_ab(const double2* __res
   const int W = 2 * rw + 1, nq = nt / 4;
   V* s_t3 = (V*)s_raw;                    // [j2][p3], W x nt
   V* s_tab = s_t3 + (size_t)W * nt;       // (rw + 1) x nq
+  V* s_c = s_tab + (size_t)(rw + 1) * nq; // [j2][j3], W x W
   const int j1 = blockIdx.x;
   const int slot = blockIdx.y;
   if constexpr (TL)
@@ -51,6 +54,14 @@ __global__ __launch_bounds__(kBandAbThreads) void k_band_ab(const double2* __res
   const V* tab = TL ? s_tab : gtab;
   const int band = slot_band(band_idx, band0, nvalid, nrows, slot);
   const double2* c = coef + (size_t)band * npw;
+  if constexpr (CL) {
+    const int32_t* map = wf_map + (size_t)j1 * W * W;
+    for (int i = threadIdx.x; i < W * W; i += blockDim.x) {
+      const int ig = map[i];
+      const double2 v = ig >= 0 ? c[ig] : double2{0.0, 0.0};
+      s_c[i] = V{T(v.x), T(v.y)};
+    }
+  }
   if constexpr (TL) __syncthreads();
   const int ng = (nq + kBq - 1) / kBq;    // groups of quads; the last one overlaps its neighbour
   for (int task = threadIdx.x; task < W * ng; task += blockDim.x) {
@@ -60,6 +71,7 @@ __global__ __launch_bounds__(kBandAbThreads) void k_band_ab(const double2* __res
     points_of_quads<V, kBq>(
         rw, q0 == 0,
         [&](int n) {
+          if constexpr (CL) return s_c[j2 * W + rw + n];
           const int ig = map[n];
           if (ig < 0) return V{T(0), T(0)};
           const double2 v = c[ig];
@@ -117,9 +129,9 @@ __global__ __launch_bounds__(256) void k_band_c(const cx<T>* __restrict__ tB, in
     }
 }
 
-template <typename T, bool TL>
+template <typename T, bool TL, bool CL>
 hipError_t allow_lds() {
-  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_band_ab<T, TL>),
+  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_band_ab<T, TL, CL>),
                                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   return e;
 }
@@ -140,18 +152,19 @@ hipError_t launch_band_to_real(const Geom& g, const double2* coef, int nrows, co
   // wavefunction spheres are limited by their slab on the stated grid
   if ((size_t)(128 + W * g.nd) * sizeof(cx<T>) > 160 * 1024 || slab > 160 * 1024) return hipErrorInvalidValue;
   const dim3 grid(W, nslot);
-  const bool tl = both <= 160 * 1024;
-  const hipError_t ea = tl ? allow_lds<T, true>() : allow_lds<T, false>();
-  if (ea != hipSuccess) return ea;
+  const size_t all = both + (size_t)W * W * sizeof(cx<T>);
   const int ng = (nq + kBq - 1) / kBq;
   const int threads = std::min(kBandAbThreads, (nt * ng + 63) / 64 * 64);
-  if (tl)
-    k_band_ab<T, true><<<grid, threads, both, st>>>(coef, g.npw, band_idx, band0, nvalid, nrows, g.d_wf_map, g.rw, nt,
-                                                    row, tab, (cx<T>*)tB);
-  else
-    k_band_ab<T, false><<<grid, threads, slab, st>>>(coef, g.npw, band_idx, band0, nvalid, nrows, g.d_wf_map, g.rw,
-                                                     nt, row, tab, (cx<T>*)tB);
-  const hipError_t e = hipGetLastError();
+  auto run = [&](auto f, hipError_t allowed, size_t lds) {
+    if (allowed != hipSuccess) return allowed;
+    f<<<grid, threads, lds, st>>>(coef, g.npw, band_idx, band0, nvalid, nrows, g.d_wf_map, g.rw, nt, row, tab,
+                                  (cx<T>*)tB);
+    return hipGetLastError();
+  };
+  constexpr size_t kLds = 160 * 1024;
+  hipError_t e = all <= kLds    ? run(k_band_ab<T, true, true>, allow_lds<T, true, true>(), all)
+                 : both <= kLds ? run(k_band_ab<T, true, false>, allow_lds<T, true, false>(), both)
+                                : run(k_band_ab<T, false, false>, allow_lds<T, false, false>(), slab);
   if (e != hipSuccess) return e;
   k_band_c<T><<<dim3((nt * row + 255) / 256, nslot, ng), 256, 0, st>>>((const cx<T>*)tB, g.rw, nt, row, tab,
                                                                        (cx<T>*)psi);

@@ -3,7 +3,7 @@ points (chunks of x3 quads in fours and sixes, an empty last chunk, short last c
 both sides of the change of shape between max|n_chi| = 7 and 8.  Against the oracle on the stated grid.
 
 Tolerance 2e-5, as for the other float32 parity tests (pair densities of relative error ~1e-7, float32
-sums of up to some hundred pairs)."""
+sums of up to some hundred pairs); float64 1e-10."""
 import numpy as np
 import pytest
 
@@ -31,6 +31,28 @@ def test_plane_chunks_match_oracle(gpu, nd, rw, rc):
             err = np.linalg.norm(chi - ref) / np.linalg.norm(ref)
             print(f"N {nd}, rw {rw}, rc {rc}: {err:.2e}", flush=True)
             assert err <= 2e-5 and np.abs(chi - ref).max() <= 2e-5 * np.abs(ref).max(), err
+    finally:
+        p.gw_geom_destroy(geom)
+        p.gw_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("nd,rw,rc", [(88, 36, 5), (104, 46, 3), (104, 48, 3)])
+def test_band_slabs_of_every_lds_form_match_oracle(gpu, nd, rw, rc):
+    # float64 slabs with the factors, but not the coefficients, beside them in LDS, and with neither
+    import torch
+    import paper_1601_06767_amd as p
+    gw, gc, cv, ev, cc, ec = _case(nd, rw, rc, 2, 3, False)
+    ref = oracle.chi0_bands(cv, ev, cc, ec, gw, gc, (nd,) * 3)[0]
+    dev = torch.device("cuda", 0)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    ctx = p.gw_ctx_create(0)
+    geom = p.gw_geom_create(ctx, (nd,) * 3, gw, gc)
+    try:
+        ts = [t(cv), t(ev), t(cc), t(ec)]
+        chi = p.gw_chi0_build(ctx, [p.make_problem(geom, *ts)], [len(gc)], [0.0], 0.0, p.GW_FP64)[0][0].cpu().numpy()
+        err = np.linalg.norm(chi - ref) / np.linalg.norm(ref)
+        print(f"N {nd}, rw {rw}, rc {rc}: {err:.2e}", flush=True)
+        assert err <= 1e-10 and np.abs(chi - ref).max() <= 1e-10 * np.abs(ref).max(), err
     finally:
         p.gw_geom_destroy(geom)
         p.gw_ctx_destroy(ctx)
