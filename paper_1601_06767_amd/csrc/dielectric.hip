@@ -647,9 +647,10 @@ __global__ void k_sweep_form(const double* __restrict__ v, const double2* __rest
 // A_jj <- -1/d, A_ij <- A_ij / d, A_ji <- conj(A_ij) / d, A_ik -= A_ij conj(A_kj) / d, Hermitian throughout,
 // so it needs column j only, which its owners leave in LDS for the next step: one barrier, eight LDS
 // reads and 64 FMAs per step.  The next step's column is brought up to date, stored and read back before the
-// rest of the piece, whose FMAs run under the reads (NG 2000 in all: 2.07 ms, 2.12 with them before the store).  Row and column j come out of the same update with the factors -1/d for
-// A_jj / d and -1 for A_jj, from zeroed entries.  A pivot that is not positive sets the flag.  (A Cholesky
-// factor, its inverse and their product, all in LDS, took 126 us per block.)
+// rest of the piece, whose FMAs run under the reads (NG 2000 in all: 2.07 ms, 2.12 with them before the
+// store).  Row and column j come out of the same update with the factors -1/d for A_jj / d and -1 for A_jj,
+// from zeroed entries.  A pivot that is not positive sets the flag.  (A Cholesky factor, its inverse and
+// their product, all in LDS, took 126 us per block.)
 __device__ __forceinline__ void diag_inverse(double (&xr)[4][4], double (&xi)[4][4], double2 (*s_col)[kSw],
                                              double2* __restrict__ dinv, int* __restrict__ flag) {
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
