@@ -440,8 +440,8 @@ def main():
                          "their adjoints down to the energy gradients; grouping-study: the 96^3 spectrum summed "
                          "exactly and grouped on several energy grids (accuracy and time against the exact sum); "
                          "extensions: the k-point sum, the static COH self-energy and the plasmon-pole "
-                         "eps^-1(w); reduced-box: the static inputs on the stated 72^3 grid and on the smallest "
-                         "supported alias-free grid (48^3), reported beside the metric, never as it; chunk: "
+                         "eps^-1(w); reduced-box: the static inputs with the stated 72^3 grid and with 48^3 "
+                         "stated (both run on the smallest alias-free grid), beside the metric, never as it; chunk: "
                          "one conduction chunk of a configuration's shape (--chunk), a short driver for "
                          "profiler and counter runs, no JSON line")
     ap.add_argument("--grid", type=int, default=0,
@@ -812,9 +812,9 @@ def run_grouped(args, torch, synth, p, dev, backward):
     k = 2 * int(np.abs(gc).max()) + 1
     npair = cfg.nv * len(col)
     fl = flops_model(transform_grid(nd, gw, gc), k, ng, npair, cfg.nv + len(col))
-    # the adjoint recomputes the pair densities and forms Y = M Gbar^T (8 NG^2 per pair)
+    # the adjoint recomputes the pair densities and forms Y = M L^T, L a lower triangle (4 NG^2 per pair),
     # and Zbar -> chi0bar (two NG^3 complex products, 16 NG^3)
-    bw = fl["planes"] + fl["finish"] + fl["band"] + 2.0 * fl["contract"] + 2.0 * fl["eps_inv"] if backward else 0.0
+    bw = fl["planes"] + fl["finish"] + fl["band"] + fl["contract"] + 2.0 * fl["eps_inv"] if backward else 0.0
     modes = [m for m in args.modes.split(",") if m]
     wsb = max(p.gw_chi0_workspace_size(ctx, [prob], 1, p.PRECISIONS[m]) for m in modes)
     ws = torch.empty(wsb, dtype=torch.uint8, device=dev)
