@@ -51,8 +51,10 @@ template <> struct AMfma<float> {
 // XCD holds at once then share 4 M and 8 chibar row slices of a stage, where the row-major
 // order (the tiles of one pair tile spread over all XCDs) had each XCD read about 32 chibar
 // slices per stage, all of chibar once per pair tile (split-BF16x3 at NG 8000, 32k pairs: L2
-// misses 225 -> 62 GB, 41.1 -> 35.9 ms per launch).  The grid is rounded up to a multiple of
-// 8; the workgroups past the last tile return at once.
+// misses 225 -> 62 GB, 41.1 -> 35.9 ms per launch).  Every other block takes its chibar tiles in
+// descending order: of a lower triangle they differ in length, and a CU that always took the longer
+// one would drift away from the others' stages (NG 8000: 20.5 -> 18.6 ms; NG 4000:
+// 5.30 -> 5.10).  The grid is rounded up to a multiple of 8; the workgroups past the last tile return at once.
 __device__ __forceinline__ void adj_tile(int t, int npt, int ntg, int* pt, int* tg) {
   constexpr int BP = 8, BG = 4;
   const int band = t / (BP * ntg);
@@ -61,7 +63,8 @@ __device__ __forceinline__ void adj_tile(int t, int npt, int ntg, int* pt, int* 
   const int cb = local / (nr * BG);
   const int w = local - cb * nr * BG;
   *pt = band * BP + w % nr;
-  *tg = cb * BG + w / nr;
+  const int ng = min(BG, ntg - cb * BG);     // chibar tiles in this block
+  *tg = cb * BG + (cb & 1 ? ng - 1 - w / nr : w / nr);
 }
 
 // out = chibar + chibar^H (rows by 32 x 32 tiles, the transposed one through LDS); lower: its lower triangle
