@@ -673,7 +673,9 @@ hipError_t run_mfma(const Geom& g, const void* psi_v, const void* psi_c, int nvs
 // wave, two waves per SIMD, one workgroup of eight waves per CU over a fixed grid: RC 9 on 60^3 8.1 ms
 // (before 10.3; workgroups of four waves 8.8), RC 12 on 80^3 16.2 ms (before 22; 17.9).
 // float64: four waves, half a line per lane; RC 7 on 44^3 4.7 ms, RC 9 on 60^3 20.3 (one wave per SIMD
-// beyond RC 7).
+// beyond RC 7).  Up to RC 4 and 32 points the row buffers are half as long and the registers suffice for
+// three waves per SIMD (24^3,
+// RC 4 on 20^3, 3840 pairs: 74 us, 93 with two).
 template <typename T, int RC>
 hipError_t run_planes(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q, hipStream_t st) {
   if constexpr (std::is_same<T, float>::value) {
@@ -682,6 +684,10 @@ hipError_t run_planes(const Geom& g, const void* psi_v, const void* psi_c, int n
     else
       return run_mfma<RC, MfmaShape<RC, 4, 8, 4, 8, 4032, 2>>(g, psi_v, psi_c, nvs, ncs, q, st);
   } else {
+    if constexpr (RC <= 4) {
+      if (g.nt <= 32)
+        return run_shape<T, RC, PlaneShape<T, RC, 2, 1, 4, 8, 32, 3>>(g, psi_v, psi_c, nvs, ncs, q, st);
+    }
     if constexpr (RC <= 7) {
       if (g.nt <= 64)
         return run_shape<T, RC, PlaneShape<T, RC, 2, 1, 4, 8, 64, 2>>(g, psi_v, psi_c, nvs, ncs, q, st);
