@@ -906,7 +906,7 @@ GppCohLayout gpp_coh_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nq, i
     const Geom& g = probs[i].geom->g;
     const size_t r = round_up(L.total, 256) + 2 * round_up((size_t)g.ngp * g.ngp * sizeof(double2), 256);
     c.region = std::max(c.region, r);
-    c.part_pass = std::max(c.part_pass, gw::gpp_coh_part_bytes(g.ngp));
+    c.part_pass = std::max(c.part_pass, gw::gpp_coh_part_bytes(g.ngp, L.pp[0].cc));
   }
   const int bs = gw::gpp_coh_states_per_block(), be = gw::gpp_coh_energies_per_pass();
   c.nsb = (probs[0].nv + bs - 1) / bs;

@@ -149,7 +149,7 @@ hipError_t launch_coh_reduce(const void* m, const void* z, int ns, int cc, int n
 int gpp_coh_tile();
 int gpp_coh_states_per_block();
 int gpp_coh_energies_per_pass();
-size_t gpp_coh_part_bytes(int ngp);
+size_t gpp_coh_part_bytes(int ngp, int cc);   // one pass's partial sums, over chunks of cc columns
 hipError_t launch_gpp_coh_prep(const void* modes, const double* v, int ng, int ngp, void* b, void* w, hipStream_t st);
 hipError_t launch_gpp_coh(const void* b, const void* w, int ngp, const void* m, int cc, int ns, int sa, int sb,
                           int nvalid, const double* e_col, const double* n_col, int c0, const double* energies, int ne,

@@ -108,23 +108,30 @@ __global__ void k_coh_sum(const double2* __restrict__ part, int nblk, int nout, 
 //     W_re = X1_r - X2_i, W_im = X1_i + X2_r (lanes 8 apart);
 //   Y[n'][n] += sum_G' w_c M_n'(G') W[G'][n]: an accumulator register of W holds four G' of each lane
 //     group, which is the B operand's layout, so W goes straight into the second product.
-// The states of a column come in by direct loads one column ahead.  Partial sums per (tile, wave, share
-// of the columns) are reduced in a fixed order.
+// The states of a column come in by direct loads one column ahead.  Partial sums per (tile, share of
+// the columns) are reduced in a fixed order.
 constexpr int kGpT = 64;      // G rows and G' columns of a tile
 constexpr int kGpWaves = 8;   // each wave 16 G' and half of the G: two or more waves per SIMD, so that one
                               // evaluates elements while another's products run
 constexpr int kGpS = 8;       // states per block
 constexpr int kGpE = 4;       // energies per pass
-// Shares of the columns: one workgroup runs per CU, so of 1 .. 16 shares the fewest whose rounds over 256 CUs,
-// as a part of a workgroup's columns, are least (169 tiles of NG 800: three shares in two rounds, 2.0 ms; four
-// in three rounds 2.3).
-inline int gpp_split(int ngp) {
-  const int tiles = (ngp / kGpT) * (ngp / kGpT);
+static_assert(kGpE <= kGpWaves, "a wave per energy adds the partial sums");
+// Shares of the columns.  One workgroup runs per CU, so a launch lasts as long as its rounds over 256 CUs times
+// the columns of a share; more shares are taken where that falls by two per cent or more (196 tiles of NG 800,
+// 300 columns: five shares of 60 in four rounds, 2.70 ms a call; 13 shares of 24 in ten rounds, every wave with
+// partial sums of its own, 2.83).  Every share keeps partial sums (4 KiB a tile): as many shares as keep
+// them within 8 MiB a pass, up to 16, and up to eight on any sphere.
+inline int gpp_tiles(int ngp) { return (ngp / kGpT) * (ngp / kGpT); }
+inline int gpp_shares(int tiles, int columns, int most) {
+  auto cost = [&](int s) { return (long long)((tiles * s + 255) / 256) * ((columns + s - 1) / s); };
   int best = 1;
-  auto rounds = [&](int s) { return (tiles * s + 255) / 256; };
-  for (int s = 2; s <= 16; ++s)
-    if (rounds(s) * best < rounds(best) * s) best = s;
+  for (int s = 2; s <= std::min(most, columns); ++s)
+    if (cost(s) * 50 < cost(best) * 49) best = s;
   return best;
+}
+// shares that the partial sums of a pass over chunks of cc columns have room for
+inline int gpp_share_room(int tiles, int cc) {
+  return gpp_shares(tiles, cc, std::min(16, std::max(8, 2048 / tiles)));
 }
 
 struct GppEnergies {
@@ -176,10 +183,10 @@ __device__ __forceinline__ double lane_xor8(double x) {
   return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// part[((slot * 8 + wave) * kGpE + j) * 64 + lane] += sum over this share of the chunk's columns for lane's
-// (n, n') = (lane / 8, lane % 8) of state blocks (sa, sb), slot = tile * split + share; states >= ns repeat
+// part[(slot * kGpE + j) * 64 + lane] += sum over this share of the chunk's columns for lane's
+// (n, n') = (lane / 8, lane % 8) of state blocks (sa, sb), slot = tile * shares + share; states >= ns repeat
 // the last one (their sums are not read).  Bound by float64 MFMA beside the
-// evaluation of the elements on the VALU.  Measured (NG 800, 8 states, 300 columns, 4 energies): 2.1 ms;
+// evaluation of the elements on the VALU.  Measured (NG 800, 8 states, 300 columns, 4 energies): 1.84 ms;
 // 13.3 with the sums on the VALU, W through LDS and divisions in place of a reciprocal.
 __global__ __launch_bounds__(64 * kGpWaves, 2) void k_coh_gpp(const double2* __restrict__ bb, const double2* __restrict__ ww,
                                                     int ngp, int ntile1, const double2* __restrict__ m, int cc, int ns,
@@ -267,24 +274,31 @@ __global__ __launch_bounds__(64 * kGpWaves, 2) void k_coh_gpp(const double2* __r
     }
   }
   wait_vm<0>();
-  // Y rows (n', part') = lk + 4 r, columns (n, part) = li, through LDS to one (n, n') per lane:
+  // Y rows (n', part') = lk + 4 r, columns (n, part) = li, through LDS to one (n, n') per lane, the waves' sums
+  // added in their order (wave j takes energy j):
   // S_re = Y[re][re] + Y[im][im], S_im = Y[re][im] - Y[im][re]  (row part, column part)
-  double* sy = (double*)s_m0 + wave * 256;   // 16 KB of the 16.25
-  double2* dst = part + ((size_t)((tile * gridDim.y + blockIdx.y) * kGpWaves + wave) * kGpE) * 64 + lane;
+  double* sy = (double*)s_m0;   // 256 per wave: 16 KB of the 16.25
+  double2* dst = part + ((size_t)(tile * gridDim.y + blockIdx.y) * kGpE) * 64 + lane;
   const int pn = lane / kGpS, pm = lane % kGpS;
 #pragma unroll
   for (int j = 0; j < kGpE; ++j) {
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 4; ++k) sy[(lk + 4 * k) * 16 + li] = y[j][k];
+    for (int k = 0; k < 4; ++k) sy[wave * 256 + (lk + 4 * k) * 16 + li] = y[j][k];
     __syncthreads();
-    const double2 o = dst[(size_t)j * 64];
-    dst[(size_t)j * 64] = double2{o.x + (sy[pm * 16 + pn] + sy[(pm + 8) * 16 + pn + 8]),
-                                  o.y + (sy[pm * 16 + pn + 8] - sy[(pm + 8) * 16 + pn])};
+    if (wave == j) {
+      double2 t = dst[(size_t)j * 64];
+      for (int w = 0; w < kGpWaves; ++w) {
+        const double* yw = sy + w * 256;
+        t.x += yw[pm * 16 + pn] + yw[(pm + 8) * 16 + pn + 8];
+        t.y += yw[pm * 16 + pn + 8] - yw[(pm + 8) * 16 + pn];
+      }
+      dst[(size_t)j * 64] = t;
+    }
   }
 }
 
-// out[j][n][n'] += 1/2 sum over tiles and waves of part (fixed order: each thread a fixed
+// out[j][n][n'] += 1/2 sum over the slots of part (fixed order: each thread a fixed
 // strided subset, then a fixed tree), one workgroup per (j, n, n') of the pass
 __global__ __launch_bounds__(256) void k_coh_gpp_sum(const double2* __restrict__ part, int nslot, int ne, int ns,
                                                      int sa, int sb, int e0, double2* __restrict__ out) {
@@ -313,9 +327,9 @@ int coh_max_states() { return kCohMaxStates; }
 int gpp_coh_tile() { return kGpT; }
 int gpp_coh_states_per_block() { return kGpS; }
 int gpp_coh_energies_per_pass() { return kGpE; }
-size_t gpp_coh_part_bytes(int ngp) {
-  const size_t nt = (size_t)(ngp / kGpT) * (ngp / kGpT);
-  return nt * gpp_split(ngp) * kGpWaves * kGpE * 64 * sizeof(double2);
+size_t gpp_coh_part_bytes(int ngp, int cc) {
+  const int tiles = gpp_tiles(ngp);
+  return (size_t)tiles * gpp_share_room(tiles, cc) * kGpE * 64 * sizeof(double2);
 }
 
 hipError_t launch_gpp_coh_prep(const void* modes, const double* v, int ng, int ngp, void* b, void* w, hipStream_t st) {
@@ -329,13 +343,13 @@ hipError_t launch_gpp_coh_prep(const void* modes, const double* v, int ng, int n
 hipError_t launch_gpp_coh(const void* b, const void* w, int ngp, const void* m, int cc, int ns, int sa, int sb,
                           int nvalid, const double* e_col, const double* n_col, int c0, const double* energies, int ne,
                           double delta, void* part, hipStream_t st) {
-  if (ngp % kGpT != 0 || ne < 1 || ne > kGpE) return hipErrorInvalidValue;
+  if (ngp % kGpT != 0 || ne < 1 || ne > kGpE || nvalid < 1 || nvalid > cc) return hipErrorInvalidValue;
   GppEnergies en{};
   for (int j = 0; j < ne; ++j) en.e[j] = energies[j];
-  const int nt1 = ngp / kGpT;
-  k_coh_gpp<<<dim3(nt1 * nt1, gpp_split(ngp)), 64 * kGpWaves, 0, st>>>((const double2*)b, (const double2*)w, ngp, nt1,
-                                                             (const double2*)m, cc, ns, sa, sb, nvalid, e_col, n_col,
-                                                             c0, en, ne, delta, (double2*)part);
+  const int tiles = gpp_tiles(ngp), shares = gpp_shares(tiles, nvalid, gpp_share_room(tiles, cc));
+  k_coh_gpp<<<dim3(tiles, shares), 64 * kGpWaves, 0, st>>>((const double2*)b, (const double2*)w, ngp, ngp / kGpT,
+                                                           (const double2*)m, cc, ns, sa, sb, nvalid, e_col, n_col, c0,
+                                                           en, ne, delta, (double2*)part);
   return hipGetLastError();
 }
 
