@@ -103,27 +103,31 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
     items += (long long)q.ntl * nomega * L.nparts;
     L.pp.push_back(q);
   }
-  // Split the pair ranges, at most 16 ways (24^3 float64: 218 us per build with 16, 232 with 32, 244 with
-  // 8; 72^3 float64: 58.5 / 59.7 / 59.1 ms), so that (a) the batch has about 8 items per CU and (b) for a
+  // Split the pair ranges so that (a) the batch has about 8 items per CU and (b) for a
   // single job, the rows of M that the items in flight share (one pair range) stay near
   // 32 MB, so they are served from cache instead of HBM (with several jobs the items of one
   // range already share their rows).  Every split costs a float64 partial NG^2 per job, so
-  // the splits are capped to keep the partials within 16 GB (or their unsplit size).  A
-  // tuned choice overrides.
+  // the splits are capped to keep the partials within 16 GB (or their unsplit size), and at 32,
+  // in float64 at 16 (24^3: 218 us per build with 16, 232 with 32, 244 with 8; 72^3: 58.5 / 59.7 /
+  // 59.1 ms).  The other modes sum a range in float32, with an error that grows with its length on
+  // the diagonal, whose terms have one sign (float32, of the norm, with 16 and 32: 24^3 3.0e-7 and
+  // 2.7e-7, at two frequencies 5.5e-7 and 3.8e-7, 332 and 368 us; NG 4000, 32k pairs 5.2e-7 and
+  // 3.6e-7, 29.8 and 32.3 ms).  A tuned choice overrides.
   // The row-image contraction (static split-BF16x3) runs a static grid of two workgroups per
   // CU and reads its operands through L2 in tile order, so it wants only about two items per
   // workgroup and no cache-sized ranges: every split adds a float64 read-modify-write of a
   // 256 KB partial per item (one 128^3 / NG 8000 chunk of 32k pairs: 21.1 ms unsplit, 21.8 with
   // 4 splits, 25.6 with 32).
   const long long want = L.images ? 4LL * 256 : 8LL * 256;
-  const int ks_par = items >= want ? 1 : (int)std::min<long long>(16, (want + items - 1) / items);
+  const int ks_max = L.fp64 ? 16 : 32;
+  const int ks_par = items >= want ? 1 : (int)std::min<long long>(ks_max, (want + items - 1) / items);
   const int njobs = nomega * L.nparts;
   size_t acc1 = 0;   // partials of all problems with one split each
   for (const auto& q : L.pp) acc1 += (size_t)q.p->geom->g.ngp * q.p->geom->g.ngp * sizeof(double2) * njobs;
   const int ks_mem = (int)std::max<size_t>(1, (size_t(16) << 30) / std::max<size_t>(acc1, 1));
   for (auto& q : L.pp) {
     const size_t mbytes = (size_t)q.npair * q.p->geom->g.ngp * L.csz;
-    const int ks_cache = njobs > 1 || L.images ? 1 : (int)std::min<size_t>(16, (mbytes + (32u << 20) - 1) / (32u << 20));
+    const int ks_cache = njobs > 1 || L.images ? 1 : (int)std::min<size_t>(ks_max, (mbytes + (32u << 20) - 1) / (32u << 20));
     int k = std::min(std::max(ks_par, ks_cache), ks_mem);
     auto it = ctx->tune.find(shape_key(q.p->geom->g, q.p->nv, q.p->ncol, prec));
     if (it != ctx->tune.end()) {
