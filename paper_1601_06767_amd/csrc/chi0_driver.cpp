@@ -28,9 +28,8 @@ namespace {
 size_t round_up(size_t x, size_t m) { return (x + m - 1) / m * m; }
 
 constexpr int kPairTarget = 32768;   // band pairs per conduction chunk
-constexpr int kColumnStep = 16;      // conduction columns of a chunk: whole workgroups of the pair kernel
 
-// columns of a chunk beside nvs (padded) valence slots
+// columns of a chunk beside nvs (padded) valence slots: whole workgroups of the pair kernel, eight columns each
 int chunk_columns(int nvs) { return std::max(8, (kPairTarget / nvs) / 8 * 8); }
 
 // Bands per band-transform launch pair: 32 fill the chip from the 72^3 spheres on; smaller grids take as
@@ -96,7 +95,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
     ProbPlan q;
     q.p = &probs[i];
     q.nvs = (int)round_up(probs[i].nv, 4);
-    q.cc = (int)round_up(std::min<int>(chunk_columns(q.nvs), probs[i].ncol), kColumnStep);
+    q.cc = (int)round_up(std::min<int>(chunk_columns(q.nvs), probs[i].ncol), 8);
     q.npair = q.nvs * q.cc;
     const int nt = (g.ng + gw::contract_tile(L.mode) - 1) / gw::contract_tile(L.mode);   // tiles with a G < ng
     q.ntl = nt * (nt + 1) / 2;
