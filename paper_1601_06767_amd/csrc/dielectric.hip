@@ -77,7 +77,7 @@ __device__ __forceinline__ unsigned wave_max(unsigned k) {
   return (unsigned)__builtin_amdgcn_readlane((int)k, 63);
 }
 
-// 1 / d for a normal d > 0: the hardware estimate and two Newton steps
+// 1 / d for d > 0 whose 1 / d is finite: the hardware estimate and two Newton steps
 __device__ __forceinline__ double recip(double d) {
   double r = __builtin_amdgcn_rcp(d);
   r = fma(fma(-d, r, 1.0), r, r);
@@ -86,21 +86,40 @@ __device__ __forceinline__ double recip(double d) {
 
 // The S pivot steps of the panel columns [c0, c0 + sc), sc <= S, in one workgroup: each thread holds R
 // rows of the S columns in registers.  Per step: the pivot as the largest |x|^2 of the rows from
-// j on (compared to 2^-9 relative, the lower row on ties, so that value and row share one 32-bit key),
-// its row and row j through LDS, then row j <- row p / d, row p <- row j (old) eliminated, every other
+// j on (the lower row on ties), its row and row j through LDS, then row j <- row p / d, row p <- row j (old) eliminated, every other
 // row eliminated, column <- the corresponding column of the transform.  Register column 0 is the
 // step's pivot column and every step rotates the columns by one: the loop stays rolled (unrolled, a
 // launch spent its time on instruction fetch, 18 us per step).  Serial: two barriers and a
 // reduction per step.
 constexpr int kGjThreads = 512;
-constexpr int kGjMaxRows = 2048;   // rows the registers hold, and row numbers a key holds
+constexpr int kGjMaxRows = 2048;   // rows the registers hold
+// A row and its |x|^2 as two words, the upper one raised by one: 0 for no row.  The largest is found by the
+// upper words; only where lanes or waves tie there do the lower words and the row numbers decide (4 x 1114:
+// 5.8 ms; 6.4 with every step over the whole value, 5.6 with a single word of 21 bits and the row, which
+// lost the pivots whose squares are subnormal).
+struct GjCandidate {
+  unsigned hi, lo;
+  int row, pad;
+};
+// the lane of the largest candidate among those of mask; top: its upper word
+__device__ __forceinline__ int gj_winner(const GjCandidate& k, unsigned top, unsigned long long mask) {
+  unsigned long long m = __ballot(k.hi == top) & mask;
+  if ((m & (m - 1)) != 0) {
+    const unsigned lo = wave_max(k.hi == top ? k.lo : 0u);
+    const bool tie = k.hi == top && k.lo == lo;
+    const unsigned last = wave_max(tie ? (unsigned)(kGjMaxRows - k.row) : 0u);   // the lowest row
+    m = __ballot(tie && (unsigned)(kGjMaxRows - k.row) == last) & mask;
+  }
+  return __builtin_ctzll(m);
+}
 template <int R, int S>
 __global__ __launch_bounds__(kGjThreads) void k_gj_sub(const double2* __restrict__ pin, int n, int j0, int c0, int sc,
                                                        size_t ws, double2* __restrict__ tout, int* __restrict__ piv,
                                                        int* __restrict__ flag) {
-  static_assert(R * kGjThreads <= kGjMaxRows, "row numbers of a key");
+  static_assert(R * kGjThreads <= kGjMaxRows, "rows of the pivot steps");
   constexpr int NW = kGjThreads / 64;
-  __shared__ __align__(16) unsigned s_key[2][NW];
+  static_assert(NW == 8, "a candidate per wave, read by lane mod 8");
+  __shared__ __align__(16) GjCandidate s_best[2][NW];
   __shared__ double2 s_prow[2][S], s_rowj[2][S];
   pin = slice(pin, ws);
   tout = slice(tout, ws);
@@ -117,21 +136,29 @@ __global__ __launch_bounds__(kGjThreads) void k_gj_sub(const double2* __restrict
 #pragma unroll 1
   for (int jc = 0; jc < sc; ++jc) {
     const int j = j0 + c0 + jc, b = jc & 1;
-    unsigned key = 0;
+    double best = -1.0;   // no comparison holds for a NaN
+    int row = kGjMaxRows;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int i = tid + kGjThreads * r;
       const double m = x[r][0].x * x[r][0].x + x[r][0].y * x[r][0].y;
-      const unsigned k = ((unsigned)(__double_as_longlong(m) >> 32) & ~(unsigned)(kGjMaxRows - 1)) | (kGjMaxRows - 1 - i);
-      if (i >= j && i < n && k > key) key = k;
+      if (i >= j && i < n && m > best) {
+        best = m;
+        row = i;
+      }
     }
-    key = wave_max(key);
-    if ((tid & 63) == 0) s_key[b][tid >> 6] = key;
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(best);
+    GjCandidate k{row < kGjMaxRows ? (unsigned)(bits >> 32) + 1 : 0u, (unsigned)bits, row, 0};
+    const unsigned most = wave_max(k.hi);
+    if ((tid & 63) == (most != 0 ? gj_winner(k, most, ~0ull) : 0)) s_best[b][tid >> 6] = k;
     __syncthreads();
-    key = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) key = max(key, s_key[b][w]);
-    const int p = __builtin_amdgcn_readfirstlane(kGjMaxRows - 1 - (int)(key & (kGjMaxRows - 1)));   // some row >= j
+    k = s_best[b][tid & 7];
+    unsigned top = k.hi;   // of the eight waves, in every lane
+    top = max(top, (unsigned)__builtin_amdgcn_update_dpp(0, (int)top, 0xb1, 0xf, 0xf, false));    // lane ^ 1
+    top = max(top, (unsigned)__builtin_amdgcn_update_dpp(0, (int)top, 0x4e, 0xf, 0xf, false));    // lane ^ 2
+    top = max(top, (unsigned)__builtin_amdgcn_update_dpp(0, (int)top, 0x141, 0xf, 0xf, false));   // 7 - lane
+    const int win = __builtin_amdgcn_readlane(k.row, gj_winner(k, top, (1ull << NW) - 1));
+    const int p = win < n ? win : j;   // no finite candidate: row j, the flag reports it
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int i = tid + kGjThreads * r;
@@ -151,8 +178,13 @@ __global__ __launch_bounds__(kGjThreads) void k_gj_sub(const double2* __restrict
       piv[j] = p;
       if (!(den > 0.0) || !isfinite(den)) *flag = 1;
     }
-    const double rden = den > 0.0 ? recip(den) : 0.0;
-    const double2 dinv{d.x * rden, -d.y * rden};
+    double2 dinv{0.0, 0.0};
+    if (den >= 0x1p-1021 && den <= 0x1p1021) {   // 1 / den normal too
+      const double rden = recip(den);
+      dinv = double2{d.x * rden, -d.y * rden};
+    } else if (den > 0.0) {
+      dinv = double2{d.x / den, -d.y / den};
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int i = tid + kGjThreads * r;
@@ -174,7 +206,7 @@ __global__ __launch_bounds__(kGjThreads) void k_gj_sub(const double2* __restrict
       }
       x[r][S - 1] = double2{-f.x, -f.y};
     }
-    // the LDS rows and keys alternate between two sets: a wave that runs ahead into the next step
+    // the LDS rows and candidates alternate between two sets: a wave that runs ahead into the next step
     // writes the other one
   }
   // after sc rotations register column c is panel column (sc + c) mod S
