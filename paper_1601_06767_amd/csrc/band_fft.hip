@@ -131,9 +131,8 @@ __global__ __launch_bounds__(256) void k_band_c(const cx<T>* __restrict__ tB, in
 
 template <typename T, bool TL, bool CL>
 hipError_t allow_lds() {
-  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_band_ab<T, TL, CL>),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  return e;
+  static OncePerDevice done;
+  return allow_whole_lds(reinterpret_cast<const void*>(&k_band_ab<T, TL, CL>), done);
 }
 
 }  // namespace
@@ -161,10 +160,9 @@ hipError_t launch_band_to_real(const Geom& g, const double2* coef, int nrows, co
                                   (cx<T>*)tB);
     return hipGetLastError();
   };
-  constexpr size_t kLds = 160 * 1024;
-  hipError_t e = all <= kLds    ? run(k_band_ab<T, true, true>, allow_lds<T, true, true>(), all)
-                 : both <= kLds ? run(k_band_ab<T, true, false>, allow_lds<T, true, false>(), both)
-                                : run(k_band_ab<T, false, false>, allow_lds<T, false, false>(), slab);
+  hipError_t e = all <= kLdsBytes    ? run(k_band_ab<T, true, true>, allow_lds<T, true, true>(), all)
+                 : both <= kLdsBytes ? run(k_band_ab<T, true, false>, allow_lds<T, true, false>(), both)
+                                     : run(k_band_ab<T, false, false>, allow_lds<T, false, false>(), slab);
   if (e != hipSuccess) return e;
   k_band_c<T><<<dim3((nt * row + 255) / 256, nslot, ng), 256, 0, st>>>((const cx<T>*)tB, g.rw, nt, row, tab,
                                                                        (cx<T>*)psi);

@@ -468,9 +468,8 @@ hipError_t run_ubar(const Geom& g, const void* qbar, const void* partner, int nv
 
 template <bool TL>
 hipError_t allow_bandT_lds() {
-  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bandT_ab<TL>),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  return e;
+  static OncePerDevice done;
+  return allow_whole_lds(reinterpret_cast<const void*>(&k_bandT_ab<TL>), done);
 }
 
 }  // namespace

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/gwchi0.h"
+#include "per_device.h"
 
 namespace gw {
 enum Stage { kStageBand = 0, kStagePlanes, kStageFinish, kStageWeights, kStageContract, kStageFinalize,
@@ -89,6 +90,17 @@ struct StageScope {
 }  // namespace gw
 
 namespace gw {
+
+// Lets a kernel take 160 KB of dynamic LDS on the current device (done: an object of the kernel's own).
+constexpr size_t kLdsBytes = 160 * 1024;
+inline hipError_t allow_whole_lds(const void* kernel, OncePerDevice& done) {
+  int device = 0;
+  const hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
+  return done.run(device, [&] {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+  });
+}
 
 bool grid_supported(int nd);   // stated FFT grids: N a multiple of 8 from 16 to 128
 

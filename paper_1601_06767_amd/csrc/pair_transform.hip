@@ -705,11 +705,10 @@ hipError_t run_finish(const Geom& g, const void* q, int npair, void* m, hipStrea
   auto run = [&](auto f, size_t lds) {
     f<<<npair, threads, lds, st>>>((const cx<T>*)q, g.d_chi_map, g.ng, g.ngp, g.nt, g.nl, scale, fac, (cx<T>*)m);
   };
-  constexpr size_t kLds = 160 * 1024;
   const size_t lds = (size_t)g.ng * sizeof(cx<T>);
-  if (lds <= kLds) {
-    static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pair_finish<T, RC, true>),
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+  if (lds <= kLdsBytes) {
+    static OncePerDevice done;
+    const hipError_t allowed = allow_whole_lds(reinterpret_cast<const void*>(&k_pair_finish<T, RC, true>), done);
     if (allowed != hipSuccess) return allowed;
     run(k_pair_finish<T, RC, true>, lds);
   } else {
