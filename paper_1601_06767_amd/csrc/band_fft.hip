@@ -28,6 +28,13 @@ __device__ __forceinline__ int slot_band(const int32_t* band_idx, int band0, int
   return band < 0 ? 0 : (band >= nrows ? nrows - 1 : band);   // never read outside the coefficient rows
 }
 
+template <typename V> __device__ __forceinline__ double2 widen(V x) { return double2{(double)x.x, (double)x.y}; }
+template <typename T> __device__ __forceinline__ cx<T> narrow(double2 x) { return cx<T>{T(x.x), T(x.y)}; }
+
+// Sums of the float32 bands: those of x3 (with the float32 factors) and of x1, which memory bounds, in float64,
+// those of x2 in float32.  The rounding of three float32 passes made about half of a pair density's error (rms
+// of the norm, 24^3 1.8e-7 -> 1.6e-7, 48^3 2.1 -> 1.7, 72^3 1.9 -> 1.5, 128^3 2.2 -> 1.8; 128^3 in 32 bands: x3 and
+// x2 112 -> 134 us, x1 88 -> 92; with float64 factors from memory x3 and x2 210 us, 1.62e-7 for 1.64e-7 at 96^3).
 constexpr int kBandAbThreads = 512;
 constexpr int kBq = 4;   // quads per thread: the four share one pass over the line's frequencies
 
@@ -67,23 +74,21 @@ __global__ __launch_bounds__(kBandAbThreads) void k_band_ab(const double2* __res
   for (int task = threadIdx.x; task < W * ng; task += blockDim.x) {
     const int j2 = task / ng, q0 = nq < kBq ? 0 : min((task % ng) * kBq, nq - kBq);
     const int32_t* map = wf_map + ((size_t)j1 * W + j2) * W + rw;   // index by n3
-    V y[kBq][4];
-    points_of_quads<V, kBq>(
+    double2 y[kBq][4];
+    points_of_quads<double2, kBq>(
         rw, q0 == 0,
         [&](int n) {
-          if constexpr (CL) return s_c[j2 * W + rw + n];
+          if constexpr (CL) return widen(s_c[j2 * W + rw + n]);
           const int ig = map[n];
-          if (ig < 0) return V{T(0), T(0)};
-          const double2 v = c[ig];
-          return V{T(v.x), T(v.y)};
+          return ig >= 0 ? c[ig] : double2{0.0, 0.0};
         },
-        [&](int n, int k) { return tab[n * nq + min(q0 + k, nq - 1)]; }, y);
+        [&](int n, int k) { return widen(tab[n * nq + min(q0 + k, nq - 1)]); }, y);
     V* dst = s_t3 + (size_t)j2 * nt + 4 * q0;
 #pragma unroll
     for (int k = 0; k < kBq; ++k)
       if (q0 + k < nq) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) dst[4 * k + a] = y[k][a];
+        for (int a = 0; a < 4; ++a) dst[4 * k + a] = narrow<T>(y[k][a]);
       }
   }
   __syncthreads();
@@ -107,7 +112,7 @@ __global__ __launch_bounds__(kBandAbThreads) void k_band_ab(const double2* __res
 // planes stored in natural x1 order.
 template <typename T>
 __global__ __launch_bounds__(256) void k_band_c(const cx<T>* __restrict__ tB, int rw, int nt, int row,
-                                                const cx<T>* __restrict__ tab, cx<T>* __restrict__ psi) {
+                                                const double2* __restrict__ tab, cx<T>* __restrict__ psi) {
   using V = cx<T>;
   const int W = 2 * rw + 1, nq = nt / 4;
   const int slot = blockIdx.y;
@@ -116,16 +121,16 @@ __global__ __launch_bounds__(256) void k_band_c(const cx<T>* __restrict__ tB, in
   const int p23 = blockIdx.x * blockDim.x + threadIdx.x;
   if (p23 >= plane) return;
   const V* src = tB + ((size_t)slot * W + rw) * plane + p23;   // index by n1
-  V y[kBq][4];
-  points_of_quads<V, kBq>(
-      rw, q0 == 0, [&](int n) { return src[(ptrdiff_t)n * plane]; },
+  double2 y[kBq][4];
+  points_of_quads<double2, kBq>(
+      rw, q0 == 0, [&](int n) { return widen(src[(ptrdiff_t)n * plane]); },
       [&](int n, int k) { return tab[n * nq + min(q0 + k, nq - 1)]; }, y);
   V* dst = psi + (size_t)slot * nt * plane + p23;
 #pragma unroll
   for (int k = 0; k < kBq; ++k)
     if (q0 + k < nq) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a) dst[(size_t)quad_x(4 * (q0 + k) + a, nt) * plane] = y[k][a];
+      for (int a = 0; a < 4; ++a) dst[(size_t)quad_x(4 * (q0 + k) + a, nt) * plane] = narrow<T>(y[k][a]);
     }
 }
 
@@ -164,7 +169,7 @@ hipError_t launch_band_to_real(const Geom& g, const double2* coef, int nrows, co
                  : both <= kLdsBytes ? run(k_band_ab<T, true, false>, allow_lds<T, true, false>(), both)
                                      : run(k_band_ab<T, false, false>, allow_lds<T, false, false>(), slab);
   if (e != hipSuccess) return e;
-  k_band_c<T><<<dim3((nt * row + 255) / 256, nslot, ng), 256, 0, st>>>((const cx<T>*)tB, g.rw, nt, row, tab,
+  k_band_c<T><<<dim3((nt * row + 255) / 256, nslot, ng), 256, 0, st>>>((const cx<T>*)tB, g.rw, nt, row, g.d_pts64,
                                                                        (cx<T>*)psi);
   return hipGetLastError();
 }

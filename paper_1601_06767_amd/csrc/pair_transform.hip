@@ -583,13 +583,18 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
 // their places in the sphere's order in LDS and the row leaves in whole lines (32k pairs, float32: K 15, NG
 // 2000 0.57 ms, 4.8 TB/s; K 25, NG 8000 2.7 ms, 4.6 TB/s; with 8-byte stores to memory and a wait for the map
 // per frequency 0.69 and 3.2); RL false, rows larger than the LDS: straight to memory.
+// Float32 sums of small spheres run in float64 (24^3: 1.6e-7 -> 1.1e-7 of the norm, 11 -> 12 us); larger ones would
+// hold too many registers (RC 12: 5.4 -> 10.6 ms).
 constexpr int kFinishMax = 512;
+template <typename T, int RC> using FinishSum = std::conditional_t<RC <= 4, double, T>;
 template <typename T, int RC, bool RL>
 __global__ __launch_bounds__(kFinishMax) void k_pair_finish(const cx<T>* __restrict__ q,
                                                             const int32_t* __restrict__ chi_map, int ng, int ngp,
-                                                            int nt, int nl, T scale, const T* __restrict__ fac,
+                                                            int nt, int nl, FinishSum<T, RC> scale,
+                                                            const FinishSum<T, RC>* __restrict__ fac,
                                                             cx<T>* __restrict__ m) {
   using V = cx<T>;
+  using A = cx<FinishSum<T, RC>>;
   extern __shared__ __align__(16) unsigned char s_raw[];
   const size_t pair = blockIdx.x;
   const int nq = nt / 4, h = nt / 2;
@@ -597,15 +602,15 @@ __global__ __launch_bounds__(kFinishMax) void k_pair_finish(const cx<T>* __restr
   V* dst = m + pair * ngp;
   V* row = RL ? (V*)s_raw : dst;
   for (int l = threadIdx.x; l < nl; l += blockDim.x) {
-    LineSums<T, RC> s;
+    LineSums<FinishSum<T, RC>, RC> s;
     s.clear();
     const V* p0 = src + l;
     V nx[4] = {p0[0], p0[(size_t)(h / 2) * nl], p0[(size_t)h * nl], p0[(size_t)(h + h / 2) * nl]};
 #pragma unroll 1
     for (int j = 0; j < nq; ++j) {
-      V x[4];
+      A x[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) x[k] = nx[k];
+      for (int k = 0; k < 4; ++k) x[k] = A{nx[k].x, nx[k].y};
       if (j + 1 < nq) {
         nx[0] = p0[(size_t)(j + 1) * nl];
         nx[1] = p0[(size_t)(h - j - 1) * nl];
@@ -620,8 +625,8 @@ __global__ __launch_bounds__(kFinishMax) void k_pair_finish(const cx<T>* __restr
     int ig[2 * RC + 1];   // all at once: one wait, not one per frequency
 #pragma unroll
     for (int n = 0; n < 2 * RC + 1; ++n) ig[n] = chi_map[(size_t)n * nl + l];
-    auto put = [&](int n1, V v) {
-      if (ig[n1 + RC] >= 0) row[ig[n1 + RC]] = V{v.x * scale, v.y * scale};
+    auto put = [&](int n1, A v) {
+      if (ig[n1 + RC] >= 0) row[ig[n1 + RC]] = V{T(v.x * scale), T(v.y * scale)};
     };
     put(0, s.c(0));
 #pragma unroll
@@ -698,8 +703,9 @@ hipError_t run_planes(const Geom& g, const void* psi_v, const void* psi_c, int n
 
 template <typename T, int RC>
 hipError_t run_finish(const Geom& g, const void* q, int npair, void* m, hipStream_t st) {
-  const T scale = T(1.0 / ((double)g.nt * g.nt * g.nt));
-  const T* fac = std::is_same<T, float>::value ? (const T*)g.d_fac32 : (const T*)g.d_fac64;
+  using A = FinishSum<T, RC>;
+  const A scale = A(1.0 / ((double)g.nt * g.nt * g.nt));
+  const A* fac = std::is_same<A, float>::value ? (const A*)g.d_fac32 : (const A*)g.d_fac64;
   const int passes = (g.nl + kFinishMax - 1) / kFinishMax;
   const int threads = ((g.nl + passes - 1) / passes + 63) / 64 * 64;
   auto run = [&](auto f, size_t lds) {
