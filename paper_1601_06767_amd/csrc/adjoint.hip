@@ -13,7 +13,8 @@
 //
 // Without broadening the weights are real and only Re s_p enters: Re s_p = Re m_p^H L m_p with L the lower
 // triangle of chibar + chibar^H, its diagonal halved, so a tile of G needs the G' up to its end only: half of
-// the products (96^3 split-bf16, 32k pairs, NG 4000: 9.0 -> 5.2 ms).  Where the coefficient gradients follow,
+// the products (96^3 split-bf16, 32k pairs, NG 4000: 9.0 -> 7.0 ms with the third part of M, see
+// k_adjoint_bf16x3).  Where the coefficient gradients follow,
 // their full product M (chibar + chibar^H)^T gives Re s_p as well (k_weight_dot): one product where three
 // were formed (72^3, 16k pairs, NG 2000: 28 -> 10 ms).
 #include <algorithm>
@@ -53,7 +54,7 @@ template <> struct AMfma<float> {
 // slices per stage, all of chibar once per pair tile (split-BF16x3 at NG 8000, 32k pairs: L2
 // misses 225 -> 62 GB, 41.1 -> 35.9 ms per launch).  Every other block takes its chibar tiles in
 // descending order: of a lower triangle they differ in length, and a CU that always took the longer
-// one would drift away from the others' stages (NG 8000: 20.5 -> 18.6 ms; NG 4000:
+// one would drift away from the others' stages (with two parts of M, NG 8000: 20.5 -> 18.6 ms; NG 4000:
 // 5.30 -> 5.10).  The grid is rounded up to a multiple of 8; the workgroups past the last tile return at once.
 __device__ __forceinline__ void adj_tile(int t, int npt, int ntg, int* pt, int* tg) {
   constexpr int BP = 8, BG = 4;
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(256) void k_adjoint(const cx<T>* __restrict__ m, in
 // ---------------------------------------------------------------- split-bf16 x3 form
 // M (float) and chibar (rounded to float) are each split into hi = bf16(x) and
 // lo = bf16(x - hi); products hi*hi + hi*lo + lo*hi on MFMA 16x16x32 bf16 with float32
-// accumulation.  Over the doubled inner index k' = [re of 16 G' | im of 16 G']:
+// accumulation, for the lower triangle residual*hi too (M = hi + lo + residual).  Over the doubled inner index k' = [re of 16 G' | im of 16 G']:
 //   Re Y = [mr | mi] [br | -bi]^T,   Im Y = [mr | mi] [bi | br]^T,   b = chibar[G][G'],
 // so both products share the M fragments; the chibar rows in LDS hold [br | bi | -bi].
 // 128 pairs x 128 G per workgroup, 8 waves on a 2 x 4 grid, each 64 pairs x 32 G.
@@ -284,8 +285,11 @@ __global__ __launch_bounds__(256) void k_split_gbar(const double2* __restrict__ 
 }
 
 // The pair densities split the same way, once per chunk: for pair row p and block kb of 16 G',
-// 64 bf16 = hi [re | im] then lo [re | im] (zero beyond ng).
-constexpr int MSPLIT = 64;   // bf16 per (pair row, 16-G' block)
+// hi [re | im] then lo [re | im] (zero beyond ng); PARTS = 3 (for the lower triangle): then the residual
+// bf16(x - hi - lo) [re | im].
+constexpr int MPART = 32;    // bf16 per (pair row, 16-G' block) and part
+constexpr int m_parts(bool lower) { return lower ? 3 : 2; }
+template <int PARTS>
 __global__ void k_split_m(const float2* __restrict__ m, int npair, int ng, int ngp, int nkb,
                           unsigned short* __restrict__ out) {
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;   // (row, block, G' in block)
@@ -300,12 +304,15 @@ __global__ void k_split_m(const float2* __restrict__ m, int npair, int ng, int n
     re = x.x;
     im = x.y;
   }
-  const unsigned short rh = bf16_rne(re), ih = bf16_rne(im);
-  unsigned short* o = out + rb * MSPLIT;
-  o[i] = rh;
-  o[16 + i] = ih;
-  o[32 + i] = bf16_rne(re - bf16_val(rh));
-  o[48 + i] = bf16_rne(im - bf16_val(ih));
+  unsigned short* o = out + rb * (PARTS * MPART);
+#pragma unroll
+  for (int q = 0; q < PARTS; ++q) {
+    const unsigned short rh = bf16_rne(re), ih = bf16_rne(im);
+    o[MPART * q + i] = rh;
+    o[MPART * q + 16 + i] = ih;
+    re -= bf16_val(rh);
+    im -= bf16_val(ih);
+  }
 }
 
 // Both operands are staged straight from their split images into LDS by 16-byte direct loads
@@ -315,21 +322,34 @@ __global__ void k_split_m(const float2* __restrict__ m, int npair, int ng, int n
 // compiler sees that a stage's LDS reads cannot alias the direct loads in flight into the other
 // buffers and does not wait for them; the stage barrier orders LDS only (lds_barrier), so the loads of the next stage stay in
 // flight across it, and each stage waits for its own loads explicitly.  LDS units of one stage: the 128 M rows
-// of 8 pieces (piece c of row r at unit 8 r + (c ^ (r & 7))), then the 128 chibar rows of 12
-// (piece p of row r at UM + 12 r + (p ^ 2 ((r >> 2) & 1))); the XORs give every MFMA fragment
-// read of 16 rows x 4 pieces four accesses per bank group, the minimum.  Rows past npair or
+// of 8 pieces (piece c of row r at unit 8 r + (c ^ (r & 7))) or 12 (at 12 r + (c ^ ((r >> 2) & 3))), then the
+// 128 chibar rows of 12 (piece p of row r at UM + 12 r + (p ^ 2 ((r >> 2) & 1))); the XORs give every MFMA
+// fragment read of 16 rows x 4 pieces four accesses per bank group, the minimum.  Rows past npair or
 // ng load the last valid row: they only feed products that the epilogue drops.
 // One workgroup per CU.  Measured with register staging (the former form), per 32k-pair
 // launch at NG 2000: 5.4 ms converting chibar in every tile, 4.2 ms with it pre-split;
 // capped at 128 registers for a second workgroup it spilled (9.4 ms); stages of 32 G' were
 // no faster (5.6 ms).
-constexpr int UM = BT * 8, UG = BT * 12, UST = UM + UG;   // 16-byte LDS units per stage
-constexpr int UPL = UST / 512;                            // units per lane per stage
-static_assert(UPL * 512 == UST && UM % 64 == 0, "stage units must split into whole wave instructions");
+//
+// LOWER: the lower triangle of chibar + chibar^H, with the residual of M's split as a third part (product
+// residual * hi).  In the full product the rounding of M enters at both rows of an element, here twice at one:
+// without the residual the share of M's rounding in the gradients' error is 1.7 times that of the full product
+// (2.8 times for a Hermitian chibar), the error in all 1.05 (1.2) times; with it 0.9 (1.0).  It takes the launch
+// from 19.6 to 26.7 ms at NG 8000, from 5.2 to 7.0 at NG 4000 (32k pairs).
+template <bool LOWER> struct AdjStage {
+  static constexpr int RM = 4 * m_parts(LOWER);   // 16-byte units of an M row
+  static constexpr int UM = BT * RM, UG = BT * 12, UST = UM + UG;   // units per stage
+  static constexpr int UPL = UST / 512;                             // units per lane per stage
+  static_assert(UPL * 512 == UST && UM % 64 == 0, "stage units must split into whole wave instructions");
+  static __device__ __forceinline__ int swizzle(int r) { return LOWER ? (r >> 2) & 3 : r & 7; }
+};
+template <bool LOWER>
 __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict__ m, int npair, int ng, int ngp,
                                                            const uint4* __restrict__ msplit,
-                                                           const uint4* __restrict__ gsplit, int lower,
+                                                           const uint4* __restrict__ gsplit,
                                                            double2* __restrict__ part) {
+  using P = AdjStage<LOWER>;
+  constexpr int RM = P::RM, UM = P::UM, UST = P::UST, UPL = P::UPL;
   __shared__ __align__(16) uint4 sa[UST];
   __shared__ __align__(16) uint4 sb[UST];
   __shared__ __align__(16) uint4 sc[UST];
@@ -348,18 +368,18 @@ __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict
   const int wr = wave / 4, wc = wave % 4;
   const int li = lane & 15, lg = lane >> 4;
   const int nkb = (ng + BKS - 1) / BKS;
-  const int nke = lower ? min(nkb, (q0 + BT) / BKS) : nkb;   // stages: a lower triangle ends with its tile
+  const int nke = LOWER ? min(nkb, (q0 + BT) / BKS) : nkb;   // stages: a lower triangle ends with its tile
 
   // this lane's source of unit 64 (8 i + wave) + lane, for every stage (block kb adds
-  // 8 kb or 12 kb pieces; the block of 64 units, and so the operand, is wave-uniform)
+  // RM kb or 12 kb pieces; the block of 64 units, and so the operand, is wave-uniform)
   const uint4* src[UPL];
 #pragma unroll
   for (int i = 0; i < UPL; ++i) {
     const int ub = 8 * i + wave;
     const int u = 64 * ub + lane;
     if (ub * 64 < UM) {
-      const int r = u / 8, c = (u % 8) ^ (r & 7);
-      src[i] = msplit + (size_t)min(p0 + r, npair - 1) * nkb * 8 + c;
+      const int r = u / RM, c = (u % RM) ^ P::swizzle(r);
+      src[i] = msplit + (size_t)min(p0 + r, npair - 1) * nkb * RM + c;
     } else {
       const int u2 = u - UM, r = u2 / 12, pc = (u2 % 12) ^ (2 * ((r >> 2) & 1));
       src[i] = gsplit + (size_t)min(q0 + r, ng - 1) * nkb * 12 + pc;
@@ -369,7 +389,7 @@ __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict
 #pragma unroll
     for (int i = 0; i < UPL; ++i) {
       const int ub = 8 * i + wave;
-      const int step = ub * 64 < UM ? 8 : 12;
+      const int step = ub * 64 < UM ? RM : 12;
       __builtin_amdgcn_global_load_lds((const void*)(src[i] + (size_t)kb * step),
                                        (__attribute__((address_space(3))) void*)&buf[64 * ub], 16, 0, 0);
     }
@@ -396,12 +416,13 @@ __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict
     issue(min(kb + 2, nke - 1), next);
     const uint4* sm = cur;
     const uint4* sg = cur + UM;
-    bf16x8 xh[BMI], xl[BMI], reh[BNJ], rel[BNJ], imh[BNJ], iml[BNJ];
+    bf16x8 xh[BMI], xl[BMI], xr[BMI], reh[BNJ], rel[BNJ], imh[BNJ], iml[BNJ];
 #pragma unroll
     for (int i = 0; i < BMI; ++i) {
       const int r = 16 * BMI * wr + 16 * i + li;
-      xh[i] = __builtin_bit_cast(bf16x8, sm[8 * r + (lg ^ (r & 7))]);
-      xl[i] = __builtin_bit_cast(bf16x8, sm[8 * r + ((4 + lg) ^ (r & 7))]);
+      xh[i] = __builtin_bit_cast(bf16x8, sm[RM * r + (lg ^ P::swizzle(r))]);
+      xl[i] = __builtin_bit_cast(bf16x8, sm[RM * r + ((4 + lg) ^ P::swizzle(r))]);
+      if constexpr (LOWER) xr[i] = __builtin_bit_cast(bf16x8, sm[RM * r + ((8 + lg) ^ P::swizzle(r))]);
     }
 #pragma unroll
     for (int j = 0; j < BNJ; ++j) {
@@ -419,9 +440,11 @@ __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict
         cre[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[i], reh[j], cre[i][j], 0, 0, 0);
         cre[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[i], rel[j], cre[i][j], 0, 0, 0);
         cre[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl[i], reh[j], cre[i][j], 0, 0, 0);
+        if constexpr (LOWER) cre[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[i], reh[j], cre[i][j], 0, 0, 0);
         cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[i], imh[j], cim[i][j], 0, 0, 0);
         cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh[i], iml[j], cim[i][j], 0, 0, 0);
         cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl[i], imh[j], cim[i][j], 0, 0, 0);
+        if constexpr (LOWER) cim[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[i], imh[j], cim[i][j], 0, 0, 0);
       }
   };
   issue(0, sa);
@@ -555,15 +578,15 @@ int adjoint_tile(int mode) { return mode == 2 ? BT : AT; }
 
 size_t gbar_split_bytes(int ng) { return (size_t)ng * ((ng + BKS - 1) / BKS) * GSPLIT * sizeof(unsigned short); }
 
-size_t m_split_bytes(int npair, int ng) {
-  return (size_t)npair * ((ng + BKS - 1) / BKS) * MSPLIT * sizeof(unsigned short);
+size_t m_split_bytes(int npair, int ng, bool lower) {
+  return (size_t)npair * ((ng + BKS - 1) / BKS) * m_parts(lower) * MPART * sizeof(unsigned short);
 }
 
-hipError_t launch_split_m(const void* m, int npair, int ng, int ngp, void* msplit, hipStream_t st) {
+hipError_t launch_split_m(const void* m, int npair, int ng, int ngp, bool lower, void* msplit, hipStream_t st) {
   const int nkb = (ng + BKS - 1) / BKS;
   const size_t ne = (size_t)npair * nkb * 16;
-  k_split_m<<<(unsigned)((ne + 255) / 256), 256, 0, st>>>((const float2*)m, npair, ng, ngp, nkb,
-                                                         (unsigned short*)msplit);
+  const auto f = lower ? k_split_m<m_parts(true)> : k_split_m<m_parts(false)>;
+  f<<<(unsigned)((ne + 255) / 256), 256, 0, st>>>((const float2*)m, npair, ng, ngp, nkb, (unsigned short*)msplit);
   return hipGetLastError();
 }
 
@@ -574,8 +597,9 @@ hipError_t launch_adjoint_bf16x3(const void* m, const void* msplit, int npair, i
   k_split_gbar<<<(unsigned)((ng + 63) / 64 * nkb), 256, 0, st>>>(gbar, ng, nkb, lower ? 1 : 0, (unsigned short*)gsplit);
   const int ntg = ngp / BT;
   const int nb = ((npair + BT - 1) / BT) * ntg;
-  k_adjoint_bf16x3<<<(nb + 7) / 8 * 8, 512, 0, st>>>((const float2*)m, npair, ng, ngp, (const uint4*)msplit,
-                                                     (const uint4*)gsplit, lower ? 1 : 0, part);
+  const auto f = lower ? k_adjoint_bf16x3<true> : k_adjoint_bf16x3<false>;
+  f<<<(nb + 7) / 8 * 8, 512, 0, st>>>((const float2*)m, npair, ng, ngp, (const uint4*)msplit, (const uint4*)gsplit,
+                                      part);
   return hipGetLastError();
 }
 

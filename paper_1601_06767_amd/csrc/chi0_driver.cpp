@@ -173,7 +173,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
       size_t ms = 0;
       for (const auto& q : L.pp) {
         gs = std::max(gs, gw::gbar_split_bytes(q.p->geom->g.ng));
-        ms = std::max(ms, gw::m_split_bytes(q.npair, q.p->geom->g.ng));
+        ms = std::max(ms, gw::m_split_bytes(q.npair, q.p->geom->g.ng, !complex_w));
       }
       L.off_gsplit = take(gs);
       L.off_msplit = take(ms);
@@ -692,9 +692,9 @@ gw_status backward_entry(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, i
       if (s != GW_OK) return s;
       GW_HIP(ctx, gw::launch_fill_f64(dx, q.npair, 0.0, ctx->stream));
       GW_HIP(ctx, gw::launch_fill_f64(dn, q.npair, 0.0, ctx->stream));
-      if (L.mode == 2)
-        GW_HIP(ctx, gw::launch_split_m(ws + q.off_m, q.npair, g.ng, g.ngp, ws + L.off_msplit, ctx->stream));
       const bool real_w = !(delta > 0.0);
+      if (L.mode == 2)
+        GW_HIP(ctx, gw::launch_split_m(ws + q.off_m, q.npair, g.ng, g.ngp, real_w, ws + L.off_msplit, ctx->stream));
       for (int iw = 0; iw < nomega; ++iw) {
         const double2* gb = (const double2*)gin + (size_t)iw * g.ng * g.ng;
         int ntg = g.ngp / gw::adjoint_tile(L.mode);

@@ -289,8 +289,8 @@ hipError_t launch_adjoint(const void* m, int npair, int ng, int ngp, const doubl
 // densities split into bf16 row images (m_split_bytes(npair, ng), written by launch_split_m once
 // per chunk), gsplit is scratch of gbar_split_bytes(ng) for chibar split the same way
 size_t gbar_split_bytes(int ng);
-size_t m_split_bytes(int npair, int ng);
-hipError_t launch_split_m(const void* m, int npair, int ng, int ngp, void* msplit, hipStream_t st);
+size_t m_split_bytes(int npair, int ng, bool lower);
+hipError_t launch_split_m(const void* m, int npair, int ng, int ngp, bool lower, void* msplit, hipStream_t st);
 hipError_t launch_adjoint_bf16x3(const void* m, const void* msplit, int npair, int ng, int ngp, const double2* gbar,
                                  bool lower, void* gsplit, double2* part, hipStream_t st);
 // Without broadening only Re s_p enters: lower = true computes it from the lower triangle of chibar + chibar^H
