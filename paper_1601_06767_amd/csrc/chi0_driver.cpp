@@ -152,7 +152,8 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
       q.off_img2 = take(gw::split_image_bytes(q.npair, g.ngp));
     }
     max_psic = std::max(max_psic, (size_t)q.cc * npts * L.csz);
-    max_scr = std::max(max_scr, gw::band_scratch_bytes(g, band_batch(g, L.fp64), L.fp64));
+    const int most = std::max(q.nvs, q.cc);   // bands of one transform call
+    max_scr = std::max(max_scr, gw::band_scratch_bytes(g, std::min(band_batch(g, L.fp64), most), L.fp64));
     max_q = std::max(max_q, (size_t)q.npair * g.q_elems() * L.csz);
     max_part = std::max(max_part, gw::adjoint_partial_bytes(q.npair, g.ngp));
     max_np = std::max(max_np, (size_t)q.npair);
@@ -188,7 +189,7 @@ Layout make_layout(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, int nom
         mb = std::max(mb, (size_t)q.npair * g.ngp * sizeof(double2));
         uc = std::max(uc, (size_t)q.cc * npts * sizeof(double2));
         uv = std::max(uv, (size_t)q.nvs * npts * sizeof(double2));
-        cb = std::max(cb, (size_t)std::max(q.cc, band_batch(g, true)) * g.npw * sizeof(double2));
+        cb = std::max(cb, (size_t)q.cc * g.npw * sizeof(double2));
       }
       L.off_mbar = take(mb);
       L.off_atmp = take(mb);

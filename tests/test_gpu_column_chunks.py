@@ -43,6 +43,17 @@ def test_columns_are_padded_to_eight(setup):
                 assert ws[8, prec] == ws[48, prec]
 
 
+def test_band_scratch_is_for_the_bands_of_the_call(setup):
+    # eight columns beside four valence bands: everything of theirs, the transforms' scratch included, is a
+    # fifth of what forty columns take
+    p, ctx, geom, t, coef, r, ng = setup
+    size = {}
+    for nc in (8, 40):
+        prob = p.make_problem(geom, t(coef(4)), t(np.zeros(4)), t(coef(nc)), t(np.ones(nc)))
+        size[nc] = p.gw_chi0_workspace_size(ctx, [prob], 1, p.GW_FP64)
+    assert 2 * size[8] < size[40], size
+
+
 @pytest.mark.parametrize("nv,nc,cut", [(5, 8, 3), (5, 40, 17), (12, 2735, 1000), (12, 5460, 2728), (20, 1640, 1632)])
 def test_call_equals_sum_of_its_parts(setup, nv, nc, cut):
     import torch
