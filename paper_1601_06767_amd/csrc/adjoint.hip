@@ -241,8 +241,8 @@ constexpr int BT = 128;     // pairs and G per tile
 constexpr int BKS = 16;     // G' per stage
 constexpr int BMI = 4, BNJ = 2;
 
-// chibar split once per call into the LDS image of its rows: for row G and block kb of 16 G',
-// 96 bf16 = hi [re | im | -im] then lo [re | im | -im] (zero beyond ng), so that the tiles
+// chibar split before every launch into the LDS image of its rows: for row G and block kb of
+// 16 G', 96 bf16 = hi [re | im | -im] then lo [re | im | -im] (zero beyond ng), so that the tiles
 // stage chibar with plain 16-byte copies instead of converting it once per pair tile.
 constexpr int GSPLIT = 96;   // bf16 per (row, 16-G' block)
 // lower: the image is that of the lower triangle of chibar + chibar^H, its diagonal halved (see above); its

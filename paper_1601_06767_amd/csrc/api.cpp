@@ -339,8 +339,6 @@ gw_status gw_geom_create(gw_ctx* ctx, const int n_fft[3], const double* cell, co
     for (int j = 0; j < nq; ++j) pts64[(size_t)n * nq + j] = j == 0 ? double2{1.0, quarter(n)} : tw[n * j % nt];
   std::vector<float2> pts32(pts64.size());
   for (size_t i = 0; i < pts64.size(); ++i) pts32[i] = float2{(float)pts64[i].x, (float)pts64[i].y};
-  const size_t npts = pts64.size();
-  pts64.insert(pts64.end(), tw.begin(), tw.end());
   std::vector<double> fac64((size_t)nq * 2 * (hk + 1), 1.0);
   for (int j = 0; j < nq; ++j)
     for (int n = 0; n <= hk; ++n) {
@@ -384,7 +382,6 @@ gw_status gw_geom_create(gw_ctx* ctx, const int n_fft[3], const double* cell, co
   upload((void**)&g.d_fac64, fac64.data(), fac64.size() * sizeof(double));
   upload((void**)&g.d_fac32, fac32.data(), fac32.size() * sizeof(float));
   g.d_rowtab = g.d_chi_map + nchi;
-  g.d_tw64 = g.d_pts64 + npts;
   g.d_amat = g.d_fac32 + nfac;
   (void)hipSetDevice(prev);
   gg->g = g;

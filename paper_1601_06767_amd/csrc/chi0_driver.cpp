@@ -657,8 +657,8 @@ gw_status backward_entry(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, i
     for (int i = 0; i < nprob; ++i)
       if (probs && probs[i].geom && !gw::coef_grad_offered(probs[i].geom->g.nd, probs[i].geom->g.K))
         return gw::fail(ctx, GW_EUNSUPPORTED,
-                        "coefficient gradients need a compiled pair-transform instance for N = " +
-                            std::to_string(probs[i].geom->g.nd) + ", K = " + std::to_string(probs[i].geom->g.K));
+                        "coefficient gradients are not offered for N = " + std::to_string(probs[i].geom->g.nd) +
+                            ", K = " + std::to_string(probs[i].geom->g.K));
   DeviceScope dev(ctx->device);
   st = check_values(ctx, probs, nprob);
   if (st != GW_OK) return st;

@@ -59,10 +59,4 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Wrap n into [0, m).
-__host__ __device__ __forceinline__ int wrap(int n, int m) {
-  int r = n % m;
-  return r < 0 ? r + m : r;
-}
-
 }  // namespace gw

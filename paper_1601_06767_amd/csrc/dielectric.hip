@@ -465,10 +465,7 @@ __device__ __forceinline__ double2 opget(const double2* x, int ld, int r, int k,
 
 __global__ __launch_bounds__(256) void k_zgemm(int m, int n, int kd, double2 alpha, const double2* __restrict__ A,
                                                int lda, int opa, const double2* __restrict__ B, int ldb, int opb,
-                                               double2 beta, double2* __restrict__ C, int ldc, size_t ws) {
-  A = slice(A, ws);   // a batch (blockIdx.y): the three operands advance by ws bytes
-  B = slice(B, ws);
-  C = slice(C, ws);
+                                               double2 beta, double2* __restrict__ C, int ldc) {
   __shared__ double2 sA[ZK][ZT + 1];   // sA[k][row]
   __shared__ double2 sB[ZK][ZT + 1];   // sB[k][col]
   const int tiles_n = (n + ZT - 1) / ZT;
@@ -546,7 +543,6 @@ __global__ __launch_bounds__(256) void k_zgemm(int m, int n, int kd, double2 alp
         }
       }
 }
-
 
 // The same for A by rows, n a multiple of 64, k of 16 and beta = 0, alpha = 1 (the products with pair
 // densities, padded with zeros): both operands by direct loads into two buffers, the next 16 k under the
@@ -1049,7 +1045,7 @@ hipError_t launch_zgemm_op(int m, int n, int k, double2 alpha, const double2* A,
     f<<<(tiles + 7) / 8 * 8, 256, 0, st>>>(m, n, k, A, lda, B, ldb, C, ldc);
     return hipGetLastError();
   }
-  k_zgemm<<<tiles, 256, 0, st>>>(m, n, k, alpha, A, lda, opa, B, ldb, opb, beta, C, ldc, 0);
+  k_zgemm<<<tiles, 256, 0, st>>>(m, n, k, alpha, A, lda, opa, B, ldb, opb, beta, C, ldc);
   return hipGetLastError();
 }
 

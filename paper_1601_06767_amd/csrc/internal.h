@@ -39,7 +39,7 @@ struct gw_ctx {
   std::vector<Mark> marks;
   double stage_ms[gw::kNumStages] = {};
   long long stage_n[gw::kNumStages] = {};
-  // launch shapes chosen by gw_tune, by problem shape: (pair-kernel residency, pair-range splits)
+  // launch shapes chosen by gw_tune, by problem shape: (pair-kernel number, pair-range splits)
   std::map<std::string, std::pair<int, int>> tune;
   // graph mode: captured launch sequences of gw_chi0_build, by argument signature
   bool graph = false;
@@ -118,7 +118,6 @@ struct Geom {
   // factors of the folded transforms (fold.h); j < nt / 4 counts the quads
   double2* d_pts64 = nullptr;    // [n <= max(rw, rchi)][j] = (cos, sin)(2 pi n j / nt), quad 0: (1, cos or sin(n pi/2))
   float2* d_pts32 = nullptr;
-  double2* d_tw64 = nullptr;     // exp(+2 pi i k / nt), k < nt (behind d_pts64)
   double* d_fac64 = nullptr;     // [j][n <= rchi] cos, then sin; quad 0: cos or sin(n pi/2)
   float* d_fac32 = nullptr;
   float* d_amat = nullptr;       // [j][32] the same as slots of the MFMA forms (behind d_fac32)
@@ -171,7 +170,7 @@ hipError_t launch_gpp_coh_sum(const void* part, size_t part_bytes, int ne, int n
 // plasmon-pole extension (gpp.hip)
 hipError_t launch_gpp(const void* eps0, int ng, const double* kvec, const int32_t* gvec, const void* rho, int half,
                       const double* omega, int nomega, double eta, void* modes, void* out, hipStream_t st);
-constexpr int kPairVariants = 7;   // pair-kernel numbers that a tuned shape may name (all the one form)
+constexpr int kPairVariants = 7;   // largest pair-kernel number that gw_tune_set takes (every number is the one form)
 // Pair planes: Q[pair][x1][line] for pairs (v, c), v < nvs (multiple of 4), c < ncs (multiple of 8),
 // pair = v * ncs + c.
 template <typename T>
