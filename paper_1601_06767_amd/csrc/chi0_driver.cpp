@@ -319,18 +319,17 @@ gw_status enqueue_build(gw_ctx* ctx, const gw_chi0_problem* probs, int nprob, in
   // ev_ready[b] (main) -> contraction j (side) -> ev_free[b] (side) -> transforms of
   // chunk j + 2 (main), and ev_join before the finalisation.
   // Overlap pays where the contraction leaves registers for a pair-kernel workgroup on the
-  // same CU and is small beside the transforms: the split-BF16x3 form at one 512-thread
-  // workgroup per CU (146 VGPRs) with dielectric spheres up to 2048 (measured 214.7 ms per
-  // 72^3 / 512k-pair / NG 2000 step, against 221.4 ms without overlap, where the contraction
-  // alone runs two workgroups per CU at 128 VGPRs).  With larger spheres the contraction
-  // alone is the faster choice (96^3 / NG 4000 grouped step: 1.599 s alone, 1.632 s
-  // overlapped).  The float64 and float32 contractions fill the register file, so the next
-  // chunk's transforms queue behind them (no gain measured; capping the contraction at one
-  // workgroup per CU made float64 slower, 519 -> 558 ms).  The static split-BF16x3 build reads
-  // row images with workgroups that fill each CU's LDS (measured with two 80 KB workgroups per
-  // CU; the current form takes 120 KB in one), which leave nothing for the transforms: no gain
-  // either (72^3, 8 chunks of 32k pairs: 101.2 ms overlapped, 100.9 alone; 128^3, 4 chunks:
-  // 473 / 475 ms), so overlap is left to the register-staged form.
+  // same CU: the register-staged split-BF16x3 form of builds with several jobs, at one 512-thread
+  // workgroup per CU (146 VGPRs) against two at 128 VGPRs when it runs alone.  ms per build, alone /
+  // overlapped: 72^3, 128 x 1000, NG 2000, four frequencies 95.7 / 82.5, two 54.5 / 47.0; NG 1000,
+  // 128 x 2000 43.8 / 39.1; 48^3, NG 700 15.5 / 13.6.  The rule ends at spheres of 2048, as far as it was
+  // first measured; 96^3, 128 x 1000, NG 4000 would gain too (208 / 188).  The float64 and
+  // float32 contractions fill the register file, so the next chunk's transforms queue behind
+  // them (no gain measured; capping the contraction at one workgroup per CU made float64 slower,
+  // 519 -> 558 ms).  The static split-BF16x3 build reads row images with workgroups that fill
+  // each CU's LDS (120 KB in one), which leave nothing for the transforms: no gain either
+  // (measured with two 80 KB workgroups per CU: 72^3, 8 chunks of 32k pairs 101.2 ms overlapped,
+  // 100.9 alone; 128^3, 4 chunks 473 / 475 ms), so overlap is left to the register-staged form.
   int max_ngp = 0;
   for (const ProbPlan& q : L.pp) max_ngp = std::max(max_ngp, q.p->geom->g.ngp);
   const bool ovl =
