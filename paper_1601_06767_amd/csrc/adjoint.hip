@@ -13,7 +13,7 @@
 //
 // Without broadening the weights are real and only Re s_p enters: Re s_p = Re m_p^H L m_p with L the lower
 // triangle of chibar + chibar^H, its diagonal halved, so a tile of G needs the G' up to its end only: half of
-// the products (96^3 split-bf16, 32k pairs, NG 4000: 9.0 -> 7.0 ms with the third part of M, see
+// the products (96^3 split-bf16, 32k pairs, NG 4000: 9.0 -> 6.8 ms with the third part of M, see
 // k_adjoint_bf16x3).  Where the coefficient gradients follow,
 // their full product M (chibar + chibar^H)^T gives Re s_p as well (k_weight_dot): one product where three
 // were formed (72^3, 16k pairs, NG 2000: 28 -> 10 ms).
@@ -322,7 +322,7 @@ __global__ void k_split_m(const float2* __restrict__ m, int npair, int ng, int n
 // compiler sees that a stage's LDS reads cannot alias the direct loads in flight into the other
 // buffers and does not wait for them; the stage barrier orders LDS only (lds_barrier), so the loads of the next stage stay in
 // flight across it, and each stage waits for its own loads explicitly.  LDS units of one stage: the 128 M rows
-// of 8 pieces (piece c of row r at unit 8 r + (c ^ (r & 7))) or 12 (at 12 r + (c ^ ((r >> 2) & 3))), then the
+// of 8 pieces (piece c of row r at unit 8 r + (c ^ (r & 7))) or 12 (at 12 r + (c ^ 2 ((r >> 2) & 1))), then the
 // 128 chibar rows of 12 (piece p of row r at UM + 12 r + (p ^ 2 ((r >> 2) & 1))); the XORs give every MFMA
 // fragment read of 16 rows x 4 pieces four accesses per bank group, the minimum.  Rows past npair or
 // ng load the last valid row: they only feed products that the epilogue drops.
@@ -335,13 +335,13 @@ __global__ void k_split_m(const float2* __restrict__ m, int npair, int ng, int n
 // residual * hi).  In the full product the rounding of M enters at both rows of an element, here twice at one:
 // without the residual the share of M's rounding in the gradients' error is 1.7 times that of the full product
 // (2.8 times for a Hermitian chibar), the error in all 1.05 (1.2) times; with it 0.9 (1.0).  It takes the launch
-// from 19.6 to 26.7 ms at NG 8000, from 5.2 to 7.0 at NG 4000 (32k pairs).
+// from 18.9 to 25.2 ms at NG 8000, from 5.2 to 6.8 at NG 4000 (32k pairs).
 template <bool LOWER> struct AdjStage {
   static constexpr int RM = 4 * m_parts(LOWER);   // 16-byte units of an M row
   static constexpr int UM = BT * RM, UG = BT * 12, UST = UM + UG;   // units per stage
   static constexpr int UPL = UST / 512;                             // units per lane per stage
   static_assert(UPL * 512 == UST && UM % 64 == 0, "stage units must split into whole wave instructions");
-  static __device__ __forceinline__ int swizzle(int r) { return LOWER ? (r >> 2) & 3 : r & 7; }
+  static __device__ __forceinline__ int swizzle(int r) { return LOWER ? 2 * ((r >> 2) & 1) : r & 7; }
 };
 template <bool LOWER>
 __global__ __launch_bounds__(512) void k_adjoint_bf16x3(const float2* __restrict__ m, int npair, int ng, int ngp,
