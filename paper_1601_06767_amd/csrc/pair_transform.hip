@@ -583,6 +583,9 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
 // their places in the sphere's order in LDS and the row leaves in whole lines (32k pairs, float32: K 15, NG
 // 2000 0.57 ms, 4.8 TB/s; K 25, NG 8000 2.7 ms, 4.6 TB/s; with 8-byte stores to memory and a wait for the map
 // per frequency 0.69 and 3.2); RL false, rows larger than the LDS: straight to memory.
+// Quad 0 stands before the loop and the map is read for eight frequencies at a time: with both in one piece the
+// larger spheres took twice the registers, up to spills (float64, us: 2048 pairs, RC 12 593 -> 303; 4096 pairs, RC
+// 13 519 -> 466, RC 15 2226 -> 1060).
 // Float32 sums of small spheres run in float64 (24^3: 1.6e-7 -> 1.1e-7 of the norm, 11 -> 12 us); larger ones would
 // hold too many registers (RC 12: 5.4 -> 10.6 ms).
 constexpr int kFinishMax = 512;
@@ -606,33 +609,47 @@ __global__ __launch_bounds__(kFinishMax) void k_pair_finish(const cx<T>* __restr
     s.clear();
     const V* p0 = src + l;
     V nx[4] = {p0[0], p0[(size_t)(h / 2) * nl], p0[(size_t)h * nl], p0[(size_t)(h + h / 2) * nl]};
-#pragma unroll 1
-    for (int j = 0; j < nq; ++j) {
-      A x[4];
+    A x[4];
+    auto next = [&](int j) {   // quad j's planes come in under the sums of the one before
 #pragma unroll
       for (int k = 0; k < 4; ++k) x[k] = A{nx[k].x, nx[k].y};
-      if (j + 1 < nq) {
-        nx[0] = p0[(size_t)(j + 1) * nl];
-        nx[1] = p0[(size_t)(h - j - 1) * nl];
-        nx[2] = p0[(size_t)(h + j + 1) * nl];
-        nx[3] = p0[(size_t)(nt - j - 1) * nl];
+      if (j < nq) {
+        nx[0] = p0[(size_t)j * nl];
+        nx[1] = p0[(size_t)(h - j) * nl];
+        nx[2] = p0[(size_t)(h + j) * nl];
+        nx[3] = p0[(size_t)(nt - j) * nl];
       }
-      if (j == 0)
-        s.add0(fold_quad0(x), fac);
-      else
-        s.add(fold_quad(x), fac + (size_t)j * (2 * RC + 2));
-    }
-    int ig[2 * RC + 1];   // all at once: one wait, not one per frequency
-#pragma unroll
-    for (int n = 0; n < 2 * RC + 1; ++n) ig[n] = chi_map[(size_t)n * nl + l];
-    auto put = [&](int n1, A v) {
-      if (ig[n1 + RC] >= 0) row[ig[n1 + RC]] = V{T(v.x * scale), T(v.y * scale)};
     };
-    put(0, s.c(0));
+    next(1);
+    s.add0(fold_quad0(x), fac);
+#pragma unroll 1
+    for (int j = 1; j < nq; ++j) {
+      next(j + 1);
+      s.add(fold_quad(x), fac + (size_t)j * (2 * RC + 2));
+    }
+    // the map of up to kGroup frequencies at once: one wait, not one per frequency
+    constexpr int kGroup = 8;
 #pragma unroll
-    for (int n = 1; n <= RC; ++n) {
-      put(n, plus_i(s.c(n), s.s(n)));
-      put(-n, minus_i(s.c(n), s.s(n)));
+    for (int n0 = 0; n0 <= RC; n0 += kGroup) {
+      int ig[2 * kGroup];
+#pragma unroll
+      for (int k = 0; k < 2 * kGroup; ++k) {
+        const int n = n0 + k / 2;
+        ig[k] = n <= RC && (n > 0 || k == 0) ? chi_map[(size_t)(RC + (k % 2 ? -n : n)) * nl + l] : -1;
+      }
+      if constexpr (RC > 10) asm volatile("" ::: "memory");   // few of the results in registers at a time
+      auto put = [&](int k, A v) {
+        if (ig[k] >= 0) row[ig[k]] = V{T(v.x * scale), T(v.y * scale)};
+      };
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        const int n = n0 + k;
+        if (n == 0) put(0, s.c(0));
+        if (n > 0 && n <= RC) {
+          put(2 * k, plus_i(s.c(n), s.s(n)));
+          put(2 * k + 1, minus_i(s.c(n), s.s(n)));
+        }
+      }
     }
   }
   if constexpr (RL) {
