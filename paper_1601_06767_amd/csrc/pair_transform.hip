@@ -381,9 +381,12 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes_mfma(const float
 //
 // Shape of a workgroup.  HS: waves that share a line's x3 quads (partial sums added in LDS);
 // QS: quads of x2 rows per step; NM: largest grid (the LDS row buffers).
-template <typename T, int RC, int HS_, int QS_, int TV_, int TC_, int NM_, int MINW_>
+// AL: the partial sums lie where the step's rows were, one set per share, and the next step's rows are loaded
+// after them: half the LDS, for two workgroups per CU or for twice the row quads in one.
+template <typename T, int RC, int HS_, int QS_, int TV_, int TC_, int NM_, int MINW_, bool AL_ = false>
 struct PlaneShape {
   static constexpr int HS = HS_, QS = QS_, TV = TV_, TC = TC_, NM = NM_, MINW = MINW_;
+  static constexpr bool AL = AL_;
   static constexpr int K = 2 * RC + 1;
   static constexpr int NP = TV * TC;               // pairs
   static constexpr int PG = NP / 16;               // waves per row quad and half: 16 pairs x 4 rows
@@ -392,11 +395,14 @@ struct PlaneShape {
   static constexpr int PADE = 16 / (int)sizeof(cx<T>);   // row padding (complex values): odd 16-byte units
   // row buffer: per band its QS quads of rows and one 16-byte unit (an odd stride between bands)
   static constexpr int NU = (TC + TV) * (QS * 4 * (NM + PADE) / PADE + 1);
-  static constexpr int NZ = QS * NP * PS;
-  static constexpr size_t lds = (size_t)NU * 16 + (size_t)NZ * sizeof(cx<T>);
+  static constexpr int NB = AL ? HS : 1;           // sets of partial sums
+  static constexpr int NZ = NB * QS * NP * PS;
+  static constexpr size_t rows = (size_t)NU * 16, sums = (size_t)NZ * sizeof(cx<T>);
+  static constexpr size_t lds = AL ? std::max(rows, sums) : rows + sums;
   static constexpr int NITEM = NP * K;
   static constexpr int IPL = (NITEM + NT - 1) / NT;
   static_assert(lds <= 160 * 1024, "planes workgroup exceeds the LDS");
+  static_assert(HS == 1 || HS == 2, "shares of a line");
 };
 
 template <typename T, int RC, typename P>
@@ -407,8 +413,10 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
   using V = cx<T>;
   constexpr int K = P::K, NT = P::NT, TV = P::TV, TC = P::TC, HS = P::HS, QS = P::QS, PS = P::PS;
   constexpr int EPU = P::PADE;   // complex values per 16-byte unit
-  __shared__ __align__(16) uint4 s_u[P::NU];   // [band: TC columns, TV valence][quad][t][row], band stride odd
-  __shared__ __align__(16) V s_z[P::NZ];   // [quad][pair][t][n3]
+  // [band: TC columns, TV valence][quad][t][row], band stride odd
+  __shared__ __align__(16) uint4 s_u[P::AL ? P::lds / 16 : P::NU];
+  __shared__ __align__(16) V s_z0[P::AL ? 1 : P::NZ];
+  V* s_z = P::AL ? (V*)s_u : s_z0;   // [set][quad][pair][t][n3]
 
   int x1, c0, v0;
   if (!plane_item(blockIdx.x / 8, nt, ncs / TC, nvs / TV, x1, c0, v0)) return;
@@ -508,8 +516,9 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
         sm.add(fold_quad(p), f);
       }
     }
-    V* z = s_z + (qs * P::NP + pair) * PS + t * K + RC;
-    if (HS == 1 || hf == 1) {
+    V* z = s_z + (((P::AL ? hf : 0) * QS + qs) * P::NP + pair) * PS + t * K + RC;
+    if constexpr (P::AL) lds_barrier();   // every wave is done with the rows
+    if (HS == 1 || P::AL || hf == 1) {
       if (live) {
         z[0] = sm.c(0);
 #pragma unroll
@@ -520,8 +529,9 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
       }
     }
     lds_barrier();   // every wave is done with the rows
-    if (st + 1 < nstep) issue(st + 1);
-    if constexpr (HS == 2) {
+    if constexpr (!P::AL)
+      if (st + 1 < nstep) issue(st + 1);
+    if constexpr (HS == 2 && !P::AL) {
       if (live && hf == 0) {
         z[0] = cadd(z[0], sm.c(0));
 #pragma unroll
@@ -543,13 +553,23 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
         for (int r = 0; r < P::IPL; ++r) {
           const int it = min(tid + NT * r, P::NITEM - 1);
           const V* y = s_z + (k * P::NP + it / K) * PS + it % K;
-          const V p[4] = {y[0], y[K], y[2 * K], y[3 * K]};
+          V p[4] = {y[0], y[K], y[2 * K], y[3 * K]};
+#pragma unroll
+          for (int b = 1; b < P::NB; ++b) {
+            const V* yb = y + b * QS * P::NP * PS;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) p[a] = cadd(p[a], yb[a * K]);
+          }
           if (kFirst && k == 0)
             qa[r].add0(fold_quad0(p), f);
           else
             qa[r].add(fold_quad(p), f);
         }
       }
+    }
+    if constexpr (P::AL) {
+      lds_barrier();   // every wave is done with the sums
+      if (st + 1 < nstep) issue(st + 1);
     }
   };
   issue(0);
@@ -694,10 +714,19 @@ hipError_t run_mfma(const Geom& g, const void* psi_v, const void* psi_c, int nvs
 // workgroups of eight waves 2.5).  From RC = 8 a slot pair has twice the accumulators: four row quads per
 // wave, two waves per SIMD, one workgroup of eight waves per CU over a fixed grid: RC 9 on 60^3 8.1 ms
 // (before 10.3; workgroups of four waves 8.8), RC 12 on 80^3 16.2 ms (before 22; 17.9).
-// float64: four waves, half a line per lane; RC 7 on 44^3 4.7 ms, RC 9 on 60^3 20.3 (one wave per SIMD
-// beyond RC 7).  Up to RC 4 and 32 points the row buffers are half as long and the registers suffice for
-// three waves per SIMD (24^3,
-// RC 4 on 20^3, 3840 pairs: 74 us, 93 with two).
+// float64: half a line per lane, at most 256 registers per lane for two waves per SIMD.
+// Up to RC 7: workgroups of four waves, two per CU; RC 7 on 44^3 4.6 ms.  The rows of more than 64 points leave no
+// room for the sums beside them, so these take the rows' place (4096 pairs, RC 7 on 72 points 3.35 -> 2.12 ms, RC 5
+// on 68 2.78 -> 1.76).  Up to 64 points the next rows load under the sums.
+// Up to RC 4 and 32 points the row buffers are half as long and the registers suffice for three waves per SIMD
+// (24^3, RC 4 on 20^3, 3840 pairs: 74 us, 93 with two).
+// RC 8 and 9: 32 pairs need two of stage 2's sums per lane, more than two waves' registers; 16 pairs and four (beyond
+// 76 points three) row quads per step need one, one workgroup of eight (six) waves per CU, the sums in the rows'
+// place: RC 9 on 60^3 16.6 ms (one wave per SIMD with 32 pairs 19.9); 4096 pairs, RC 8 on 68 points 2.82 (3.43), RC 9
+// on 72 3.24 (3.89); 2048 pairs, RC 9 on 96 4.17 (4.21), on 104 5.14 (6.61).
+// From RC 10 one wave per SIMD.  From RC 12 32 pairs' sums are more than its registers too: 16 pairs and two row
+// quads, as far as the LDS allows (4096 pairs, RC 15 on 48 points 7.5 -> 2.46 ms, on 76 19.4 -> 7.0; RC 12 on 64 5.2 ->
+// 4.0, 2048 pairs on 96 6.7 -> 5.4); RC 10 and 11 fit with 32.
 template <typename T, int RC>
 hipError_t run_planes(const Geom& g, const void* psi_v, const void* psi_c, int nvs, int ncs, void* q, hipStream_t st) {
   if constexpr (std::is_same<T, float>::value) {
@@ -713,8 +742,20 @@ hipError_t run_planes(const Geom& g, const void* psi_v, const void* psi_c, int n
     if constexpr (RC <= 7) {
       if (g.nt <= 64)
         return run_shape<T, RC, PlaneShape<T, RC, 2, 1, 4, 8, 64, 2>>(g, psi_v, psi_c, nvs, ncs, q, st);
+      return run_shape<T, RC, PlaneShape<T, RC, 2, 1, 4, 8, 104, 2, true>>(g, psi_v, psi_c, nvs, ncs, q, st);
     }
-    return run_shape<T, RC, PlaneShape<T, RC, 2, 1, 4, 8, 128, 1>>(g, psi_v, psi_c, nvs, ncs, q, st);
+    if constexpr (RC == 8 || RC == 9) {
+      if (g.nt <= 76)
+        return run_shape<T, RC, PlaneShape<T, RC, 2, 4, 4, 4, 76, 2, true>>(g, psi_v, psi_c, nvs, ncs, q, st);
+      return run_shape<T, RC, PlaneShape<T, RC, 2, 3, 4, 4, 104, 2, true>>(g, psi_v, psi_c, nvs, ncs, q, st);
+    }
+    if constexpr (RC >= 12) {
+      constexpr int nm = RC == 12 ? 104 : RC == 15 ? 88 : 96;
+      if (g.nt <= nm)
+        return run_shape<T, RC, PlaneShape<T, RC, 2, 2, 4, 4, nm, 1>>(g, psi_v, psi_c, nvs, ncs, q, st);
+    }
+    if constexpr (RC >= 10)
+      return run_shape<T, RC, PlaneShape<T, RC, 2, 1, 4, 8, 128, 1>>(g, psi_v, psi_c, nvs, ncs, q, st);
   }
 }
 
