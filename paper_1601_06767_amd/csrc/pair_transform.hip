@@ -601,7 +601,7 @@ __global__ __launch_bounds__(P::NT, P::MINW) void k_pair_planes(const cx<T>* __r
 // One workgroup per pair, one thread per line (n2, n3) that holds a G of the sphere.  HBM-bound:
 // Q is read once, the next quad's planes in flight while the current one is summed.  The frequencies go to
 // their places in the sphere's order in LDS and the row leaves in whole lines (32k pairs, float32: K 15, NG
-// 2000 0.57 ms, 4.8 TB/s; K 25, NG 8000 2.7 ms, 4.6 TB/s; with 8-byte stores to memory and a wait for the map
+// 2000 0.57 ms, 4.8 TB/s; K 25, NG 8000 2.42 ms, 5.1 TB/s; with 8-byte stores to memory and a wait for the map
 // per frequency 0.69 and 3.2); RL false, rows larger than the LDS: straight to memory.
 // Quad 0 stands before the loop and the map is read for eight frequencies at a time: with both in one piece the
 // larger spheres took twice the registers, up to spills (float64, us: 2048 pairs, RC 12 593 -> 303; 4096 pairs, RC
